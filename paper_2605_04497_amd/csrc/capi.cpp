@@ -284,6 +284,24 @@ std::vector<ShortRow<T>> short_rows(const std::vector<PathHdr>& hdr,
   return out;
 }
 
+// Allocate the grouped walk's tables for n short rows.
+void short_walk(size_t n, hipStream_t s, ShortWalk& w) {
+  if (n == 0) return;
+  auto alloc = [&](size_t bytes) {
+    void* p = nullptr;
+    const hipError_t e = device_alloc(&p, bytes, s, false);
+    if (e != hipSuccess) {
+      (void)hipStreamSynchronize(s);  // earlier uploads may still read host vectors
+      check_hip(e, "hipMalloc");
+    }
+    return p;
+  };
+  w.row32 = (WalkRow<float>*)alloc(n * sizeof(WalkRow<float>));
+  w.row64 = (WalkRow<double>*)alloc(n * sizeof(WalkRow<double>));
+  w.coef32 = (float*)alloc(n * kShortCoef * sizeof(float));
+  w.coef64 = (double*)alloc(n * kShortCoef * sizeof(double));
+}
+
 void keep_trees(const qts_tree_arrays& t, qts_ensemble::Trees& k) {
   const int64_t n = t.n_trees > 0 ? t.tree_offsets[t.n_trees] : 0;
   k.off.assign(t.tree_offsets, t.tree_offsets + (t.n_trees + 1));
@@ -359,7 +377,9 @@ void free_device(DeviceTable& d) {
                   d.mhdr,   d.mfeat,   d.mlo,     d.mhi,     d.mb32,    d.mcb32,
                   d.mb64,   d.mcb64,   d.side,    d.pr_side, d.share,   d.mshare,
                   d.lfeat,  d.segs,    d.seg_feat, d.mlfeat, d.msegs,  d.mseg_feat,
-                  d.srow32, d.srow64,  d.msrow32, d.msrow64};
+                  d.srow32, d.srow64,  d.msrow32, d.msrow64,
+                  d.walk.row32, d.walk.row64, d.walk.coef32, d.walk.coef64,
+                  d.mwalk.row32, d.mwalk.row64, d.mwalk.coef32, d.mwalk.coef64};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   d = DeviceTable{};
@@ -373,6 +393,8 @@ void build_nodes(DeviceTable& d) {
     d.n32.w[m] = (float)w[m];
     d.n64.t[m] = t[m];
     d.n64.w[m] = w[m];
+    d.n64.r[m] = -1.0 / s[m];
+    d.n32.r[m] = (float)d.n64.r[m];
     // the FP32 short-row walks take the rule as instruction literals
     if (d.n32.t[m] != rule8_t32(m) || d.n32.w[m] != rule8_w32(m))
       fail(QTS_E_UNSUPPORTED, "the FP32 8-node rule differs from the kernels' constants");
@@ -385,6 +407,8 @@ void build_nodes(DeviceTable& d) {
       f32.w[m] = m < n ? (float)w[m] : 0.f;
       f64.t[m] = m < n ? t[m] : 0.0;
       f64.w[m] = m < n ? w[m] : 0.0;
+      f32.r[m] = 0.f;
+      f64.r[m] = 0.0;
     }
   };
   rule(4, d.n32_4, d.n64_4);
@@ -1048,6 +1072,11 @@ int qts_load_ensemble_grouped(const qts_tree_arrays* trees, const int32_t* tree_
         d.srow64 = upload(r64, s);
         d.msrow32 = upload(m32, s);
         d.msrow64 = upload(m64, s);
+        short_walk(r64.size(), s, d.walk);
+        short_walk(m64.size(), s, d.mwalk);
+        const PathArrays plain = plain_arrays(d, h), merged = merged_arrays(d, h);
+        for (const Bucket& bk : h.buckets) launch_short_walk(plain, bk, d.n64, s);
+        for (const Bucket& bk : h.mbuckets) launch_short_walk(merged, bk, d.n64, s);
         check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
       }
       d.leaf_val = upload(h.leaf_value, s);

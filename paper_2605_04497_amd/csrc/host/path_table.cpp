@@ -415,14 +415,18 @@ HostTable build_host_table(const qts_tree_arrays& t, int32_t F, int32_t n_groups
   h.mshare = prefix_share(h.mhdr, h.mfeat, h.mlo, h.mhi, h.mb);
   // the rows of capacity-8 buckets, numbered in bucket order, index the
   // short-row records of each table
-  for (std::vector<Bucket>* bks : {&h.buckets, &h.mbuckets}) {
+  auto number_short = [](std::vector<Bucket>& bks, const std::vector<PathHdr>& hdr) {
     int32_t n = 0;
-    for (Bucket& bk : *bks)
+    for (Bucket& bk : bks)
       if (bk.dmax == 8) {
         bk.srow_begin = n;
         n += bk.path_end - bk.path_begin;
+        for (int32_t p = bk.path_begin; p < bk.path_end; ++p)
+          bk.top = std::max(bk.top, hdr[(size_t)p].d - 4);
       }
-  }
+  };
+  number_short(h.buckets, h.hdr);
+  number_short(h.mbuckets, h.mhdr);
   if (wide_features(F)) {
     h.compact = build_compact(h.hdr, h.feat, h.buckets, F);
     h.mcompact = build_compact(h.mhdr, h.mfeat, h.mbuckets, F);

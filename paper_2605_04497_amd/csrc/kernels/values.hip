@@ -516,6 +516,290 @@ __device__ __forceinline__ void values_rows_shared(
   }
 }
 
+// A select by a lane mask held in scalar registers (one bit per lane): b
+// where the lane's bit is set, else a.
+__device__ __forceinline__ float pick(uint64_t mask, float a, float b) {
+  float r;
+  asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(mask));
+  return r;
+}
+__device__ __forceinline__ double pick(uint64_t mask, double a, double b) {
+  const float lo = pick(mask, __int_as_float(__double2loint(a)), __int_as_float(__double2loint(b)));
+  const float hi = pick(mask, __int_as_float(__double2hiint(a)), __int_as_float(__double2hiint(b)));
+  return __hiloint2double(__float_as_int(hi), __float_as_int(lo));
+}
+
+// The same with -a in place of a.
+__device__ __forceinline__ float pick_neg(uint64_t mask, float a, float b) {
+  float r;
+  asm("v_cndmask_b32 %0, -%1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(mask));
+  return r;
+}
+__device__ __forceinline__ double pick_neg(uint64_t mask, double a, double b) {
+  const float lo = pick(mask, __int_as_float(__double2loint(a)), __int_as_float(__double2loint(b)));
+  const float hi =
+      pick_neg(mask, __int_as_float(__double2hiint(a)), __int_as_float(__double2hiint(b)));
+  return __hiloint2double(__float_as_int(hi), __float_as_int(lo));
+}
+
+typedef float acc_v4 __attribute__((ext_vector_type(4)));
+
+// acc[i] += sum_m A[4 (8 G + m) + i] H[m] per lane: block 8 G + m of the
+// 4x4x1 product's A operand, broadcast to all 16 blocks of four samples.
+template <int G>
+__device__ __forceinline__ acc_v4 node_sums4(float A, const float (&H)[8], acc_v4 acc) {
+  acc = __builtin_amdgcn_mfma_f32_4x4x1f32(A, H[0], acc, 4, 8 * G + 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_4x4x1f32(A, H[1], acc, 4, 8 * G + 1, 0);
+  acc = __builtin_amdgcn_mfma_f32_4x4x1f32(A, H[2], acc, 4, 8 * G + 2, 0);
+  acc = __builtin_amdgcn_mfma_f32_4x4x1f32(A, H[3], acc, 4, 8 * G + 3, 0);
+  acc = __builtin_amdgcn_mfma_f32_4x4x1f32(A, H[4], acc, 4, 8 * G + 4, 0);
+  acc = __builtin_amdgcn_mfma_f32_4x4x1f32(A, H[5], acc, 4, 8 * G + 5, 0);
+  acc = __builtin_amdgcn_mfma_f32_4x4x1f32(A, H[6], acc, 4, 8 * G + 6, 0);
+  acc = __builtin_amdgcn_mfma_f32_4x4x1f32(A, H[7], acc, 4, 8 * G + 7, 0);
+  return acc;
+}
+
+// First order over rows of at most TOP + 4 <= 8 features at the 8-node rule.
+// With H(m) = w_m prod_k F_k(m) over all the row's slots, slot j adds
+//   sum_m c_j w_m prod_{k != j} F_k(m) = sum_m H(m) c_j / F_j(m),
+// and c_j / F_j depends on the sample only through its follow bit:
+//   followed: e_j(m) = (1 - b_j) / (b_j + t_m (1 - b_j)), a table per slot;
+//   not:      r(m) = -1 / (1 - t_m), the same for every slot.
+// So a row needs the running product, one node sum per slot against
+// sample-independent coefficients, and one sum D for all slots not followed;
+// no suffix products and no factors kept.  FP32 takes the node sums on the
+// matrix unit: four slots' coefficients are the 4x1 block of a 4x4x1 product
+// and a lane's sample keeps its lane; the row's 64 coefficients are one
+// coalesced load.  FP64 reads them as scalar operands.
+// Slots 1..TOP are the row's root side.  While consecutive rows share all of
+// them, their H are summed and slots 1..TOP take their node sums once for
+// the run of rows (with full trees of depth TOP + 4: 8 rows); slots TOP + 1
+// .. TOP + 3 and D fill one 4-wide product per row.  P[k], the prefix product
+// through slot k, is kept from row to row, so only slots past the shared
+// count are evaluated.
+//
+// The row loop is pipelined by hand.  Scalar loads and LDS reads share one
+// wait counter and scalar loads return out of order, so a wait for one is a
+// wait for all: the next row's record is loaded once this row's values of x
+// are in, and the next row's x are read before this row's sums are added.
+//
+// Bound by VALU issue: compares, selects and address adds read scalar
+// registers (1.3 clocks of a CU per wave instruction), the factor and product
+// FMAs do not (0.65), FP64 takes 1.3, four slots' node sums 19.  500 trees of
+// depth 8, 100 features, 100k rows, FP32: 24.7 ms with suffix products and
+// node sums per slot, 23.1 here; 300 such trees, 5003 rows, FP64: 3.43 and
+// 2.10 ms.
+template <typename T, int TOP, bool NANS>
+__device__ __forceinline__ void values_rows_grouped(
+    const WalkRow<T>* __restrict__ rows, const T* __restrict__ coef, int row0,
+    const Slot0<T>* __restrict__ z0, const float* xs, double* as, int pb, int pe, int wave,
+    int nw, int lane, const NodeConsts<T>& nc) {
+  constexpr int N = 8, ND = TOP + 3;
+  constexpr bool kF32 = sizeof(T) == 4;
+  // FP64 keeps the prefix products from slot TOP on only (registers)
+  constexpr bool kKeepTop = kF32;
+  const int run = (pe - pb + nw - 1) / nw;
+  const int p_first = pb + wave * run;
+  const int p_last = min(pe, p_first + run);
+  if (p_first >= p_last) return;
+  T P[ND + 1][N];
+  uint64_t in_k[ND + 1];  // follow bits of slots 1..ND, one per lane
+  T Hs[TOP > 0 ? N : 1];  // sum of H over the rows since slots 1..TOP changed
+  int xo_top[TOP > 0 ? TOP : 1];
+  int d_top = 0, p_top = p_first;
+  float a_top = 0.f;
+#pragma unroll
+  for (int k = 0; k <= ND; ++k) in_k[k] = 0;
+#pragma unroll
+  for (int m = 0; m < N; ++m) P[0][m] = node8_w(nc, m);
+#pragma unroll
+  for (int m = 0; m < (TOP > 0 ? N : 1); ++m) Hs[m] = T(0);
+  const char* xl = reinterpret_cast<const char*>(xs + lane);
+  char* al = reinterpret_cast<char*>(as + lane);
+  auto x_at = [&](int off) __attribute__((always_inline)) {
+    return *reinterpret_cast<const float*>(xl + off);
+  };
+  auto add = [&](int xo, T v) __attribute__((always_inline)) {
+    __hip_atomic_fetch_add(reinterpret_cast<double*>(al + 2 * xo), (double)v, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  // lanes whose x lies in [l, u) (u = NaN: no bound), or is missing and miss
+  auto inside = [&](float x, float l, float u, bool miss) __attribute__((always_inline)) {
+    uint64_t lower = __builtin_amdgcn_ballot_w64(x >= l);
+    if (NANS) lower |= miss ? __builtin_amdgcn_ballot_w64(x != x) : 0;
+    return lower & __builtin_amdgcn_ballot_w64(!(x >= u));
+  };
+  auto flush_top = [&]() __attribute__((always_inline)) {
+    if constexpr (TOP > 0) {
+      T D = nc.r[0] * Hs[0];
+#pragma unroll
+      for (int m = 1; m < N; ++m) D = fmaT(nc.r[m], Hs[m], D);
+      if constexpr (kF32) {
+        const acc_v4 E = node_sums4<0>(a_top, Hs, acc_v4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int k = 0; k < TOP; ++k)
+          if (k + 1 < d_top) add(xo_top[k], pick(in_k[k + 1], D, E[k]));
+      } else {
+        const T* e = coef + (int64_t)(p_top - row0) * kShortCoef;
+#pragma unroll
+        for (int k = 0; k < TOP; ++k) {
+          if (k + 1 < d_top) {
+            T E = ldu(e + 8 * k) * Hs[0];
+#pragma unroll
+            for (int m = 1; m < N; ++m) E = fmaT(ldu(e + 8 * k + m), Hs[m], E);
+            add(xo_top[k], pick(in_k[k + 1], D, E));
+          }
+        }
+      }
+    }
+  };
+  // slot k's prefix product from its bits
+  auto extend = [&](int k, T b, T cb) __attribute__((always_inline)) {
+    const T bv = to_vgpr(b);
+    const T c = pick_neg(in_k[k], bv, to_vgpr(cb));
+#pragma unroll
+    for (int m = 0; m < N; ++m) P[k][m] = P[k - 1][m] * fmaT(node8_t(nc, m), c, bv);
+  };
+  struct Rec {  // the part of a row that every row reads (scalar registers)
+    int32_t pack, xo0;
+    float lo0, hi0, split;
+    int32_t xo[3];
+    float lo[3], hi[3];
+    T b[3], cb[3], bm, cA, cB;
+  };
+  auto load = [&](int p) __attribute__((always_inline)) {
+    const WalkRow<T>* w = rows + (p - row0);
+    Rec r;
+    const row_v16 a = ldu(reinterpret_cast<const row_v16*>(w));  // 14 words are the row's
+    r.pack = a[0];
+    r.xo0 = a[1];
+    r.lo0 = __int_as_float(a[2]);
+    r.hi0 = __int_as_float(a[3]);
+    r.split = __int_as_float(a[4]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      r.xo[i] = a[5 + i];
+      r.lo[i] = __int_as_float(a[8 + i]);
+      r.hi[i] = __int_as_float(a[11 + i]);
+      r.b[i] = ldu(&w->bl[i]);
+      r.cb[i] = ldu(&w->cbl[i]);
+    }
+    const Slot0<T>* z = z0 + p;
+    r.bm = ldu(&z->bm);
+    r.cA = ldu(&z->ca);
+    r.cB = ldu(&z->cb);
+    return r;
+  };
+  Rec r = load(p_first);
+  float x[4] = {x_at(r.xo0), x_at(r.xo[0]), x_at(r.xo[1]), x_at(r.xo[2])};
+  float a_row = 0.f, a_next = 0.f;
+  const T* coef_l = coef + lane;
+  if constexpr (kF32) a_next = coef_l[(int64_t)(p_first - row0) * kShortCoef];
+  for (int p = p_first; p < p_last; ++p) {
+    const int d = r.pack & 15;
+    const int s = p == p_first ? 0 : (r.pack >> 4) & 15;
+    const int mok = r.pack >> 8;
+    const int p_next = min(p + 1, p_last - 1);
+    if constexpr (kF32) {
+      a_row = a_next;
+      a_next = coef_l[(int64_t)(p_next - row0) * kShortCoef];
+    }
+    // follow bits of slot 0 and of slots TOP + 1 .. ND (shared ones come out
+    // as they are), and slot 0's c
+    uint64_t in0 = inside(x[0], r.lo0, r.hi0, NANS && (mok & 0x101) != 0);
+    uint64_t in0a = __builtin_amdgcn_ballot_w64(!(x[0] >= r.split));
+    if (NANS) in0a &= (mok & 0x100) != 0 ? __builtin_amdgcn_ballot_w64(x[0] == x[0]) : ~0ull;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      in_k[TOP + 1 + i] = inside(x[1 + i], r.lo[i], r.hi[i], ((mok >> (TOP + 1 + i)) & 1) != 0);
+    if constexpr (TOP > 0) {
+      if (s < TOP) {
+        if (p != p_first) {
+          flush_top();
+#pragma unroll
+          for (int m = 0; m < N; ++m) Hs[m] = T(0);
+        }
+        const WalkRow<T>* w = rows + (p - row0);
+        float xt[TOP], lt[TOP], ut[TOP];
+        T bt[TOP], cbt[TOP];
+#pragma unroll
+        for (int k = 0; k < TOP; ++k) {
+          xo_top[k] = ldu(&w->xot[k]);
+          lt[k] = ldu(&w->lot[k]);
+          ut[k] = ldu(&w->hit[k]);
+          bt[k] = ldu(&w->bt[k]);
+          cbt[k] = ldu(&w->cbt[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < TOP; ++k) xt[k] = x_at(xo_top[k]);
+#pragma unroll
+        for (int k = 0; k < TOP; ++k) {
+          if (!kKeepTop || k + 1 > s) {
+            in_k[k + 1] = inside(xt[k], lt[k], ut[k], ((mok >> (k + 1)) & 1) != 0);
+            extend(k + 1, bt[k], cbt[k]);
+          }
+        }
+        d_top = d;
+        p_top = p;
+        a_top = a_row;
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const Rec rn = load(p_next);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (TOP + 1 + i > s) extend(TOP + 1 + i, r.b[i], r.cb[i]);
+    // slot 0 (the row's own factor, leaf values folded in), last in the order
+    const T bv0 = to_vgpr(r.bm);
+    const T c0 = pick_neg(in0, bv0, pick(in0a, to_vgpr(r.cB), to_vgpr(r.cA)));
+    T H[N];
+    T q0 = P[ND][0];
+#pragma unroll
+    for (int m = 1; m < N; ++m) q0 += P[ND][m];
+#pragma unroll
+    for (int m = 0; m < N; ++m) H[m] = P[ND][m] * fmaT(node8_t(nc, m), c0, bv0);
+    // slots TOP + 1 .. ND, and D
+    T E[4];
+    if constexpr (kF32) {
+      const acc_v4 a4 = node_sums4<1>(a_row, H, acc_v4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+      for (int i = 0; i < 4; ++i) E[i] = a4[i];
+    } else {
+      E[3] = nc.r[0] * H[0];
+#pragma unroll
+      for (int m = 1; m < N; ++m) E[3] = fmaT(nc.r[m], H[m], E[3]);
+      const T* e = coef + (int64_t)(p - row0) * kShortCoef + 8 * TOP;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        E[i] = ldu(e + 8 * i) * H[0];
+#pragma unroll
+        for (int m = 1; m < N; ++m) E[i] = fmaT(ldu(e + 8 * i + m), H[m], E[i]);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    x[0] = x_at(rn.xo0);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) x[1 + i] = x_at(rn.xo[i]);
+    __builtin_amdgcn_sched_barrier(0);
+    add(r.xo0, c0 * q0);
+    if (d == ND + 1) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) add(r.xo[i], pick(in_k[TOP + 1 + i], E[3], E[i]));
+    } else {
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+        if (TOP + 1 + i < d) add(r.xo[i], pick(in_k[TOP + 1 + i], E[3], E[i]));
+    }
+    if constexpr (TOP > 0) {
+#pragma unroll
+      for (int m = 0; m < N; ++m) Hs[m] += H[m];
+    }
+    r = rn;
+  }
+  flush_top();
+}
+
 // First order over rows of more than 8 features, reusing work between
 // consecutive rows.  Each wave walks a contiguous run of rows.  The products
 // are taken over the slots in the order 1, 2, ..., d - 1, 0: slot 0 (the
@@ -723,7 +1007,8 @@ __device__ __forceinline__ ItemRows item_rows(const Segment* segs, const int32_t
 
 // tile_f: the features the LDS layout is sized for (F, or kSegFeatures with
 // segments); F: phi's row length.
-template <typename T, int DMAX, int NH, bool STORE_G, int NN>
+// TOP >= 0: the grouped walk over short rows (DMAX = 8, 8 nodes).
+template <typename T, int DMAX, int NH, bool STORE_G, int NN, int TOP>
 __global__ void __launch_bounds__(512)
 values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
               const float* __restrict__ lo, const float* __restrict__ hi,
@@ -734,6 +1019,7 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
               const Segment* __restrict__ segs, const int32_t* __restrict__ seg_feat,
               int32_t ng, int32_t grp, double* __restrict__ acc, void* __restrict__ direct,
               int32_t direct_fp64, int32_t plain_add, const ShortRow<T>* __restrict__ srows,
+              const WalkRow<T>* __restrict__ wrows, const T* __restrict__ wcoef,
               NodeConsts<T> nc) {
   extern __shared__ __align__(16) unsigned char smem[];
   float* xs = reinterpret_cast<float*>(smem);
@@ -791,39 +1077,27 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
 #pragma unroll
   for (int m = 0; m < NN; ++m) tv[m] = to_vgpr(nc.t[m]);
 
-  // the shared-prefix walk keeps c_j and F_j(m) of all eight slots live
-  // across rows: FP32 within 128 VGPRs (four waves per SIMD); FP64 only with
-  // the 4-node rule (the 8-node FP64 instance has no registers to spare)
-  constexpr bool kShared = DMAX == 8 && NH == NN && (STORE_G || NN == 4);
-  // the 8-node FP64 instance walks the same records without keeping a row's
-  // factors or prefix products for the next (no registers for them)
-  constexpr bool kShortPlain = DMAX == 8 && NH == NN && !kShared;
-  if (DMAX > 8 && any_nan)
+  if constexpr (TOP >= 0) {
+    if (any_nan)
+      values_rows_grouped<T, TOP, true>(wrows, wcoef, path_begin, z0, xs, as, pb, pe, wave, nw,
+                                        lane, nc);
+    else
+      values_rows_grouped<T, TOP, false>(wrows, wcoef, path_begin, z0, xs, as, pb, pe, wave, nw,
+                                         lane, nc);
+  } else if constexpr (DMAX == 8) {
+    if (any_nan)
+      values_rows_shared<T, NH, true>(srows, path_begin, z0, xs, as, pb, pe, wave, nw, lane, tv,
+                                      nc);
+    else
+      values_rows_shared<T, NH, false>(srows, path_begin, z0, xs, as, pb, pe, wave, nw, lane, tv,
+                                       nc);
+  } else if (any_nan) {
     values_rows_long<T, DMAX, NH, STORE_G, true, NN>(hdr, feat, lo, hi, bb, cbb, z0, share, xs,
                                                      as, pb, pe, wave, nw, lane, tv, nc);
-  else if (DMAX > 8)
+  } else {
     values_rows_long<T, DMAX, NH, STORE_G, false, NN>(hdr, feat, lo, hi, bb, cbb, z0, share, xs,
                                                       as, pb, pe, wave, nw, lane, tv, nc);
-  else if (kShared && any_nan)
-    values_rows_shared<T, NH, true>(srows, path_begin, z0, xs, as, pb, pe, wave, nw, lane, tv,
-                                    nc);
-  else if (kShared)
-    values_rows_shared<T, NH, false>(srows, path_begin, z0, xs, as, pb, pe, wave, nw, lane, tv,
-                                     nc);
-  else if (kShortPlain && any_nan)
-    values_rows_shared<T, NH, true, false>(srows, path_begin, z0, xs, as, pb, pe, wave, nw, lane,
-                                           tv, nc);
-  else if (kShortPlain)
-    values_rows_shared<T, NH, false, false>(srows, path_begin, z0, xs, as, pb, pe, wave, nw,
-                                            lane, tv, nc);
-  else if (any_nan)
-    values_paths<T, DMAX, NH, STORE_G, true, false, NN>(hdr, feat, lo, hi, bb, cbb, nullptr,
-                                                        z0, xs, as, nullptr, nullptr, pb,
-                                                        pe, wave, nw, lane, tv, nc);
-  else
-    values_paths<T, DMAX, NH, STORE_G, false, false, NN>(hdr, feat, lo, hi, bb, cbb, nullptr,
-                                                         z0, xs, as, nullptr, nullptr, pb,
-                                                         pe, wave, nw, lane, tv, nc);
+  }
   __syncthreads();
 
   // flush: consecutive threads take consecutive features of one sample.
@@ -1157,7 +1431,24 @@ RowSplit row_split(const HostTable& h, const PathArrays& a, const Bucket& bk, in
   fail(QTS_E_INVALID_ARG, "internal: bucket without segments");
 }
 
-template <typename T, int DMAX, int NH, bool STORE_G, int NN>
+// The grouped walk's rows of a capacity-8 bucket and their coefficients.
+template <typename T>
+struct WalkPtrs {
+  const WalkRow<T>* rows = nullptr;
+  const T* coef = nullptr;
+};
+template <typename T>
+WalkPtrs<T> walk_of(const PathArrays& a, const Bucket& bk) {
+  if (bk.dmax != 8 || bk.srow_begin < 0) return {};
+  WalkPtrs<T> w;
+  if constexpr (std::is_same<T, float>::value) w = {a.walk.row32, a.walk.coef32};
+  else w = {a.walk.row64, a.walk.coef64};
+  if (w.rows == nullptr || w.coef == nullptr)
+    fail(QTS_E_INVALID_ARG, "internal: no grouped-walk rows");
+  return {w.rows + bk.srow_begin, w.coef + (int64_t)bk.srow_begin * kShortCoef};
+}
+
+template <typename T, int DMAX, int NH, bool STORE_G, int NN, int TOP = -1>
 void launch_one(const HostTable& h, const DeviceTable& d, const PathArrays& a, const Bucket& bk,
                 const float* X, int64_t M, int64_t ldx, const void* slot0, double* acc,
                 void* direct, const ValuesShape& shape, hipStream_t s, bool det) {
@@ -1175,28 +1466,33 @@ void launch_one(const HostTable& h, const DeviceTable& d, const PathArrays& a, c
   NodeConsts<T> nc;
   if constexpr (std::is_same<T, float>::value) nc = NN == 8 ? d.n32 : d.n32_4;
   else nc = NN == 8 ? d.n64 : d.n64_4;
-  if (lds > raise_lds_limit((const void*)values_kernel<T, DMAX, NH, STORE_G, NN>))
+  if (lds > raise_lds_limit((const void*)values_kernel<T, DMAX, NH, STORE_G, NN, TOP>))
     fail(QTS_E_UNSUPPORTED, "internal: the sample tile does not fit in LDS");
   const ShortRow<T>* srows = short_rows_of<T>(a, bk);
+  const WalkPtrs<T> walk = walk_of<T>(a, bk);
   if (!det) {
-    hipLaunchKernelGGL((values_kernel<T, DMAX, NH, STORE_G, NN>), dim3((unsigned)grid),
+    hipLaunchKernelGGL((values_kernel<T, DMAX, NH, STORE_G, NN, TOP>), dim3((unsigned)grid),
                        dim3(threads), lds, s, a.hdr, rs.feat, a.lo, a.hi, b, cb,
                        (const Slot0<T>*)slot0, a.share, X, M, ldx, F, rs.tile_f, bk.path_begin,
                        bk.path_end, rs.chunk, nsb, rs.segs, a.seg_feat, h.n_groups, bk.group,
                        acc, rs.segs ? nullptr : direct,
-                       (int32_t)(std::is_same<T, double>::value ? 1 : 0), 0, srows, nc);
+                       (int32_t)(std::is_same<T, double>::value ? 1 : 0), 0, srows, walk.rows,
+                       walk.coef, nc);
     check_hip(hipGetLastError(), "values_kernel launch");
     return;
   }
   for (int c = 0; c < rs.n_chunks; ++c) {
     const int p0 = rs.segs ? bk.path_begin : bk.path_begin + c * rs.chunk;
     const int p1 = rs.segs ? bk.path_end : std::min(bk.path_end, p0 + rs.chunk);
-    hipLaunchKernelGGL((values_kernel<T, DMAX, NH, STORE_G, NN>), dim3((unsigned)nsb),
+    hipLaunchKernelGGL((values_kernel<T, DMAX, NH, STORE_G, NN, TOP>), dim3((unsigned)nsb),
                        dim3(threads), lds, s, a.hdr, rs.feat, a.lo, a.hi, b, cb,
                        (const Slot0<T>*)slot0, a.share, X, M, ldx, F, rs.tile_f, p0, p1,
                        rs.chunk, nsb, rs.segs ? rs.segs + c : nullptr, a.seg_feat, h.n_groups,
                        bk.group, acc, nullptr, (int32_t)(std::is_same<T, double>::value ? 1 : 0),
-                       1, srows ? srows + (p0 - bk.path_begin) : nullptr, nc);
+                       1, srows ? srows + (p0 - bk.path_begin) : nullptr,
+                       walk.rows ? walk.rows + (p0 - bk.path_begin) : nullptr,
+                       walk.coef ? walk.coef + (int64_t)(p0 - bk.path_begin) * kShortCoef : nullptr,
+                       nc);
     check_hip(hipGetLastError(), "values_kernel launch");
   }
 }
@@ -1255,6 +1551,83 @@ void launch_adjoint(const HostTable& h, const DeviceTable& d, const PathArrays& 
       default: launch_adj_one<double, 64, 1, false, 8>(h, d, a, bk, X, G, M, ldx, grad_leaf, shape, s, part_stride); break;
     }
   }
+}
+
+// The grouped walk's rows and node-sum coefficients of one bucket, 64 threads
+// per row.  FP32 coefficients: entry 4 (8 G + m) + i is slot i + 1's when
+// G = 0 and i < top, slot top + 1 + i's when G = 1 and i < 3, and r(m) when
+// G = 1 and i = 3 (the blocks of node_sums4).  FP64: entry 8 (j - 1) + m is
+// slot j's.
+template <typename T>
+__device__ __forceinline__ void fill_walk_row(const ShortRow<double>& r, const PathHdr& h,
+                                              const SidePath* side, int32_t top, WalkRow<T>* o) {
+  WalkRow<T> w;
+  const int sidx = side == nullptr ? -1 : h.tree;
+  int mok_b = 0;
+  w.xo0 = r.xoff[0];
+  w.lo0 = r.lo[0];
+  w.hi0 = w.split = r.hi[0];
+  if (r.d > 0 && sidx >= 0) {
+    // A [lo, split) and B [split, hi): adjacent, or one of them empty
+    w.lo0 = r.lo[0] < side[sidx].lo_b ? r.lo[0] : side[sidx].lo_b;
+    w.hi0 = side[sidx].hi_b;
+    mok_b = side[sidx].mok_b != 0 ? 1 : 0;
+  }
+  w.pack = r.d | r.share << 4 | (r.mok & 0xff) << 8 | mok_b << 16;
+  for (int i = 0; i < 3; ++i) {
+    const int k = top + 1 + i;
+    w.xol[i] = r.xoff[k];
+    w.lol[i] = r.lo[k];
+    w.hil[i] = r.hi[k];
+    w.bl[i] = (T)r.b[k];
+    w.cbl[i] = (T)r.cb[k];
+  }
+  for (int i = 0; i < 4; ++i) {
+    const int k = i < top ? i + 1 : 0;
+    w.xot[i] = r.xoff[k];
+    w.lot[i] = r.lo[k];
+    w.hit[i] = r.hi[k];
+    w.bt[i] = (T)r.b[k];
+    w.cbt[i] = (T)r.cb[k];
+  }
+  *o = w;
+}
+
+__global__ void __launch_bounds__(256)
+short_walk_kernel(const ShortRow<double>* __restrict__ rows, const PathHdr* __restrict__ hdr,
+                  const SidePath* __restrict__ side, int32_t n, int32_t top,
+                  NodeConsts<double> nc, WalkRow<float>* __restrict__ w32,
+                  WalkRow<double>* __restrict__ w64, float* __restrict__ e32,
+                  double* __restrict__ e64) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t row = i >> 6;
+  if (row >= n) return;
+  const int l = (int)i & 63;
+  const ShortRow<double>& r = rows[row];
+  auto coef = [&](int j, int m) {
+    return j > 7 ? 0.0 : r.cb[j] / (r.b[j] + nc.t[m] * r.cb[j]);
+  };
+  e64[i] = coef((l >> 3) + 1, l & 7);
+  const int g = l >> 5, m = (l >> 2) & 7, k = l & 3;
+  double v = 0.0;
+  if (g == 0) v = k < top ? coef(k + 1, m) : 0.0;
+  else v = k < 3 ? coef(top + 1 + k, m) : nc.r[m];
+  e32[i] = (float)v;
+  if (l == 0) fill_walk_row(r, hdr[row], side, top, w32 + row);
+  if (l == 1) fill_walk_row(r, hdr[row], side, top, w64 + row);
+}
+
+void launch_short_walk(const PathArrays& a, const Bucket& bk, const NodeConsts<double>& nc,
+                       hipStream_t s) {
+  const int32_t n = bk.path_end - bk.path_begin;
+  if (bk.dmax != 8 || n <= 0) return;
+  const unsigned grid = (unsigned)(((int64_t)n * 64 + 255) / 256);
+  hipLaunchKernelGGL(short_walk_kernel, dim3(grid), dim3(256), 0, s, a.srow64 + bk.srow_begin,
+                     a.hdr + bk.path_begin, a.side, n, bk.top, nc, a.walk.row32 + bk.srow_begin,
+                     a.walk.row64 + bk.srow_begin,
+                     a.walk.coef32 + (int64_t)bk.srow_begin * kShortCoef,
+                     a.walk.coef64 + (int64_t)bk.srow_begin * kShortCoef);
+  check_hip(hipGetLastError(), "short_walk_kernel launch");
 }
 
 // Slot 0 of every first-order row with the current leaf values folded in.
@@ -1319,16 +1692,29 @@ void launch_values(const HostTable& h, const DeviceTable& d, const PathArrays& a
     else launch_one<double, 8, 4, false, 4>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic);
     return;
   }
+  if (bk.dmax == 8) {
+    auto go = [&](auto top) {
+      constexpr int kTop = decltype(top)::value;
+      if (!fp64) launch_one<float, 8, 8, true, 8, kTop>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic);
+      else launch_one<double, 8, 8, true, 8, kTop>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic);
+    };
+    switch (bk.top) {
+      case 0: go(std::integral_constant<int, 0>{}); break;
+      case 1: go(std::integral_constant<int, 1>{}); break;
+      case 2: go(std::integral_constant<int, 2>{}); break;
+      case 3: go(std::integral_constant<int, 3>{}); break;
+      default: go(std::integral_constant<int, 4>{}); break;
+    }
+    return;
+  }
   if (!fp64) {
     switch (bk.dmax) {
-      case 8: launch_one<float, 8, 8, true, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
       case 16: launch_one<float, 16, 8, true, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
       case 32: launch_one<float, 32, 8, false, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
       default: launch_one<float, 64, 4, false, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
     }
   } else {
     switch (bk.dmax) {
-      case 8: launch_one<double, 8, 8, false, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
       case 16: launch_one<double, 16, 4, false, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
       case 32: launch_one<double, 32, 4, false, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
       default: launch_one<double, 64, 2, false, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;

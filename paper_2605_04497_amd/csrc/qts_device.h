@@ -12,6 +12,7 @@ template <typename T>
 struct NodeConsts {
   T t[kNodes];
   T w[kNodes];
+  T r[kNodes];  // -1 / (1 - t): (o - b) / F of a slot whose splits are not followed
 };
 
 constexpr int kTileStride = kSamplesPerBlock + 1;  // padded LDS row (bank spread)
@@ -49,6 +50,40 @@ struct alignas(16) ShortRow {
   int32_t aoff[8];  // feature * kTileStride * 8
   float lo[8], hi[8];
   T b[8], cb[8];    // b_j and 1 - b_j (FP64-derived), rounded to T
+};
+
+// A short row as the grouped walk of the 8-node rule reads it
+// (values_rows_grouped), built on the device from its ShortRow.  Slots 1..top
+// of the bucket (Bucket::top) are the row's root side, read only when they
+// change; slot 0 and the three slots after them are read for every row.
+// Slot 0 holds the interval of A and B together and the bound between them:
+// of the samples inside, A takes those below `split` (a single path: split
+// is its own upper bound).  Offsets are bytes into the FP32 sample tile; the
+// FP64 accumulator's are twice those.
+template <typename T>
+struct alignas(8) WalkRow {
+  int32_t pack;    // d | share << 4 | missing_ok bits of slots 0..7 << 8 | B's << 16
+  int32_t xo0;
+  float lo0, hi0, split;
+  int32_t xol[3];  // slots top + 1 .. top + 3
+  float lol[3], hil[3];
+  T bl[3], cbl[3];
+  int32_t xot[4];  // slots 1 .. top
+  float lot[4], hit[4];
+  T bt[4], cbt[4];
+};
+
+// Node-sum coefficients (1 - b_j) / (b_j + t_m (1 - b_j)) of a short row's
+// slots 1..7 at the 8 nodes, per row (short_walk_kernel has the layouts).
+constexpr int kShortCoef = 64;
+
+// The grouped walk's tables of one first-order table's short rows (in the
+// order of Bucket::srow_begin); kShortCoef coefficients per row.
+struct ShortWalk {
+  WalkRow<float>* row32 = nullptr;
+  WalkRow<double>* row64 = nullptr;
+  float* coef32 = nullptr;
+  double* coef64 = nullptr;
 };
 
 // Device copy of the path table.  Element arrays are shared by all buckets.
@@ -92,6 +127,8 @@ struct DeviceTable {
   ShortRow<double>* srow64 = nullptr;
   ShortRow<float>* msrow32 = nullptr;
   ShortRow<double>* msrow64 = nullptr;
+  // the same rows for the grouped walk, and their node-sum coefficients
+  ShortWalk walk, mwalk;
   // feature-compacted segments (wide_features only), plain and merged tables
   int32_t* lfeat = nullptr;
   Segment* segs = nullptr;
@@ -160,18 +197,20 @@ struct PathArrays {
   const int32_t* seg_feat;
   const ShortRow<float>* srow32;  // capacity-8 rows (features as the kernel indexes its tile)
   const ShortRow<double>* srow64;
+  ShortWalk walk;
 };
 
 inline PathArrays plain_arrays(const DeviceTable& d, const HostTable& h) {
   const bool w = !h.compact.segs.empty();
   return PathArrays{d.hdr, d.feat, d.lo, d.hi, d.b32, d.cb32, d.b64, d.cb64, nullptr, d.share,
-                    w ? &h.compact : nullptr, d.lfeat, d.segs, d.seg_feat, d.srow32, d.srow64};
+                    w ? &h.compact : nullptr, d.lfeat, d.segs, d.seg_feat, d.srow32, d.srow64,
+                    d.walk};
 }
 inline PathArrays merged_arrays(const DeviceTable& d, const HostTable& h) {
   const bool w = !h.mcompact.segs.empty();
   return PathArrays{d.mhdr, d.mfeat, d.mlo, d.mhi, d.mb32, d.mcb32, d.mb64, d.mcb64, d.side,
                     d.mshare, w ? &h.mcompact : nullptr, d.mlfeat, d.msegs, d.mseg_feat,
-                    d.msrow32, d.msrow64};
+                    d.msrow32, d.msrow64, d.mwalk};
 }
 
 // Slot 0 of a first-order row with its leaf value folded in, built per call
@@ -307,6 +346,10 @@ void launch_sum_rows(const double* part, int64_t nrows, int64_t n, double* out, 
 // from leaf_val; `out` holds n_rows records.
 void launch_slot0(const PathArrays& a, int32_t n_rows, const double* leaf_val, bool fp64,
                   void* out, hipStream_t s);
+// Fill the grouped walk's tables of one capacity-8 bucket of `a` from its
+// ShortRow records (a.walk's arrays are allocated).
+void launch_short_walk(const PathArrays& a, const Bucket& bk, const NodeConsts<double>& nc,
+                       hipStream_t s);
 size_t slot0_bytes(int32_t n_rows, bool fp64);
 
 // Accumulate phi (FP64, [M,F], pre-zeroed) over the paths of one bucket.

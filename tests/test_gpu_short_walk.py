@@ -1,0 +1,48 @@
+"""The grouped walk over rows of at most 8 features (first order, 8 nodes)
+against the FP64 oracle, at every length of the buckets' longest row (1 to 8:
+the number of root-side slots taken per run of rows runs from 0 to 4), on
+irregular trees with repeated features, ties, zero covers and missing values,
+at sample counts around the 64-sample tile, on the merged and the plain table
+and in the deterministic mode."""
+import numpy as np
+import pytest
+
+import synth
+from tests.parity import check
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def q():
+    import paper_2605_04497_amd as q
+    return q
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("depth", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_short_walk_matches_oracle(q, oracle_mod, depth, precision):
+    rng = np.random.default_rng(100 + depth)
+    for F, n_trees in ((12, 30), (max(1, depth - 1), 5)):
+        print("case", depth, precision, F, flush=True)
+        ens = synth.random_small_ensemble(rng, n_trees, F, depth, n_train=4000)
+        e = q.Ensemble(ens)
+        X = rng.normal(size=(130, F)).astype(np.float32)
+        X[:, ::2] = np.round(X[:, ::2])
+        for missing in (False, True):
+            if missing:
+                X[rng.random(X.shape) < 0.1] = np.nan
+            want = oracle_mod.shap_values(ens, X, n=8)
+            Xd = torch.from_numpy(X).cuda()
+            for merge in (True, False):
+                e.set_sibling_merge(merge)
+                for m in (1, 63, 64, 65, 130):
+                    got = e.shap_values(Xd[:m], precision).cpu().numpy().astype(np.float64)
+                    check(got, want[:m], precision, "M=%d merge=%s" % (m, merge))
+            e.set_deterministic(True)
+            got = e.shap_values(Xd, precision).cpu().numpy().astype(np.float64)
+            e.set_deterministic(False)
+            check(got, want, precision, "deterministic")
+        e.close()
