@@ -396,7 +396,8 @@ void build_nodes(DeviceTable& d) {
     d.n64.r[m] = -1.0 / s[m];
     d.n32.r[m] = (float)d.n64.r[m];
     // the FP32 short-row walks take the rule as instruction literals
-    if (d.n32.t[m] != rule8_t32(m) || d.n32.w[m] != rule8_w32(m))
+    if (d.n32.t[m] != rule8_t32(m) || d.n32.w[m] != rule8_w32(m) ||
+        d.n32.r[m] != rule8_r32(m))
       fail(QTS_E_UNSUPPORTED, "the FP32 8-node rule differs from the kernels' constants");
   }
   // fewer-node rules, padded with zero nodes and weights

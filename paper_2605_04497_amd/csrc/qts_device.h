@@ -33,6 +33,12 @@ __host__ __device__ constexpr float rule8_w32(int m) {
   return w[m];
 }
 
+// -1 / (1 - t_m): (o - b) / F of a slot whose splits are not followed.
+__host__ __device__ constexpr float rule8_r32(int m) {
+  constexpr float r[kNodes] = {-0x1.052f940p+0f, -0x1.1cf8e20p+0f, -0x1.4f9edc0p+0f, -0x1.b0a3960p+0f, -0x1.39821e0p+1f, -0x1.0dc6ac0p+2f, -0x1.3ac0fa0p+3f, -0x1.92eb720p+5f};
+  return r[m];
+}
+
 // A first-order row of a capacity-8 bucket as the walk over short rows reads
 // it: every field of the row in one record, so a wave fetches the row with a
 // few wide scalar loads from one address, and the LDS byte offsets of the

@@ -1,9 +1,10 @@
-"""The grouped walk over rows of at most 8 features (first order, 8 nodes)
-against the FP64 oracle, at every length of the buckets' longest row (1 to 8:
+"""The walks of the first-order kernel that sum products over runs of rows,
+against the FP64 oracle.  Rows of at most 8 features (8 nodes): at every length of the buckets' longest row (1 to 8:
 the number of root-side slots taken per run of rows runs from 0 to 4), on
-irregular trees with repeated features, ties, zero covers and missing values,
+irregular trees with repeated features, ties and missing values,
 at sample counts around the 64-sample tile, on the merged and the plain table
-and in the deterministic mode."""
+and in the deterministic mode.  Longer rows: irregular deep trees of three
+capacities."""
 import numpy as np
 import pytest
 
@@ -46,3 +47,27 @@ def test_short_walk_matches_oracle(q, oracle_mod, depth, precision):
             e.set_deterministic(False)
             check(got, want, precision, "deterministic")
         e.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("depth,F,leaf", [(12, 16, 0.05), (24, 40, 0.02), (64, 70, 0.0)])
+def test_long_walk_matches_oracle(q, oracle_mod, depth, F, leaf, precision):
+    print("case", depth, F, precision, flush=True)
+    rng = np.random.default_rng(200 + depth)
+    ens = synth.random_small_ensemble(rng, 4, F, depth, n_train=400, p_leaf=leaf,
+                                      zero_cover=depth == 12)
+    e = q.Ensemble(ens)
+    assert e.info["max_unique"] > 8
+    X = rng.normal(size=(70, F)).astype(np.float32)
+    X[:, ::3] = np.round(X[:, ::3])
+    for missing in (False, True):
+        if missing:
+            X[rng.random(X.shape) < 0.1] = np.nan
+        want = oracle_mod.shap_values(ens, X, n=8)
+        Xd = torch.from_numpy(X).cuda()
+        for merge in (True, False):
+            e.set_sibling_merge(merge)
+            for m in (1, 64, 70):
+                got = e.shap_values(Xd[:m], precision).cpu().numpy().astype(np.float64)
+                check(got, want[:m], precision, "M=%d merge=%s" % (m, merge))
+    e.close()
