@@ -518,35 +518,9 @@ __device__ __forceinline__ void values_rows_shared(
 
 // A select by a lane mask held in scalar registers (one bit per lane): b
 // where the lane's bit is set, else a.
-__device__ __forceinline__ float pick(uint64_t mask, float a, float b) {
-  float r;
-  asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(mask));
-  return r;
-}
-__device__ __forceinline__ double pick(uint64_t mask, double a, double b) {
-  const float lo = pick(mask, __int_as_float(__double2loint(a)), __int_as_float(__double2loint(b)));
-  const float hi = pick(mask, __int_as_float(__double2hiint(a)), __int_as_float(__double2hiint(b)));
-  return __hiloint2double(__float_as_int(hi), __float_as_int(lo));
-}
-
-// The same with -a in place of a.
-__device__ __forceinline__ float pick_neg(uint64_t mask, float a, float b) {
-  float r;
-  asm("v_cndmask_b32 %0, -%1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(mask));
-  return r;
-}
-__device__ __forceinline__ double pick_neg(uint64_t mask, double a, double b) {
-  const float lo = pick(mask, __int_as_float(__double2loint(a)), __int_as_float(__double2loint(b)));
-  const float hi =
-      pick_neg(mask, __int_as_float(__double2hiint(a)), __int_as_float(__double2hiint(b)));
-  return __hiloint2double(__float_as_int(hi), __float_as_int(lo));
-}
-
-// The lane's bit of a mask held in scalar registers.
-__device__ __forceinline__ uint32_t lane_bit(uint64_t mask) {
-  uint32_t r;
-  asm("v_cndmask_b32 %0, 0, 1, %1" : "=v"(r) : "s"(mask));
-  return r;
+template <typename T>
+__device__ __forceinline__ T pick(uint64_t mask, T a, T b) {
+  return __builtin_amdgcn_inverse_ballot_w64(mask) ? b : a;
 }
 
 // f(integral_constant 0), ..., f(integral_constant N - 1), and downwards.
@@ -679,7 +653,7 @@ __device__ __forceinline__ void values_rows_grouped(
   // slot k's prefix product from its bits
   auto extend = [&](int k, T b, T cb) __attribute__((always_inline)) {
     const T bv = to_vgpr(b);
-    const T c = pick_neg(in_k[k], bv, to_vgpr(cb));
+    const T c = pick(in_k[k], -bv, to_vgpr(cb));
 #pragma unroll
     for (int m = 0; m < N; ++m) P[k][m] = P[k - 1][m] * fmaT(node8_t(nc, m), c, bv);
   };
@@ -775,7 +749,7 @@ __device__ __forceinline__ void values_rows_grouped(
       if (TOP + 1 + i > s) extend(TOP + 1 + i, r.b[i], r.cb[i]);
     // slot 0 (the row's own factor, leaf values folded in), last in the order
     const T bv0 = to_vgpr(r.bm);
-    const T c0 = pick_neg(in0, bv0, pick(in0a, to_vgpr(r.cB), to_vgpr(r.cA)));
+    const T c0 = pick(in0, -bv0, pick(in0a, to_vgpr(r.cB), to_vgpr(r.cA)));
     T H[N];
     T q0 = P[ND][0];
 #pragma unroll
@@ -961,7 +935,7 @@ __device__ __forceinline__ void values_rows_batched(
 #pragma unroll
         for (int k = 0; k < BS; ++k) {
           in[k] = inside(x[k], l[k], u[k], (fw[k] & kMissingOkBit) != 0);
-          w |= lane_bit(in[k]) << k;
+          w |= pick(in[k], 0u, 1u) << k;
         }
         bits[b] = w;
         float run_[N];
@@ -969,7 +943,7 @@ __device__ __forceinline__ void values_rows_batched(
         for (int m = 0; m < N; ++m) run_[m] = P[b][m];
         auto extend = [&](int k) __attribute__((always_inline)) {
           const float bv = to_vgpr(bj[k]);
-          const float c = pick_neg(in[k], bv, to_vgpr(cj[k]));
+          const float c = pick(in[k], -bv, to_vgpr(cj[k]));
 #pragma unroll
           for (int m = 0; m < N; ++m) run_[m] *= __builtin_fmaf(rule8_t32(m), c, bv);
         };
@@ -989,7 +963,7 @@ __device__ __forceinline__ void values_rows_batched(
     const uint64_t inA = inside(x0, lo0, hi0, (f0w & kMissingOkBit) != 0);
     const uint64_t inB = inside(x0, loB, hiB, mokB);
     const float bv0 = to_vgpr(bm);
-    const float c0 = pick(inA, pick_neg(inB, bv0, to_vgpr(cB)), to_vgpr(cA));
+    const float c0 = pick(inA, pick(inB, -bv0, to_vgpr(cB)), to_vgpr(cA));
     static_for<NB>([&](auto bc) __attribute__((always_inline)) {
       constexpr int b = decltype(bc)::value;
       if (b == nb - 1) {
