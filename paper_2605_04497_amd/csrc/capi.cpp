@@ -379,6 +379,7 @@ void free_device(DeviceTable& d) {
                   d.lfeat,  d.segs,    d.seg_feat, d.mlfeat, d.msegs,  d.mseg_feat,
                   d.srow32, d.srow64,  d.msrow32, d.msrow64,
                   d.walk.row32, d.walk.row64, d.walk.coef32, d.walk.coef64,
+                  d.bkt_begin, d.bkt_group, d.mbkt_begin, d.mbkt_group,
                   d.mwalk.row32, d.mwalk.row64, d.mwalk.coef32, d.mwalk.coef64};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -657,6 +658,8 @@ void issue_values(const qts_ensemble* ens, const float* X, int64_t M, int64_t ld
                                              : plain_arrays(ens->dev, ens->host);
   const std::vector<Bucket>& bks = ens->merge_siblings ? h.mbuckets : h.buckets;
   launch_slot0(arr, value_rows(ens), leaf, fp64, slot0, ln.main);
+  // a call with leaf values of its own is a training step's (launch_values)
+  const bool per_row = leaf != ens->dev.leaf_val;
   // wide feature spaces: X transposed into the scratch, the accumulator
   // [K][F][M], transposed into phi at the end
   const bool fmajor = wide_features(h.F);
@@ -685,30 +688,33 @@ void issue_values(const qts_ensemble* ens, const float* X, int64_t M, int64_t ld
     // one stream, buckets and chunks in order, adds without atomics
     launch_fill_zero(a, n, ln.main);
     TimedScope ts(0, timed ? ln.main : nullptr, timed);
-    for (const Bucket& bk : bks)
-      launch_values(h, ens->dev, arr, bk, fp64, Xk, M, ldk, slot0, a, nullptr,
-                    ens->vshape[pol_index(ens)][fp64 ? 1 : 0][cap_index(bk.dmax)],
-                    nodes_of(ens), ln.main, true);
+    for (const BucketSpan& sp : bucket_spans(bks, true))
+      launch_values(h, ens->dev, arr, sp, fp64, Xk, M, ldk, slot0, a, nullptr,
+                    ens->vshape[pol_index(ens)][fp64 ? 1 : 0][cap_index(sp.dmax())],
+                    nodes_of(ens), ln.main, per_row, true);
     ts.done();
     finish();
     return;
   }
   if (direct_call(ens, M, fp64)) {
     TimedScope ts(0, timed ? ln.main : nullptr, timed);
-    launch_values(h, ens->dev, arr, bks[0], fp64, X, M, ldx, slot0, nullptr, phi,
+    launch_values(h, ens->dev, arr, bucket_spans(bks, true)[0], fp64, X, M, ldx, slot0, nullptr, phi,
                   ens->vshape[pol_index(ens)][fp64 ? 1 : 0][cap_index(bks[0].dmax)],
-                  nodes_of(ens), ln.main);
+                  nodes_of(ens), ln.main, per_row);
     ts.done();
     return;
   }
   launch_fill_zero(a, n, ln.main);
   TimedScope ts(0, timed ? ln.main : nullptr, timed);
-  ln.fork((int)bks.size());
-  for (size_t i = 0; i < bks.size(); ++i) {
-    const Bucket& bk = bks[i];
-    launch_values(h, ens->dev, arr, bk, fp64, Xk, M, ldk, slot0, a, nullptr,
-                  ens->vshape[pol_index(ens)][fp64 ? 1 : 0][cap_index(bk.dmax)], nodes_of(ens),
-                  ln.pick((int)i));
+  // one launch per capacity, over all output groups (7 outputs, 350 trees of
+  // depth 6, 4099 rows: 340 us with a launch per group, 232 with one)
+  const std::vector<BucketSpan> spans = bucket_spans(bks, false);
+  ln.fork((int)spans.size());
+  for (size_t i = 0; i < spans.size(); ++i) {
+    const BucketSpan& sp = spans[i];
+    launch_values(h, ens->dev, arr, sp, fp64, Xk, M, ldk, slot0, a, nullptr,
+                  ens->vshape[pol_index(ens)][fp64 ? 1 : 0][cap_index(sp.dmax())], nodes_of(ens),
+                  ln.pick((int)i), per_row);
   }
   ln.join();
   ts.done();
@@ -854,9 +860,9 @@ void issue_backward(const qts_ensemble* ens, const float* X, int64_t M, int64_t 
     const PathArrays arr = ens->merge_siblings ? merged_arrays(ens->dev, ens->host)
                                                : plain_arrays(ens->dev, ens->host);
     TimedScope ts(2, timed ? ln.main : nullptr, timed);
-    for (const Bucket& bk : bks)
-      launch_adjoint(h, ens->dev, arr, bk, fp64, X, grad_phi, M, ldx, scratch,
-                     ens->ashape[pol_index(ens)][fp64 ? 1 : 0][cap_index(bk.dmax)],
+    for (const BucketSpan& sp : bucket_spans(bks, false))
+      launch_adjoint(h, ens->dev, arr, sp, fp64, X, grad_phi, M, ldx, scratch,
+                     ens->ashape[pol_index(ens)][fp64 ? 1 : 0][cap_index(sp.dmax())],
                      nodes_of(ens), ln.main, L);
     ts.done();
     launch_sum_rows(scratch, nsb, L, grad_leaf, ln.main);
@@ -868,11 +874,12 @@ void issue_backward(const qts_ensemble* ens, const float* X, int64_t M, int64_t 
   const std::vector<Bucket>& bks = ens->merge_siblings ? h.mbuckets : h.buckets;
   const PathArrays arr = ens->merge_siblings ? merged_arrays(ens->dev, ens->host)
                                              : plain_arrays(ens->dev, ens->host);
-  ln.fork((int)bks.size());
-  for (size_t i = 0; i < bks.size(); ++i) {
-    const Bucket& bk = bks[i];
-    launch_adjoint(h, ens->dev, arr, bk, fp64, X, grad_phi, M, ldx, grad_leaf,
-                   ens->ashape[pol_index(ens)][fp64 ? 1 : 0][cap_index(bk.dmax)], nodes_of(ens),
+  const std::vector<BucketSpan> spans = bucket_spans(bks, false);
+  ln.fork((int)spans.size());
+  for (size_t i = 0; i < spans.size(); ++i) {
+    const BucketSpan& sp = spans[i];
+    launch_adjoint(h, ens->dev, arr, sp, fp64, X, grad_phi, M, ldx, grad_leaf,
+                   ens->ashape[pol_index(ens)][fp64 ? 1 : 0][cap_index(sp.dmax())], nodes_of(ens),
                    ln.pick((int)i));
   }
   ln.join();
@@ -1081,6 +1088,22 @@ int qts_load_ensemble_grouped(const qts_tree_arrays* trees, const int32_t* tree_
         check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
       }
       d.leaf_val = upload(h.leaf_value, s);
+      if (h.n_groups > 1) {
+        std::vector<int32_t> begin, group, mbegin, mgroup;
+        for (const Bucket& bk : h.buckets) {
+          begin.push_back(bk.path_begin);
+          group.push_back(bk.group);
+        }
+        for (const Bucket& bk : h.mbuckets) {
+          mbegin.push_back(bk.path_begin);
+          mgroup.push_back(bk.group);
+        }
+        d.bkt_begin = upload(begin, s);
+        d.bkt_group = upload(group, s);
+        d.mbkt_begin = upload(mbegin, s);
+        d.mbkt_group = upload(mgroup, s);
+        check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
+      }
       {
         PairTable pt = build_pair_table(h);
         e->pair_classes = pt.classes;
@@ -1588,9 +1611,9 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
           float best_ms = 1e30f;
           for (int waves : {4, 6, 8})
             for (int items : {4096, 8192, 16384, 32768, 65536}) {
-              const ValuesShape cand{waves, items};
+              const ValuesShape cand{waves, items, true};
               const float ms = time_ms(3, [&] {
-                launch_values(h, d, arr, bk, fp64, X, Mt, ldt, slot0.p, (double*)acc.p, nullptr,
+                launch_values(h, d, arr, BucketSpan{&bk, 1, 0}, fp64, X, Mt, ldt, slot0.p, (double*)acc.p, nullptr,
                               cand, nodes_of(ens), s);
               });
               if (ms < best_ms) {
@@ -1600,6 +1623,7 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
             }
           tune_cache_put(key, best.waves_per_block, best.items);
         }
+        best.tuned = true;
         ens->vshape[pol][pi][cap_index(bk.dmax)] = best;
       }
     }
@@ -1622,9 +1646,9 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
           float best_ms = 1e30f;
           for (int waves : {4, 6, 8})
             for (int items : {4096, 8192, 16384, 32768, 65536}) {
-              const ValuesShape cand{waves, items};
+              const ValuesShape cand{waves, items, true};
               const float ms = time_ms(3, [&] {
-                launch_adjoint(h, d, arr, bk, fp64, X, G, Mt, ldt, (double*)gl.p, cand,
+                launch_adjoint(h, d, arr, BucketSpan{&bk, 1, 0}, fp64, X, G, Mt, ldt, (double*)gl.p, cand,
                                nodes_of(ens), s);
               });
               if (ms < best_ms) {
@@ -1634,6 +1658,7 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
             }
           tune_cache_put(key, best.waves_per_block, best.items);
         }
+        best.tuned = true;
         ens->ashape[pol][pi][cap_index(bk.dmax)] = best;
       }
     }

@@ -416,14 +416,15 @@ HostTable build_host_table(const qts_tree_arrays& t, int32_t F, int32_t n_groups
   // the rows of capacity-8 buckets, numbered in bucket order, index the
   // short-row records of each table
   auto number_short = [](std::vector<Bucket>& bks, const std::vector<PathHdr>& hdr) {
-    int32_t n = 0;
+    int32_t n = 0, top = 0;
     for (Bucket& bk : bks)
       if (bk.dmax == 8) {
         bk.srow_begin = n;
         n += bk.path_end - bk.path_begin;
         for (int32_t p = bk.path_begin; p < bk.path_end; ++p)
-          bk.top = std::max(bk.top, hdr[(size_t)p].d - 4);
+          top = std::max(top, hdr[(size_t)p].d - 4);
       }
+    for (Bucket& bk : bks) bk.top = top;  // one launch may take several buckets
   };
   number_short(h.buckets, h.hdr);
   number_short(h.mbuckets, h.mhdr);

@@ -3,6 +3,7 @@
 // tiled transposes (the feature-major layouts of wide feature spaces).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <utility>
@@ -11,9 +12,16 @@
 
 namespace qts {
 
-size_t raise_lds_limit(const void* fn) {
+namespace {
+
+struct FnLimits {
+  size_t lds;  // usable dynamic LDS bytes
+  int vgprs;
+};
+
+FnLimits fn_limits(const void* fn) {
   static std::mutex mu;
-  static std::map<std::pair<const void*, int>, size_t> done;
+  static std::map<std::pair<const void*, int>, FnLimits> done;
   int dev = 0;
   check_hip(hipGetDevice(&dev), "hipGetDevice");
   std::lock_guard<std::mutex> lock(mu);
@@ -22,11 +30,31 @@ size_t raise_lds_limit(const void* fn) {
   if (it != done.end()) return it->second;
   hipFuncAttributes fa;
   check_hip(hipFuncGetAttributes(&fa, fn), "hipFuncGetAttributes");
-  const size_t limit = (size_t)kMaxLdsBytes - fa.sharedSizeBytes;
-  check_hip(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)limit),
+  const FnLimits l{(size_t)kMaxLdsBytes - fa.sharedSizeBytes, fa.numRegs};
+  check_hip(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.lds),
             "hipFuncSetAttribute");
-  done.emplace(key, limit);
-  return limit;
+  done.emplace(key, l);
+  return l;
+}
+
+}  // namespace
+
+size_t raise_lds_limit(const void* fn) { return fn_limits(fn).lds; }
+
+int resident_waves(const void* fn, size_t lds) {
+  constexpr int kSimds = 4, kVgprs = 512, kMostWaves = 8;
+  const int regs = std::max(8, (fn_limits(fn).vgprs + 7) / 8 * 8);
+  const int per_cu = kSimds * std::min(kMostWaves, kVgprs / regs);
+  const int by_lds = (int)std::max<size_t>(1, kMaxLdsBytes / std::max<size_t>(lds, 1024));
+  int best = 8, most = 0;
+  for (int w : {8, 6, 4}) {
+    const int n = std::min(by_lds, std::max(1, per_cu / w)) * w;
+    if (n > most) {
+      most = n;
+      best = w;
+    }
+  }
+  return best;
 }
 
 __global__ void __launch_bounds__(256) fill_zero_kernel(double* __restrict__ p, int64_t n) {

@@ -78,62 +78,104 @@ __device__ __forceinline__ T node8_w(const NodeConsts<T>& nc, int m) {
   else return nc.w[m];
 }
 
-// Add a row's leaf-value gradient, summed over the wave's 64 samples.  det:
-// grad_leaf is this sample block's own row of partial sums, and every leaf
-// belongs to one row, so a plain store suffices (and keeps the result
-// independent of scheduling).
+// Add to a leaf's gradient in memory.  det: grad_leaf is this sample block's
+// own row of partial sums, and every leaf belongs to one row, so a plain store
+// suffices (and keeps the result independent of scheduling).
 __device__ __forceinline__ void leaf_add(double* grad_leaf, int leaf, double v, bool det) {
   if (det) grad_leaf[leaf] = v;
   else if (v != 0.0) unsafeAtomicAdd(&grad_leaf[leaf], v);
 }
 
-// The path loop of one workgroup.  NANS: the tile holds a NaN, so the
-// missing-value rule is evaluated; otherwise plain interval tests suffice.
-// ADJ: adjoint mode.  phi is linear in the leaf value, so d phi[s, f_j] /
-// d val = c_j LOO_j; instead of scattering val c_j LOO_j into the phi tile,
-// each lane gathers g[s, f_j] c_j LOO_j from the upstream-gradient tile gs,
-// the wave sums its 64 samples in FP64 (DPP reduction into lane 63) and adds
-// the result to grad_leaf.
-template <typename T, int DMAX, int NH, bool STORE_G, bool NANS, bool ADJ, int NN>
-__device__ __forceinline__ void values_paths(
+// Leaf A (which = 0) or B (1) of a row; -1: a single path has no B.
+__device__ __forceinline__ int leaf_of(const PathHdr* hdr, const SidePath* side, int row,
+                                       int which) {
+  if (which == 0) return hdr[row].leaf;
+  const int sidx = side == nullptr ? -1 : hdr[row].tree;
+  return sidx < 0 ? -1 : side[sidx].leaf_b;
+}
+
+// Sums the rows' leaf gradients over the wave's 64 samples and adds them to the workgroup's LDS sums,
+// part[2 (row - pb) + which], or without them (part null) to memory.
+struct LeafSums {
+  double* part;
+  double* grad_leaf;
+  const PathHdr* hdr;
+  const SidePath* side;
+  int pb, lane;
+  bool det;
+  double u_prev = 0.0, w_prev = 0.0;  // rows of the four that wait
+
+  // One row at a time (no registers to let rows wait).
+  __device__ __forceinline__ void add_row(double a, double b, int row) const {
+    double z = fold16(fold32(a, b), 0.0);
+    z += dpp_lanes<0x128>(z);
+    z += dpp_lanes<0x141>(z);
+    z += dpp_lanes<0xb1>(z);
+    z += dpp_lanes<0x4e>(z);
+    if ((lane & 31) == 0) put(z, row, lane >> 5);
+  }
+
+  __device__ __forceinline__ void put(double z, int row, int which) const {
+    if (part != nullptr) {
+      __hip_atomic_fetch_add(&part[2 * (row - pb) + which], z, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else {
+      const int leaf = leaf_of(hdr, side, row, which);
+      if (leaf >= 0) leaf_add(grad_leaf, leaf, z, det);
+    }
+  }
+
+  // Four rows together; a, b: leaf A's and B's terms of row `row`, the i-th of the wave's
+  // consecutive rows; last: no row follows
+  __device__ __forceinline__ void add(double a, double b, int i, int row, bool last) {
+    const double ab = fold32(a, b);
+    const int q = i & 3;
+    if ((q & 1) == 0 && !last) {
+      u_prev = ab;
+      return;
+    }
+    const double w = (q & 1) ? fold16(u_prev, ab) : fold16(ab, 0.0);
+    if (q < 2 && !last) {
+      w_prev = w;
+      return;
+    }
+    const double z = q < 2 ? wave_sum8(w, 0.0, lane) : wave_sum8(w_prev, w, lane);
+    const int v = wave_sum8_index(lane);
+    if ((lane & 7) != 0 || (v >> 1) > q) return;
+    put(z, row - (q - (v >> 1)), v & 1);
+  }
+};
+
+// The adjoint's path loop for rows of more than 8 features and for FP64.  NANS:
+// the tile holds a NaN, so the missing-value rule is evaluated; otherwise
+// plain interval tests suffice.  phi is linear in the leaf value, so
+// d phi[s, f_j] / d val = c_j LOO_j: each lane gathers g[s, f_j] c_j LOO_j from
+// the upstream-gradient tile gs, and the wave sums its 64 samples in FP64.
+template <typename T, int DMAX, int NH, bool STORE_G, bool NANS, int NN>
+__device__ __forceinline__ void adjoint_paths(
     const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
     const float* __restrict__ lo, const float* __restrict__ hi, const T* __restrict__ bb,
     const T* __restrict__ cbb, const SidePath* __restrict__ side,
-    const Slot0<T>* __restrict__ z0, const float* xs, double* as, const T* gs,
-    double* __restrict__ grad_leaf, int pb, int pe, int wave, int nw, int lane, const T* tv,
-    const NodeConsts<T>& nc, bool det = false) {
+    const float* xs, const T* gs, LeafSums sums, int pb, int pe, int wave, int nw, int lane,
+    const T* tv, const NodeConsts<T>& nc) {
   constexpr int NB = DMAX / 8;  // feature batches
   for (int p = pb + wave; p < pe; p += nw) {
     const int d = ldu(&hdr[p].d);
     const int off = ldu(&hdr[p].off);
-    const int leaf = ldu(&hdr[p].leaf);
-    // First order: slot 0 comes from Slot0 (leaf value folded in; the row's
-    // own b_0, 1 - b_0 are not read).  Adjoint of a merged sibling pair:
+    // A merged sibling pair:
     // slot 0 is the parent's split feature L, made inert in the products
     // (b = 1, c = 0), so the sweep yields w Q_j(m) = w prod_{k >= 1, k != j} F_k(m);
     // then
     //   d/dvA = sum_m F_A(m) R(m) + g_L c_A sum_m w Q_0(m),
     //   R(m) = sum_{j >= 1} g_j c_j w Q_j(m)   (shared by A and B),
     // and likewise for B with F_B and c_B.
-    const int sidx = (!ADJ || side == nullptr) ? -1 : ldu(&hdr[p].tree);
-    const bool merged = sidx >= 0;  // adjoint only
-    const bool own0 = !ADJ || merged;  // slot 0 not taken from the row's elements
-    T bm = T(0), cA = T(0), cB = T(0);
+    const int sidx = side == nullptr ? -1 : ldu(&hdr[p].tree);
+    const bool merged = sidx >= 0;  // slot 0 not taken from the row's elements
     T ba = T(0), cba = T(0), bb2 = T(0), cbb2 = T(0);
     float loB = 0.f, hiB = 0.f;
     bool mokB = false;
-    int leafB = 0;
-    if (!ADJ) {
-      const Slot0<T>* z = z0 + p;
-      bm = ldu(&z->bm);
-      cA = ldu(&z->ca);
-      cB = ldu(&z->cb);
-      loB = ldu(&z->lo_b);
-      hiB = ldu(&z->hi_b);
-      mokB = ldu(&z->mok_b) != 0;
-    } else if (merged) {
+    if (merged) {
       const SidePath* sp = side + sidx;
-      leafB = ldu(&sp->leaf_b);
       loB = ldu(&sp->lo_b);
       hiB = ldu(&sp->hi_b);
       mokB = ldu(&sp->mok_b) != 0;
@@ -141,14 +183,13 @@ __device__ __forceinline__ void values_paths(
       cba = (T)ldu(&sp->cb_a);
       bb2 = (T)ldu(&sp->b_b);
       cbb2 = (T)ldu(&sp->cb_b);
-      bm = T(1);
     }
-    // b_j of slot j (slot 0 of a merged path: bm)
-    auto bload = [&](int j) -> T { return (j == 0 && own0) ? bm : ldu(bb + off + j); };
+    // b_j of slot j (slot 0 of a merged path: 1, inert)
+    auto bload = [&](int j) -> T { return (j == 0 && merged) ? T(1) : ldu(bb + off + j); };
     double gacc = 0.0;
-    double gaccB = 0.0;          // adjoint of a merged path: B's gradient
-    T oc0A = T(0), oc0B = T(0);  // adjoint of a merged path: c_A and c_B
-    T q0 = T(0);                 // adjoint of a merged path: sum_m w Q_0(m)
+    double gaccB = 0.0;          // a merged path: B's gradient
+    T oc0A = T(0), oc0B = T(0);  // a merged path: c_A and c_B
+    T q0 = T(0);                 // a merged path: sum_m w Q_0(m)
     const int nb = (d + 7) >> 3;  // batches in use; slots [d, 8 nb) are inert
 
     // c_j per slot, eight slots per batch
@@ -183,18 +224,14 @@ __device__ __forceinline__ void values_paths(
           }
           const bool upper = !(x[k] >= u[k]);
           cf[jb + k] = (lower & upper) ? cbl[k] : -bl[k];
-          if (b == 0 && k == 0 && own0) {
+          if (b == 0 && k == 0 && merged) {
             bool lowerB;
             if (NANS) lowerB = mokB ? !(x[0] < loB) : (x[0] >= loB);
             else lowerB = x[0] >= loB;
             const bool upperB = !(x[0] >= hiB);
-            if (ADJ) {
-              oc0A = (lower & upper) ? cba : -ba;
-              oc0B = (lowerB & upperB) ? cbb2 : -bb2;
-              cf[0] = T(0);
-            } else {
-              cf[0] = (lower & upper) ? cA : ((lowerB & upperB) ? cB : -bm);
-            }
+            oc0A = (lower & upper) ? cba : -ba;
+            oc0B = (lowerB & upperB) ? cbb2 : -bb2;
+            cf[0] = T(0);
           }
         }
       }
@@ -226,9 +263,9 @@ __device__ __forceinline__ void values_paths(
       T S[NH];
 #pragma unroll
       for (int m = 0; m < NH; ++m) S[m] = T(1);
-      T R[ADJ ? NH : 1];
+      T R[NH];
 #pragma unroll
-      for (int m = 0; m < (ADJ ? NH : 1); ++m) R[m] = T(0);
+      for (int m = 0; m < NH; ++m) R[m] = T(0);
 #pragma unroll
       for (int b = NB - 1; b >= 0; --b) {
         if (b < nb) {
@@ -256,12 +293,12 @@ __device__ __forceinline__ void values_paths(
             const int j = jb + k;
             if (j < d) {
               const int f = ldu(feat + off + j) & kFeatureMask;
-              if (ADJ && merged) {
+              if (merged) {
                 if (j > 0) {
                   const T gc = gs[f * kTileStride + lane] * cf[j];
 #pragma unroll
                   for (int m = 0; m < NH; ++m)
-                    R[ADJ ? m : 0] = fmaT(gc, Pb[k][m] * S[m], R[ADJ ? m : 0]);
+                    R[m] = fmaT(gc, Pb[k][m] * S[m], R[m]);
                 } else {
 #pragma unroll
                   for (int m = 0; m < NH; ++m) q0 = fmaT(Pb[k][m], S[m], q0);
@@ -270,13 +307,7 @@ __device__ __forceinline__ void values_paths(
                 T dot = Pb[k][0] * S[0];
 #pragma unroll
                 for (int m = 1; m < NH; ++m) dot = fmaT(Pb[k][m], S[m], dot);
-                if (ADJ) {
-                  gacc += (double)(gs[f * kTileStride + lane] * cf[j] * dot);
-                } else {
-                  const double c = (double)(cf[j] * dot);
-                  __hip_atomic_fetch_add(&as[f * kTileStride + lane], c, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_WORKGROUP);
-                }
+                gacc += (double)(gs[f * kTileStride + lane] * cf[j] * dot);
               }
             }
             if (j > 0) {
@@ -289,35 +320,29 @@ __device__ __forceinline__ void values_paths(
           }
         }
       }
-      if (ADJ && merged) {
+      if (merged) {
         T sa = T(0), sb = T(0);
 #pragma unroll
         for (int m = 0; m < NH; ++m) {
-          sa = fmaT(fmaT(tv[m0 + m], oc0A, ba), R[ADJ ? m : 0], sa);
-          sb = fmaT(fmaT(tv[m0 + m], oc0B, bb2), R[ADJ ? m : 0], sb);
+          sa = fmaT(fmaT(tv[m0 + m], oc0A, ba), R[m], sa);
+          sb = fmaT(fmaT(tv[m0 + m], oc0B, bb2), R[m], sb);
         }
         gacc += (double)sa;
         gaccB += (double)sb;
       }
     }
-    if (ADJ) {
-      if (merged) {
-        const T gL = gs[(ldu(feat + off) & kFeatureMask) * kTileStride + lane];
-        gacc += (double)(gL * oc0A * q0);
-        gaccB += (double)(gL * oc0B * q0);
-        gaccB = wave_sum_last(gaccB);
-        if (lane == 63) leaf_add(grad_leaf, leafB, gaccB, det);
-      }
-      gacc = wave_sum_last(gacc);
-      if (lane == 63) leaf_add(grad_leaf, leaf, gacc, det);
+    if (merged) {
+      const T gL = gs[(ldu(feat + off) & kFeatureMask) * kTileStride + lane];
+      gacc += (double)(gL * oc0A * q0);
+      gaccB += (double)(gL * oc0B * q0);
     }
+    sums.add_row(gacc, gaccB, p);
   }
 }
 
 
 // Wide scalar loads of a ShortRow (dword-aligned vectors of 4 and 16 words).
 typedef int32_t row_v4 __attribute__((ext_vector_type(4), aligned(4)));
-typedef int32_t row_v8 __attribute__((ext_vector_type(8), aligned(4)));
 typedef int32_t row_v16 __attribute__((ext_vector_type(16), aligned(4)));
 static_assert(offsetof(ShortRow<float>, xoff) == 16 && offsetof(ShortRow<float>, lo) == 80 &&
                   offsetof(ShortRow<float>, b) == 144 && offsetof(ShortRow<float>, cb) == 176 &&
@@ -334,25 +359,14 @@ struct ShortRowRegs {
 };
 
 // The record of row p in four wide scalar loads, all issued before any is
-// used.  AO = false leaves out the accumulator offsets (twice the sample
-// tile's: the caller derives them where it adds, which saves 8 SGPRs).
-template <typename T, bool AO = true>
+// used.
+template <typename T>
 __device__ __forceinline__ ShortRowRegs<T> load_short_row(const ShortRow<T>* rows, int row0,
                                                           int p) {
   ShortRowRegs<T> r;
   const int32_t* rw = reinterpret_cast<const int32_t*>(rows + (p - row0));
   const row_v4 hd = ldu(reinterpret_cast<const row_v4*>(rw));
-  row_v16 of;
-  if constexpr (AO) {
-    of = ldu(reinterpret_cast<const row_v16*>(rw + 4));
-  } else {
-    const row_v8 o8 = ldu(reinterpret_cast<const row_v8*>(rw + 4));
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      of[k] = o8[k];
-      of[8 + k] = 2 * o8[k];
-    }
-  }
+  const row_v16 of = ldu(reinterpret_cast<const row_v16*>(rw + 4));
   const row_v16 bd = ldu(reinterpret_cast<const row_v16*>(rw + 20));
   if constexpr (sizeof(T) == 4) {
     const row_v16 bc = ldu(reinterpret_cast<const row_v16*>(rw + 36));
@@ -394,21 +408,29 @@ __device__ __forceinline__ ShortRowRegs<T> load_short_row(const ShortRow<T>* row
 // evaluated as usual, each with the prefix product through it in the same
 // step, so the shared count picks one entry into a single straight run of
 // code; inert padding slots (b = 1, c = 0) give a factor of exactly 1.
-template <typename T, int NH, bool NANS, bool KEEP = true>
+// ND: slots 1..ND of the bucket's rows can be real; the slots past it are inert
+// in every row, and leaving out a factor of exactly 1 changes no bit.
+template <typename T, int NH, int ND, bool NANS>
 __device__ __forceinline__ void values_rows_shared(
     const ShortRow<T>* __restrict__ rows, int row0, const Slot0<T>* __restrict__ z0,
     const float* xs, double* as, int pb, int pe, int wave, int nw, int lane, const T* tv,
     const NodeConsts<T>& nc) {
   constexpr bool kScalarT = NH == 8;
+  // the last slot whose prefix product is formed: slot 7's is only summed
+  constexpr int kLastP = ND < 7 ? ND : 6;
+  // 1 in a register the compiler knows nothing of: slot 0's node sum stays a
+  // chain of FMAs on the rounded prefix products, as with ND = 7
+  T one = T(1);
+  asm volatile("" : "+v"(one));
   const int run = (pe - pb + nw - 1) / nw;
   const int p_first = pb + wave * run;
   const int p_last = min(pe, p_first + run);
-  T cf[8];       // c_j of the current row
-  T G[8][NH];    // F_j(m) of the current row
+  T cf[ND + 1];  // c_j of the current row
+  T G[ND + 1][NH];  // F_j(m) of the current row
   // prefix products in the order 1..7, 0: P[q] = w prod over the first q
   // slots of that order (slot q + 1 at position q); P[1..s] depend only on
   // shared slots and are kept from the previous row
-  T P[7][NH];
+  T P[ND + 1][NH];
 #pragma unroll
   for (int m = 0; m < NH; ++m) P[0][m] = kScalarT ? node8_w(nc, m) : nc.w[m];
   const char* xl = reinterpret_cast<const char*>(xs + lane);
@@ -417,8 +439,7 @@ __device__ __forceinline__ void values_rows_shared(
     // the record and slot 0, all loads issued before any is used.  An empty
     // row (d = 0) is walked too: its slots are inert and its Slot0 factor
     // is 0, so it adds exact zeros.
-    // the 8-node FP64 walk derives the accumulator offsets (SGPR room)
-    const ShortRowRegs<T> r = load_short_row<T, !(sizeof(T) == 8 && !KEEP)>(rows, row0, p);
+    const ShortRowRegs<T> r = load_short_row<T>(rows, row0, p);
     const Slot0<T>* z = z0 + p;
     const T bm = ldu(&z->bm);
     const T cA = ldu(&z->ca);
@@ -427,7 +448,7 @@ __device__ __forceinline__ void values_rows_shared(
     const float hiB = ldu(&z->hi_b);
     const bool mokB = ldu(&z->mok_b) != 0;
     const int d = r.d;
-    const int s = (KEEP && p != p_first) ? r.share : 0;
+    const int s = p != p_first ? r.share : 0;
     const int mok = r.mok;
     const auto& xo = r.xo;
     const auto& ao = r.ao;
@@ -435,11 +456,11 @@ __device__ __forceinline__ void values_rows_shared(
     const auto& u = r.u;
     const auto& bl = r.bl;
     const auto& cbl = r.cbl;
-    float x[8];
+    float x[ND + 1];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = *reinterpret_cast<const float*>(xl + xo[k]);
+    for (int k = 0; k <= ND; ++k) x[k] = *reinterpret_cast<const float*>(xl + xo[k]);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k <= ND; ++k) {
       if (k == 0 || k > s) {
         bool lower;
         if (NANS) {
@@ -473,29 +494,31 @@ __device__ __forceinline__ void values_rows_shared(
           for (int m = 0; m < NH; ++m) G[k][m] = fmaT(tv[m], c, b);
         }
         // the prefix through this slot (every later slot is evaluated too)
-        if (k >= 1 && k <= 6) {
+        if (k >= 1 && k <= kLastP) {
 #pragma unroll
           for (int m = 0; m < NH; ++m) P[k][m] = P[k - 1][m] * G[k][m];
         }
       }
     }
-    // slot 0, last in the order: its leave-one-out product is P[6] F_7
+    // slot 0, last in the order: its leave-one-out product is that of slots
+    // 1..ND (P[6] F_7 for ND = 7)
     {
-      T dot = P[6][0] * G[7][0];
+      T dot = P[kLastP][0] * (ND < 7 ? one : G[ND][0]);
 #pragma unroll
-      for (int m = 1; m < NH; ++m) dot = fmaT(P[6][m], G[7][m], dot);
+      for (int m = 1; m < NH; ++m)
+        dot = fmaT(P[kLastP][m], ND < 7 ? one : G[ND][m], dot);
       __hip_atomic_fetch_add(reinterpret_cast<double*>(al + ao[0]), (double)(cf[0] * dot),
                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    // slots 7..1: suffix products, starting from slot 0's factor.  A full
-    // row (d = 8, most rows of depth-8 trees) takes a sweep without the
+    // slots ND..1: suffix products, starting from slot 0's factor.  A full
+    // row (most rows of full trees) takes a sweep without the
     // per-slot test of j < d.
     T S[NH];
 #pragma unroll
     for (int m = 0; m < NH; ++m) S[m] = G[0][m];
     auto sweep = [&](auto full) __attribute__((always_inline)) {
 #pragma unroll
-      for (int q = 6; q >= 0; --q) {
+      for (int q = ND - 1; q >= 0; --q) {
         const int j = q + 1;
         if (decltype(full)::value || j < d) {
           T dot = P[q][0] * S[0];
@@ -511,7 +534,7 @@ __device__ __forceinline__ void values_rows_shared(
         }
       }
     };
-    if (d == 8) sweep(std::true_type{});
+    if (d == ND + 1) sweep(std::true_type{});
     else sweep(std::false_type{});
   }
 }
@@ -1159,26 +1182,57 @@ __device__ __forceinline__ void values_rows_long(
   }
 }
 
+// The buckets of a launch over more than one: first rows and output groups of
+// the n buckets (n = 1: all rows belong to group grp).
+struct BucketIndex {
+  const int32_t* begin;
+  const int32_t* group;
+  int32_t n;
+  int32_t grp;
+};
+
 // The rows and tile features of one work item.  Work item b is (sample block
 // b mod nsb, row chunk b div nsb).  Ordinarily a chunk is `chunk` consecutive
 // rows of the bucket and the tile holds every feature; with segments (wide
 // feature spaces) chunk c is segment c, whose tile holds its own feature
-// list, which the rows' elements index (lfeat).
+// list, which the rows' elements index (lfeat).  A launch over several buckets
+// (BucketSpan) cuts each bucket into chunks of its own, in bucket order.
 struct ItemRows {
   int p0, p1;            // rows [p0, p1)
+  int grp;               // their output group
   int nf;                // tile features
   const int32_t* fmap;   // tile feature -> global feature (null: identity)
 };
 
 __device__ __forceinline__ ItemRows item_rows(const Segment* segs, const int32_t* seg_feat,
                                               int ch, int32_t path_begin, int32_t path_end,
-                                              int32_t chunk, int32_t F) {
+                                              int32_t chunk, int32_t F, const BucketIndex& bx) {
   ItemRows ir;
+  ir.grp = bx.grp;
   if (segs != nullptr) {
     ir.p0 = ldu(&segs[ch].row_begin);
     ir.p1 = ldu(&segs[ch].row_end);
     ir.nf = ldu(&segs[ch].nfeat);
     ir.fmap = seg_feat + ldu(&segs[ch].feat_begin);
+    if (bx.n > 1) {
+      int b = 0;
+      while (b + 1 < bx.n && ir.p0 >= ldu(bx.begin + b + 1)) ++b;
+      ir.grp = ldu(bx.group + b);
+    }
+  } else if (bx.n > 1) {
+    int b = 0, c = ch, q0 = path_begin, q1 = path_end;
+    for (;; ++b) {
+      q1 = b + 1 < bx.n ? ldu(bx.begin + b + 1) : path_end;
+      const int n = (q1 - q0 + chunk - 1) / chunk;
+      if (c < n || b + 1 >= bx.n) break;
+      c -= n;
+      q0 = q1;
+    }
+    ir.p0 = q0 + c * chunk;
+    ir.p1 = min(q1, ir.p0 + chunk);
+    ir.grp = ldu(bx.group + b);
+    ir.nf = F;
+    ir.fmap = nullptr;
   } else {
     ir.p0 = path_begin + ch * chunk;
     ir.p1 = min(path_end, ir.p0 + chunk);
@@ -1190,8 +1244,13 @@ __device__ __forceinline__ ItemRows item_rows(const Segment* segs, const int32_t
 
 // tile_f: the features the LDS layout is sized for (F, or kSegFeatures with
 // segments); F: phi's row length.
-// TOP >= 0: the grouped walk over short rows (DMAX = 8, 8 nodes).
-template <typename T, int DMAX, int NH, bool STORE_G, int NN, int TOP>
+// The walk of a first-order instance: values_rows_grouped with TOP = WALK for
+// WALK = 0..4, values_rows_shared with ND = WALK - kPerRow for kPerRow + 3 ..
+// kPerRow + 7 (short rows), values_rows_long for kPerRow, values_rows_batched
+// for kBatched.
+constexpr int kPerRow = 16, kBatched = -2;
+
+template <typename T, int DMAX, int NH, bool STORE_G, int NN, int WALK>
 __global__ void __launch_bounds__(512)
 values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
               const float* __restrict__ lo, const float* __restrict__ hi,
@@ -1200,7 +1259,7 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
               const float* __restrict__ X, int64_t M, int64_t ldx, int32_t F, int32_t tile_f,
               int32_t path_begin, int32_t path_end, int32_t chunk, int32_t nsb,
               const Segment* __restrict__ segs, const int32_t* __restrict__ seg_feat,
-              int32_t ng, int32_t grp, double* __restrict__ acc, void* __restrict__ direct,
+              int32_t ng, BucketIndex bx, double* __restrict__ acc, void* __restrict__ direct,
               int32_t direct_fp64, int32_t plain_add, const ShortRow<T>* __restrict__ srows,
               const WalkRow<T>* __restrict__ wrows, const T* __restrict__ wcoef,
               NodeConsts<T> nc) {
@@ -1216,7 +1275,7 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
   const int sb = item % nsb;
   const int ch = item / nsb;
   const int64_t s0 = (int64_t)sb * kSamplesPerBlock;
-  const ItemRows ir = item_rows(segs, seg_feat, ch, path_begin, path_end, chunk, F);
+  const ItemRows ir = item_rows(segs, seg_feat, ch, path_begin, path_end, chunk, F, bx);
   const int nf = ir.nf;
 
   // stage the sample tile transposed; zero the accumulator; note any NaN.
@@ -1260,27 +1319,27 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
 #pragma unroll
   for (int m = 0; m < NN; ++m) tv[m] = to_vgpr(nc.t[m]);
 
-  if constexpr (TOP >= 0) {
+  if constexpr (DMAX == 8 && WALK < kPerRow) {
     if (any_nan)
-      values_rows_grouped<T, TOP, true>(wrows, wcoef, path_begin, z0, xs, as, pb, pe, wave, nw,
-                                        lane, nc);
-    else
-      values_rows_grouped<T, TOP, false>(wrows, wcoef, path_begin, z0, xs, as, pb, pe, wave, nw,
+      values_rows_grouped<T, WALK, true>(wrows, wcoef, path_begin, z0, xs, as, pb, pe, wave, nw,
                                          lane, nc);
-  } else if constexpr (DMAX == 8) {
-    if (any_nan)
-      values_rows_shared<T, NH, true>(srows, path_begin, z0, xs, as, pb, pe, wave, nw, lane, tv,
-                                      nc);
     else
-      values_rows_shared<T, NH, false>(srows, path_begin, z0, xs, as, pb, pe, wave, nw, lane, tv,
-                                       nc);
-  } else if constexpr (std::is_same<T, float>::value) {
+      values_rows_grouped<T, WALK, false>(wrows, wcoef, path_begin, z0, xs, as, pb, pe, wave, nw,
+                                          lane, nc);
+  } else if constexpr (WALK == kBatched) {
     if (any_nan)
       values_rows_batched<DMAX, true>(hdr, feat, lo, hi, bb, cbb, z0, share, xs, as, pb, pe,
                                       wave, nw, lane);
     else
       values_rows_batched<DMAX, false>(hdr, feat, lo, hi, bb, cbb, z0, share, xs, as, pb, pe,
                                        wave, nw, lane);
+  } else if constexpr (DMAX == 8) {
+    if (any_nan)
+      values_rows_shared<T, NH, WALK - kPerRow, true>(srows, path_begin, z0, xs, as, pb, pe, wave,
+                                                      nw, lane, tv, nc);
+    else
+      values_rows_shared<T, NH, WALK - kPerRow, false>(srows, path_begin, z0, xs, as, pb, pe,
+                                                       wave, nw, lane, tv, nc);
   } else if (any_nan) {
     values_rows_long<T, DMAX, NH, STORE_G, true, NN>(hdr, feat, lo, hi, bb, cbb, z0, share, xs,
                                                      as, pb, pe, wave, nw, lane, tv, nc);
@@ -1300,7 +1359,7 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
       const int64_t s = s0 + r;
       if (s < M) {
         const double v = as[k * kTileStride + r];
-        const int64_t o = ((int64_t)grp * F + ir.fmap[k]) * M + s;
+        const int64_t o = ((int64_t)ir.grp * F + ir.fmap[k]) * M + s;
         if (v != 0.0) {
           if (plain_add) acc[o] += v;
           else unsafeAtomicAdd(&acc[o], v);
@@ -1315,7 +1374,7 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
     const int64_t s = s0 + r;
     if (s < M) {
       const double v = as[k * kTileStride + r];
-      const int64_t o = (s * ng + grp) * F + k;  // phi[s, grp, f]
+      const int64_t o = (s * ng + ir.grp) * F + k;  // phi[s, grp, f]
       if (direct != nullptr) {
         if (direct_fp64) static_cast<double*>(direct)[o] = v;
         else static_cast<float*>(direct)[o] = (float)v;
@@ -1339,21 +1398,26 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
 // where F_A = b_A + t c_A is slot 0's factor of leaf A (a single path: its
 // own), and likewise for leaf B of a merged pair.  The sum over m of
 // F_A(m) R(m) is b_A sum_m R(m) + c_A sum_m t_m R(m).
-template <typename T, int NH, bool NANS>
+// ND as in values_rows_shared.
+template <typename T, int NH, int ND, bool NANS>
 __device__ __forceinline__ void adjoint_rows_shared(
     const ShortRow<T>* __restrict__ rows, int row0, const PathHdr* __restrict__ hdr,
-    const SidePath* __restrict__ side, const float* xs, const T* gs,
-    double* __restrict__ grad_leaf, int pb, int pe, int wave, int nw, int lane, const T* tv,
-    const NodeConsts<T>& nc, bool det) {
+    const SidePath* __restrict__ side, const float* xs, const T* gs, LeafSums sums, int pb, int pe,
+    int wave, int nw, int lane, const T* tv, const NodeConsts<T>& nc) {
   constexpr bool kScalarT = NH == 8;
+  constexpr int kLastP = ND < 7 ? ND : 6;
+  // 1 in a register the compiler knows nothing of: slot 0's node sum stays a
+  // chain of FMAs on the rounded prefix products, as with ND = 7
+  T one = T(1);
+  asm volatile("" : "+v"(one));
   const int run = (pe - pb + nw - 1) / nw;
   const int p_first = pb + wave * run;
   const int p_last = min(pe, p_first + run);
-  T cf[8], gc[8];  // slots 1..7: c_j and g_j c_j of the current row
-  T G[8][NH];      // slots 1..7: F_j(m)
+  T gc[ND + 1];     // slots 1..ND: g_j c_j of the current row
+  T G[ND + 1][NH];  // slots 1..ND: F_j(m)
   // prefix products over slots 1..q (P[q], q = 0..6; w folded in); P[1..s]
   // depend only on shared slots and are kept from the previous row
-  T P[7][NH];
+  T P[ND + 1][NH];
 #pragma unroll
   for (int m = 0; m < NH; ++m) P[0][m] = kScalarT ? node8_w(nc, m) : nc.w[m];
   const char* xl = reinterpret_cast<const char*>(xs + lane);
@@ -1363,7 +1427,6 @@ __device__ __forceinline__ void adjoint_rows_shared(
     // before any is used.  An empty row (d = 0) is walked too: its slots are
     // inert, so its leaf's gradient comes out exactly 0.
     const ShortRowRegs<T> r = load_short_row(rows, row0, p);
-    const int leaf = ldu(&hdr[p].leaf);
     const int sidx = side == nullptr ? -1 : ldu(&hdr[p].tree);
     const bool merged = sidx >= 0;
     const int d = r.d;
@@ -1376,9 +1439,9 @@ __device__ __forceinline__ void adjoint_rows_shared(
     const auto& u = r.u;
     const auto& bl = r.bl;
     const auto& cbl = r.cbl;
-    float x[8];
+    float x[ND + 1];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = *reinterpret_cast<const float*>(xl + xo[k]);
+    for (int k = 0; k <= ND; ++k) x[k] = *reinterpret_cast<const float*>(xl + xo[k]);
     auto follows = [&](float xv, float lv, float uv, bool miss) -> bool {
       bool lower;
       if (NANS) lower = miss ? !(xv < lv) : (xv >= lv);
@@ -1389,10 +1452,8 @@ __device__ __forceinline__ void adjoint_rows_shared(
     T bA = bl[0], cbA = cbl[0], bB = T(0), cbB = T(0);
     float loB = 0.f, hiB = 0.f;
     bool mokB = false;
-    int leafB = 0;
     if (merged) {
       const SidePath* sp = side + sidx;
-      leafB = ldu(&sp->leaf_b);
       loB = ldu(&sp->lo_b);
       hiB = ldu(&sp->hi_b);
       mokB = ldu(&sp->mok_b) != 0;
@@ -1405,12 +1466,11 @@ __device__ __forceinline__ void adjoint_rows_shared(
     const T cB = follows(x[0], loB, hiB, mokB) ? cbB : -bB;
     const T g0 = *reinterpret_cast<const T*>(gl + go[0]);
 #pragma unroll
-    for (int k = 1; k < 8; ++k) {
+    for (int k = 1; k <= ND; ++k) {
       if (k > s) {
         // b in a VGPR once, for the select's -b and the factor FMAs
         const T bv = kScalarT ? to_vgpr(bl[k]) : bl[k];
         const T c = follows(x[k], l[k], u[k], ((r.mok >> k) & 1) != 0) ? cbl[k] : -bv;
-        cf[k] = c;
         gc[k] = *reinterpret_cast<const T*>(gl + go[k]) * c;
         if (kScalarT) {
 #pragma unroll
@@ -1420,17 +1480,17 @@ __device__ __forceinline__ void adjoint_rows_shared(
           for (int m = 0; m < NH; ++m) G[k][m] = fmaT(tv[m], c, bl[k]);
         }
         // the prefix through this slot (every later slot is evaluated too)
-        if (k <= 6) {
+        if (k <= kLastP) {
 #pragma unroll
           for (int m = 0; m < NH; ++m) P[k][m] = P[k - 1][m] * G[k][m];
         }
       }
     }
     // sum_m w_m Q_0(m)
-    T q0 = P[6][0] * G[7][0];
+    T q0 = P[kLastP][0] * (ND < 7 ? one : G[ND][0]);
 #pragma unroll
-    for (int m = 1; m < NH; ++m) q0 = fmaT(P[6][m], G[7][m], q0);
-    // R(m), slots 7..1
+    for (int m = 1; m < NH; ++m) q0 = fmaT(P[kLastP][m], ND < 7 ? one : G[ND][m], q0);
+    // R(m), slots ND..1
     T S[NH], R[NH];
 #pragma unroll
     for (int m = 0; m < NH; ++m) {
@@ -1438,7 +1498,7 @@ __device__ __forceinline__ void adjoint_rows_shared(
       R[m] = T(0);
     }
 #pragma unroll
-    for (int q = 6; q >= 0; --q) {
+    for (int q = ND - 1; q >= 0; --q) {
       const int j = q + 1;
       if (j < d) {
 #pragma unroll
@@ -1456,73 +1516,222 @@ __device__ __forceinline__ void adjoint_rows_shared(
       stR = fmaT(kScalarT ? node8_t(nc, m) : tv[m], R[m], stR);
     }
     const T gq = g0 * q0;
-    double gA = (double)fmaT(bA, sR, cA * (stR + gq));
-    gA = wave_sum_last(gA);
-    if (lane == 63) leaf_add(grad_leaf, leaf, gA, det);
-    if (merged) {
-      double gB = (double)fmaT(bB, sR, cB * (stR + gq));
-      gB = wave_sum_last(gB);
-      if (lane == 63) leaf_add(grad_leaf, leafB, gB, det);
-    }
+    const double gA = (double)fmaT(bA, sR, cA * (stR + gq));
+    const double gB = merged ? (double)fmaT(bB, sR, cB * (stR + gq)) : 0.0;
+    if constexpr (sizeof(T) == 4) sums.add(gA, gB, p - p_first, p, p + 1 == p_last);
+    else sums.add_row(gA, gB, p);
   }
 }
 
-// Adjoint to the leaf values (same tiling as values_kernel): the tile holds
-// the samples' rows and their upstream gradient rows g[s, :].
-template <typename T, int DMAX, int NH, bool STORE_G, int NN>
-__global__ void __launch_bounds__(512)
+// Adjoint over rows of at most TOP + 4 <= 8 features at the 8-node rule, in
+// FP64.  With r_j = c_j / F_j as in values_rows_grouped, P = w prod_{k >= 1} F_k and
+//   R(m) = P(m) W(m),  W(m) = sum_{j >= 1} g_j r_j(m),
+// a leaf A of the row has gradient
+//   b_A sum_m R(m) + c_A (sum_m t_m R(m) + g_0 sum_m P(m)),
+// and B likewise.  W is linear in the slots' g_j: the followed slots' against
+// their coefficients e_j(m), and the sum of the others' against r(m).  The
+// root side's part of W is formed once for a run of rows that share it.  The
+// row loop is pipelined as in values_rows_grouped.
+// (FP32 keeps adjoint_rows_shared: its gradient is returned in FP64 and holds
+// the rounding of every row's sums, which this order would change.)
+template <typename T, int TOP, bool NANS>
+__device__ __forceinline__ void adjoint_rows_grouped(
+    const WalkRow<T>* __restrict__ rows, const T* __restrict__ coef, int row0,
+    const float* xs, const T* gs, LeafSums sums, int pb, int pe, int wave, int nw, int lane,
+    const NodeConsts<T>& nc) {
+  static_assert(sizeof(T) == 8, "offsets of the gradient tile are twice the sample tile's");
+  constexpr int N = 8, ND = TOP + 3;
+  const int run = (pe - pb + nw - 1) / nw;
+  const int p_first = pb + wave * run;
+  const int p_last = min(pe, p_first + run);
+  if (p_first >= p_last) return;
+  T P[ND + 1][N];
+  uint64_t in_k[ND + 1];
+  T Wt[N];          // W over the followed slots 1..TOP
+  T gu_top = T(0);  // sum of g over slots 1..TOP not followed
+#pragma unroll
+  for (int k = 0; k <= ND; ++k) in_k[k] = 0;
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    P[0][m] = nc.w[m];
+    Wt[m] = T(0);
+  }
+  const char* xl = reinterpret_cast<const char*>(xs + lane);
+  const char* gl = reinterpret_cast<const char*>(gs + lane);
+  struct XG {
+    float x;
+    T g;
+  };
+  auto xg_at = [&](int off) __attribute__((always_inline)) {
+    return XG{*reinterpret_cast<const float*>(xl + off),
+              *reinterpret_cast<const T*>(gl + 2 * off)};
+  };
+  auto inside = [&](float x, float l, float u, bool miss) __attribute__((always_inline)) {
+    uint64_t lower = __builtin_amdgcn_ballot_w64(x >= l);
+    if (NANS) lower |= miss ? __builtin_amdgcn_ballot_w64(x != x) : 0;
+    return lower & __builtin_amdgcn_ballot_w64(!(x >= u));
+  };
+  auto extend = [&](int k, T b, T cb) __attribute__((always_inline)) {
+    const T bv = to_vgpr(b);
+    const T c = pick(in_k[k], -bv, to_vgpr(cb));
+#pragma unroll
+    for (int m = 0; m < N; ++m) P[k][m] = P[k - 1][m] * fmaT(nc.t[m], c, bv);
+  };
+  struct Rec {
+    int32_t pack, xo0;
+    float lo0, hi0, split;
+    int32_t xo[3];
+    float lo[3], hi[3];
+    T b[3], cb[3], b0[4];
+  };
+  auto load = [&](int p) __attribute__((always_inline)) {
+    const WalkRow<T>* w = rows + (p - row0);
+    Rec r;
+    const row_v16 a = ldu(reinterpret_cast<const row_v16*>(w));  // 14 words are the row's
+    r.pack = a[0];
+    r.xo0 = a[1];
+    r.lo0 = __int_as_float(a[2]);
+    r.hi0 = __int_as_float(a[3]);
+    r.split = __int_as_float(a[4]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      r.xo[i] = a[5 + i];
+      r.lo[i] = __int_as_float(a[8 + i]);
+      r.hi[i] = __int_as_float(a[11 + i]);
+      r.b[i] = ldu(&w->bl[i]);
+      r.cb[i] = ldu(&w->cbl[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.b0[i] = ldu(&w->b0[i]);
+    return r;
+  };
+  Rec r = load(p_first);
+  XG x0 = xg_at(r.xo0);
+  XG x[3] = {xg_at(r.xo[0]), xg_at(r.xo[1]), xg_at(r.xo[2])};
+  for (int p = p_first; p < p_last; ++p) {
+    const int d = r.pack & 15;
+    const int s = p == p_first ? 0 : (r.pack >> 4) & 15;
+    const int mok = r.pack >> 8;
+    const int p_next = min(p + 1, p_last - 1);
+    const T* e = coef + (int64_t)(p - row0) * kShortCoef;
+    uint64_t in0 = inside(x0.x, r.lo0, r.hi0, NANS && (mok & 0x101) != 0);
+    uint64_t in0a = __builtin_amdgcn_ballot_w64(!(x0.x >= r.split));
+    if (NANS) in0a &= (mok & 0x100) != 0 ? __builtin_amdgcn_ballot_w64(x0.x == x0.x) : ~0ull;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      in_k[TOP + 1 + i] =
+          inside(x[i].x, r.lo[i], r.hi[i], ((mok >> (TOP + 1 + i)) & 1) != 0);
+    if constexpr (TOP > 0) {
+      if (s < TOP) {
+        const WalkRow<T>* w = rows + (p - row0);
+        XG xt[TOP];
+#pragma unroll
+        for (int k = 0; k < TOP; ++k) xt[k] = xg_at(ldu(&w->xot[k]));
+        gu_top = T(0);
+#pragma unroll
+        for (int m = 0; m < N; ++m) Wt[m] = T(0);
+#pragma unroll
+        for (int k = 0; k < TOP; ++k) {
+          in_k[k + 1] = inside(xt[k].x, ldu(&w->lot[k]), ldu(&w->hit[k]),
+                               ((mok >> (k + 1)) & 1) != 0);
+          extend(k + 1, ldu(&w->bt[k]), ldu(&w->cbt[k]));
+          // inert slots past a short row's end have no gradient
+          const T g = k + 1 < d ? xt[k].g : T(0);
+          const T og = pick(in_k[k + 1], T(0), g);
+          gu_top += g - og;
+#pragma unroll
+          for (int m = 0; m < N; ++m) Wt[m] = fmaT(ldu(e + 8 * k + m), og, Wt[m]);
+        }
+      }
+    }
+    // g of the low slots, split by their follow bits
+    T og[3], gu = gu_top;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const T g = TOP + 1 + i < d ? x[i].g : T(0);
+      og[i] = pick(in_k[TOP + 1 + i], T(0), g);
+      gu += g - og[i];
+    }
+    const T g0 = x0.g;
+    __builtin_amdgcn_sched_barrier(0);
+    const Rec rn = load(p_next);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (TOP + 1 + i > s) extend(TOP + 1 + i, r.b[i], r.cb[i]);
+    T W[N];
+#pragma unroll
+    for (int m = 0; m < N; ++m) W[m] = fmaT(nc.r[m], gu, Wt[m]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int m = 0; m < N; ++m) W[m] = fmaT(ldu(e + 8 * (TOP + i) + m), og[i], W[m]);
+    T q0 = P[ND][0], sR = P[ND][0] * W[0], stR = nc.t[0] * sR;
+#pragma unroll
+    for (int m = 1; m < N; ++m) {
+      const T R = P[ND][m] * W[m];
+      q0 += P[ND][m];
+      sR += R;
+      stR = fmaT(nc.t[m], R, stR);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    x0 = xg_at(rn.xo0);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) x[i] = xg_at(rn.xo[i]);
+    __builtin_amdgcn_sched_barrier(0);
+    const T bA = to_vgpr(r.b0[0]), bB = to_vgpr(r.b0[2]);
+    // not inside: neither leaf is followed
+    const T cA = pick(in0 & in0a, -bA, to_vgpr(r.b0[1]));
+    const T cB = pick(in0 & ~in0a, -bB, to_vgpr(r.b0[3]));
+    const T u = fmaT(g0, q0, stR);
+    sums.add(fmaT(bA, sR, cA * u), fmaT(bB, sR, cB * u), p - p_first, p, p + 1 == p_last);
+    r = rn;
+  }
+}
+
+// Adjoint to the leaf values: the tile holds the samples' rows and their
+// upstream gradient rows g[s, :].  A workgroup takes one chunk of rows and
+// every n_groups-th sample block, and keeps the chunk's leaf sums in LDS over
+// all of them, so a leaf costs one global atomic per workgroup instead of one
+// per sample block (whose adds to the same leaves ran one after another in
+// L2).  With the inert slots left out (119 VGPRs instead of 136 at depth 6,
+// four waves per SIMD), four rows' sums folded together over the wave and
+// four wavefronts' worth of registers per SIMD in use, 200 trees of depth 6,
+// 50 features, 20k rows, FP32 take 0.57 ms; 1.59 before.  part_rows = 0: no room for the sums next to the tiles, every row adds
+// to memory.  TOP: the bucket's (capacity 8); FP64 at 8 nodes takes the grouped
+// walk with it, the others adjoint_rows_shared with ND = TOP + 3.
+// Three waves per SIMD (168 VGPRs) where the instance is within a few
+// registers of them.
+template <typename T, int DMAX, int NH, bool STORE_G, int NN, int TOP>
+__global__ void
+__launch_bounds__(512, (DMAX == 16 && sizeof(T) == 4) || (DMAX == 8 && NN == 4) ? 3 : 2)
 adjoint_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
                const float* __restrict__ lo, const float* __restrict__ hi,
                const T* __restrict__ bb, const T* __restrict__ cbb,
-               const SidePath* __restrict__ side, const int32_t* __restrict__ share,
-               const float* __restrict__ X, const T* __restrict__ G, int64_t M, int64_t ldx,
-               int32_t F, int32_t tile_f, int32_t path_begin, int32_t path_end, int32_t chunk,
-               int32_t nsb, const Segment* __restrict__ segs,
-               const int32_t* __restrict__ seg_feat, int32_t ng, int32_t grp,
+               const SidePath* __restrict__ side, const float* __restrict__ X,
+               const T* __restrict__ G, int64_t M, int64_t ldx, int32_t F, int32_t tile_f,
+               int32_t path_begin, int32_t path_end, int32_t chunk, int32_t part_rows,
+               int32_t nsb, int32_t n_groups, const Segment* __restrict__ segs,
+               const int32_t* __restrict__ seg_feat, int32_t ng, BucketIndex bx,
                double* __restrict__ grad_leaf, int64_t part_stride,
-               const ShortRow<T>* __restrict__ srows, NodeConsts<T> nc) {
+               const ShortRow<T>* __restrict__ srows, const WalkRow<T>* __restrict__ wrows,
+               const T* __restrict__ wcoef, NodeConsts<T> nc) {
   extern __shared__ __align__(16) unsigned char smem[];
   float* xs = reinterpret_cast<float*>(smem);
-  size_t xs_bytes = ((size_t)tile_f * kTileStride * sizeof(float) + 15) & ~(size_t)15;
+  const size_t tile_rows = (size_t)tile_f * kTileStride;
+  const size_t xs_bytes = (tile_rows * sizeof(float) + 15) & ~(size_t)15;
   T* gs = reinterpret_cast<T*>(smem + xs_bytes);
+  double* part = part_rows == 0 ? nullptr
+      : reinterpret_cast<double*>(
+            smem + ((xs_bytes + tile_rows * sizeof(T) + 15) & ~(size_t)15));
 
   // work items dealt to the XCDs in contiguous eighths (xcd_item)
   const int item = xcd_item((int)blockIdx.x, (int)gridDim.x);
-  const int sb = item % nsb;
-  const int ch = item / nsb;
-  const int64_t s0 = (int64_t)sb * kSamplesPerBlock;
-  const ItemRows ir = item_rows(segs, seg_feat, ch, path_begin, path_end, chunk, F);
-  const int nf = ir.nf;
-
-  // stage the sample rows and gradient rows transposed (padding rows get a
-  // zero gradient, so they add nothing); note any NaN.  With segments (wide
-  // feature spaces) X is feature-major [F][ldx] and G [ng][F][M].
-  const bool fmajor = segs != nullptr;
-  const int tile = kSamplesPerBlock * nf;
-  int nan_seen = 0;
-  if (fmajor) {
-    for (int i = threadIdx.x; i < tile; i += blockDim.x) {
-      const int k = i >> 6, r = i & 63;
-      const int f = ir.fmap[k];
-      const int64_t s = s0 + r;
-      const float v = (s < M) ? X[(int64_t)f * ldx + s] : 0.0f;
-      nan_seen |= (v != v);
-      xs[k * kTileStride + r] = v;
-      gs[k * kTileStride + r] = (s < M) ? G[((int64_t)grp * F + f) * M + s] : T(0);  // G[grp, f, s]
-    }
-  } else {
-    for (int i = threadIdx.x; i < tile; i += blockDim.x) {
-      const int r = i / nf;
-      const int k = i - r * nf;
-      const int64_t s = s0 + r;
-      const float v = (s < M) ? X[s * ldx + k] : 0.0f;
-      nan_seen |= (v != v);
-      xs[k * kTileStride + r] = v;
-      gs[k * kTileStride + r] = (s < M) ? G[(s * ng + grp) * F + k] : T(0);  // G[s, grp, f]
-    }
-  }
-  const bool any_nan = __syncthreads_or(nan_seen) != 0;
-
+  const int ch = item / n_groups;
+  const int sb_first = item % n_groups;
+  const ItemRows ir = item_rows(segs, seg_feat, ch, path_begin, path_end, chunk, F, bx);
+  const int n_part = part_rows == 0 ? 0 : 2 * (ir.p1 - ir.p0);
+  for (int i = threadIdx.x; i < n_part; i += blockDim.x) part[i] = 0.0;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = __builtin_amdgcn_readfirstlane(blockDim.x >> 6);
@@ -1531,24 +1740,73 @@ adjoint_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat
   T tv[NN];
 #pragma unroll
   for (int m = 0; m < NN; ++m) tv[m] = to_vgpr(nc.t[m]);
-  // deterministic: this sample block's own row of partial sums
+  // deterministic (one sample block per workgroup): that block's own row of
+  // partial sums
   const bool det = part_stride > 0;
-  double* gl = det ? grad_leaf + (int64_t)sb * part_stride : grad_leaf;
-  constexpr bool kShared = DMAX == 8 && NH == NN && (STORE_G || NN == 4);
-  if (kShared && any_nan)
-    adjoint_rows_shared<T, NH, true>(srows, path_begin, hdr, side, xs, gs, gl, pb, pe, wave, nw,
-                                     lane, tv, nc, det);
-  else if (kShared)
-    adjoint_rows_shared<T, NH, false>(srows, path_begin, hdr, side, xs, gs, gl, pb, pe, wave, nw,
-                                      lane, tv, nc, det);
-  else if (any_nan)
-    values_paths<T, DMAX, NH, STORE_G, true, true, NN>(hdr, feat, lo, hi, bb, cbb, side, nullptr,
-                                                       xs, nullptr, gs, gl, pb, pe, wave, nw,
-                                                       lane, tv, nc, det);
-  else
-    values_paths<T, DMAX, NH, STORE_G, false, true, NN>(hdr, feat, lo, hi, bb, cbb, side, nullptr,
-                                                        xs, nullptr, gs, gl, pb, pe, wave, nw,
-                                                        lane, tv, nc, det);
+  double* gl = det ? grad_leaf + (int64_t)sb_first * part_stride : grad_leaf;
+  const LeafSums sums{part, gl, hdr, side, pb, lane, det};
+  constexpr bool kGrouped = DMAX == 8 && NN == 8 && sizeof(T) == 8;
+  const bool fmajor = segs != nullptr;
+  for (int sb = sb_first; sb < nsb; sb += n_groups) {
+    // stage the sample rows and gradient rows transposed (padding rows get a
+    // zero gradient, so they add nothing); note any NaN.  With segments (wide
+    // feature spaces) X is feature-major [F][ldx] and G [ng][F][M].
+    const int64_t s0 = (int64_t)sb * kSamplesPerBlock;
+    int nan_seen = 0;
+    // not loop invariants: the walk needs the registers that hoisted index
+    // arithmetic would hold
+    int tid = threadIdx.x, nf = ir.nf;
+    asm volatile("" : "+v"(tid), "+s"(nf));
+    const int tile = kSamplesPerBlock * nf;
+    if (fmajor) {
+      for (int i = tid; i < tile; i += blockDim.x) {
+        const int k = i >> 6, r = i & 63;
+        const int f = ir.fmap[k];
+        const int64_t s = s0 + r;
+        const float v = (s < M) ? X[(int64_t)f * ldx + s] : 0.0f;
+        nan_seen |= (v != v);
+        xs[k * kTileStride + r] = v;
+        gs[k * kTileStride + r] = (s < M) ? G[((int64_t)ir.grp * F + f) * M + s] : T(0);  // G[grp, f, s]
+      }
+    } else {
+      for (int i = tid; i < tile; i += blockDim.x) {
+        const int r = i / nf;
+        const int k = i - r * nf;
+        const int64_t s = s0 + r;
+        const float v = (s < M) ? X[s * ldx + k] : 0.0f;
+        nan_seen |= (v != v);
+        xs[k * kTileStride + r] = v;
+        gs[k * kTileStride + r] = (s < M) ? G[(s * ng + ir.grp) * F + k] : T(0);  // G[s, grp, f]
+      }
+    }
+    const bool any_nan = __syncthreads_or(nan_seen) != 0;
+    if constexpr (kGrouped) {
+      if (any_nan)
+        adjoint_rows_grouped<T, TOP, true>(wrows, wcoef, path_begin, xs, gs, sums, pb, pe, wave,
+                                           nw, lane, nc);
+      else
+        adjoint_rows_grouped<T, TOP, false>(wrows, wcoef, path_begin, xs, gs, sums, pb, pe, wave,
+                                            nw, lane, nc);
+    } else if constexpr (DMAX == 8) {
+      if (any_nan)
+        adjoint_rows_shared<T, NH, TOP + 3, true>(srows, path_begin, hdr, side, xs, gs, sums, pb,
+                                                  pe, wave, nw, lane, tv, nc);
+      else
+        adjoint_rows_shared<T, NH, TOP + 3, false>(srows, path_begin, hdr, side, xs, gs, sums, pb,
+                                                   pe, wave, nw, lane, tv, nc);
+    } else if (any_nan) {
+      adjoint_paths<T, DMAX, NH, STORE_G, true, NN>(hdr, feat, lo, hi, bb, cbb, side, xs, gs, sums,
+                                                    pb, pe, wave, nw, lane, tv, nc);
+    } else {
+      adjoint_paths<T, DMAX, NH, STORE_G, false, NN>(hdr, feat, lo, hi, bb, cbb, side, xs, gs,
+                                                     sums, pb, pe, wave, nw, lane, tv, nc);
+    }
+    __syncthreads();
+  }
+  for (int i = threadIdx.x; i < n_part; i += blockDim.x) {
+    const int leaf = leaf_of(hdr, side, pb + (i >> 1), i & 1);
+    if (leaf >= 0) leaf_add(gl, leaf, part[i], det);
+  }
 }
 
 namespace {
@@ -1556,14 +1814,31 @@ namespace {
 // Paths per work item: about 32 rounds of the ~512 resident workgroups
 // (small tail), chunks of at least 256 paths so the per-item tile load and
 // flush stay small next to the path work.
-int values_chunk(int n_paths, int nsb, int items) {
+// A launch that would leave the chip idle (under 4 workgroups per CU) takes
+// chunks of down to 32 rows instead: its time is a wavefront's walk through
+// its rows one after another (95 ragged trees of depth up to 30, 37 rows: 283
+// -> 70 us a call).
+int values_chunk(int n_paths, int nsb, int items, bool fill = true) {
   const int64_t want_items = items > 0 ? items : 16384;
   int64_t n_chunks = (want_items + nsb - 1) / nsb;
   n_chunks = std::max<int64_t>(1, std::min<int64_t>(n_chunks, (n_paths + 255) / 256));
+  constexpr int64_t kFill = 1024;
+  if (fill && n_chunks > 1 && n_chunks * nsb < kFill)
+    n_chunks = std::max(n_chunks,
+                        std::min<int64_t>((kFill + nsb - 1) / nsb, (n_paths + 31) / 32));
   return (int)((n_paths + n_chunks - 1) / n_chunks);
 }
 
 }  // namespace
+
+std::vector<BucketSpan> bucket_spans(const std::vector<Bucket>& bks, bool one_each) {
+  std::vector<BucketSpan> out;
+  for (size_t i = 0; i < bks.size(); ++i) {
+    if (!one_each && !out.empty() && out.back().dmax() == bks[i].dmax) ++out.back().n;
+    else out.push_back(BucketSpan{&bks[i], 1, (int)i});
+  }
+  return out;
+}
 
 bool values_direct(const std::vector<Bucket>& bks, int64_t M, const ValuesShape& shape) {
   if (bks.size() != 1 || M <= 0) return false;
@@ -1578,7 +1853,8 @@ namespace {
 // The short-row records of a capacity-8 bucket from its first row (null for
 // other buckets).
 template <typename T>
-const ShortRow<T>* short_rows_of(const PathArrays& a, const Bucket& bk) {
+const ShortRow<T>* short_rows_of(const PathArrays& a, const BucketSpan& sp) {
+  const Bucket& bk = sp.list[0];
   if (bk.dmax != 8 || bk.srow_begin < 0) return nullptr;
   const ShortRow<T>* r;
   if constexpr (std::is_same<T, float>::value) r = a.srow32;
@@ -1598,19 +1874,35 @@ struct RowSplit {
   int tile_f;            // features the LDS tile is laid out for
 };
 
-RowSplit row_split(const HostTable& h, const PathArrays& a, const Bucket& bk, int nsb,
-                   const ValuesShape& shape) {
+// The chunks of `chunk` rows that a span's buckets are cut into.
+int n_chunks_of(const BucketSpan& sp, int chunk) {
+  int n = 0;
+  for (int i = 0; i < sp.n; ++i)
+    n += (sp.list[i].path_end - sp.list[i].path_begin + chunk - 1) / chunk;
+  return n;
+}
+
+BucketIndex bucket_index(const PathArrays& a, const BucketSpan& sp) {
+  if (sp.n > 1 && (a.bkt_begin == nullptr || a.bkt_group == nullptr))
+    fail(QTS_E_INVALID_ARG, "internal: no bucket index");
+  return sp.n > 1 ? BucketIndex{a.bkt_begin + sp.index, a.bkt_group + sp.index, sp.n, 0}
+                  : BucketIndex{nullptr, nullptr, 1, sp.list[0].group};
+}
+
+RowSplit row_split(const HostTable& h, const PathArrays& a, const BucketSpan& sp, int nsb,
+                   const ValuesShape& shape, bool fill = true) {
   RowSplit r{a.feat, nullptr, 0, 0, h.F};
   if (a.compact == nullptr) {
-    const int n_paths = bk.path_end - bk.path_begin;
-    r.chunk = values_chunk(n_paths, nsb, shape.items);
-    r.n_chunks = (n_paths + r.chunk - 1) / r.chunk;
+    r.chunk = values_chunk(sp.path_end() - sp.path_begin(), nsb, shape.items, fill);
+    r.n_chunks = n_chunks_of(sp, r.chunk);
     return r;
   }
   const CompactTable& c = *a.compact;
   for (size_t i = 0; i + 1 < c.bucket_seg.size(); ++i) {
-    const int s0 = c.bucket_seg[i], s1 = c.bucket_seg[i + 1];
-    if (s1 > s0 && c.segs[(size_t)s0].row_begin == bk.path_begin) {
+    const int s0 = c.bucket_seg[i];
+    int s1 = c.bucket_seg[i + 1];
+    if (s1 > s0 && c.segs[(size_t)s0].row_begin == sp.path_begin()) {
+      while (s1 < (int)c.segs.size() && c.segs[(size_t)s1].row_begin < sp.path_end()) ++s1;
       r.feat = a.lfeat;
       r.segs = a.segs + s0;
       r.n_chunks = s1 - s0;
@@ -1628,7 +1920,8 @@ struct WalkPtrs {
   const T* coef = nullptr;
 };
 template <typename T>
-WalkPtrs<T> walk_of(const PathArrays& a, const Bucket& bk) {
+WalkPtrs<T> walk_of(const PathArrays& a, const BucketSpan& sp) {
+  const Bucket& bk = sp.list[0];
   if (bk.dmax != 8 || bk.srow_begin < 0) return {};
   WalkPtrs<T> w;
   if constexpr (std::is_same<T, float>::value) w = {a.walk.row32, a.walk.coef32};
@@ -1638,109 +1931,161 @@ WalkPtrs<T> walk_of(const PathArrays& a, const Bucket& bk) {
   return {w.rows + bk.srow_begin, w.coef + (int64_t)bk.srow_begin * kShortCoef};
 }
 
-template <typename T, int DMAX, int NH, bool STORE_G, int NN, int TOP = -1>
-void launch_one(const HostTable& h, const DeviceTable& d, const PathArrays& a, const Bucket& bk,
-                const float* X, int64_t M, int64_t ldx, const void* slot0, double* acc,
+template <typename T, int DMAX, int NH, bool STORE_G, int NN, int WALK = kPerRow>
+void launch_one(const HostTable& h, const DeviceTable& d, const PathArrays& a,
+                const BucketSpan& sp, const float* X, int64_t M, int64_t ldx, const void* slot0, double* acc,
                 void* direct, const ValuesShape& shape, hipStream_t s, bool det) {
   const int F = h.F;
   const int nsb = (int)((M + kSamplesPerBlock - 1) / kSamplesPerBlock);
-  const RowSplit rs = row_split(h, a, bk, nsb, shape);
+  // (deterministic: a chunk is a launch)
+  const RowSplit rs = row_split(h, a, sp, nsb, shape, !det);
+  const BucketIndex bx = bucket_index(a, sp);
+  const int32_t row0 = sp.path_begin(), row1 = sp.path_end();
   const int64_t grid = (int64_t)nsb * rs.n_chunks;
   if (grid > 0x7fffffff) fail(QTS_E_UNSUPPORTED, "grid too large");
   const size_t lds = values_lds_bytes(rs.tile_f);
   // deterministic: one wave per workgroup (no LDS atomics between waves), and
   // one launch per chunk, so each launch has one workgroup per (sample, feature)
-  const int threads = det ? 64 : 64 * shape.waves_per_block;
+  const void* fn = (const void*)values_kernel<T, DMAX, NH, STORE_G, NN, WALK>;
+  const int threads =
+      det ? 64 : 64 * (shape.tuned ? shape.waves_per_block : resident_waves(fn, lds));
   const T* b = std::is_same<T, float>::value ? (const T*)a.b32 : (const T*)a.b64;
   const T* cb = std::is_same<T, float>::value ? (const T*)a.cb32 : (const T*)a.cb64;
   NodeConsts<T> nc;
   if constexpr (std::is_same<T, float>::value) nc = NN == 8 ? d.n32 : d.n32_4;
   else nc = NN == 8 ? d.n64 : d.n64_4;
-  if (lds > raise_lds_limit((const void*)values_kernel<T, DMAX, NH, STORE_G, NN, TOP>))
+  if (lds > raise_lds_limit(fn))
     fail(QTS_E_UNSUPPORTED, "internal: the sample tile does not fit in LDS");
-  const ShortRow<T>* srows = short_rows_of<T>(a, bk);
-  const WalkPtrs<T> walk = walk_of<T>(a, bk);
+  const ShortRow<T>* srows = short_rows_of<T>(a, sp);
+  const WalkPtrs<T> walk = walk_of<T>(a, sp);
   if (!det) {
-    hipLaunchKernelGGL((values_kernel<T, DMAX, NH, STORE_G, NN, TOP>), dim3((unsigned)grid),
+    hipLaunchKernelGGL((values_kernel<T, DMAX, NH, STORE_G, NN, WALK>), dim3((unsigned)grid),
                        dim3(threads), lds, s, a.hdr, rs.feat, a.lo, a.hi, b, cb,
-                       (const Slot0<T>*)slot0, a.share, X, M, ldx, F, rs.tile_f, bk.path_begin,
-                       bk.path_end, rs.chunk, nsb, rs.segs, a.seg_feat, h.n_groups, bk.group,
-                       acc, rs.segs ? nullptr : direct,
+                       (const Slot0<T>*)slot0, a.share, X, M, ldx, F, rs.tile_f, row0, row1,
+                       rs.chunk, nsb, rs.segs, a.seg_feat, h.n_groups, bx, acc, rs.segs ? nullptr : direct,
                        (int32_t)(std::is_same<T, double>::value ? 1 : 0), 0, srows, walk.rows,
                        walk.coef, nc);
     check_hip(hipGetLastError(), "values_kernel launch");
     return;
   }
   for (int c = 0; c < rs.n_chunks; ++c) {
-    const int p0 = rs.segs ? bk.path_begin : bk.path_begin + c * rs.chunk;
-    const int p1 = rs.segs ? bk.path_end : std::min(bk.path_end, p0 + rs.chunk);
-    hipLaunchKernelGGL((values_kernel<T, DMAX, NH, STORE_G, NN, TOP>), dim3((unsigned)nsb),
+    const int p0 = rs.segs ? row0 : row0 + c * rs.chunk;
+    const int p1 = rs.segs ? row1 : std::min(row1, p0 + rs.chunk);
+    hipLaunchKernelGGL((values_kernel<T, DMAX, NH, STORE_G, NN, WALK>), dim3((unsigned)nsb),
                        dim3(threads), lds, s, a.hdr, rs.feat, a.lo, a.hi, b, cb,
                        (const Slot0<T>*)slot0, a.share, X, M, ldx, F, rs.tile_f, p0, p1,
                        rs.chunk, nsb, rs.segs ? rs.segs + c : nullptr, a.seg_feat, h.n_groups,
-                       bk.group, acc, nullptr, (int32_t)(std::is_same<T, double>::value ? 1 : 0),
-                       1, srows ? srows + (p0 - bk.path_begin) : nullptr,
-                       walk.rows ? walk.rows + (p0 - bk.path_begin) : nullptr,
-                       walk.coef ? walk.coef + (int64_t)(p0 - bk.path_begin) * kShortCoef : nullptr,
+                       bx, acc, nullptr, (int32_t)(std::is_same<T, double>::value ? 1 : 0),
+                       1, srows ? srows + (p0 - row0) : nullptr,
+                       walk.rows ? walk.rows + (p0 - row0) : nullptr,
+                       walk.coef ? walk.coef + (int64_t)(p0 - row0) * kShortCoef : nullptr,
                        nc);
     check_hip(hipGetLastError(), "values_kernel launch");
   }
 }
 
-template <typename T, int DMAX, int NH, bool STORE_G, int NN>
+// A workgroup's chunk is at most kAdjRows rows (their leaf sums in LDS, next to
+// the tiles), and the sample blocks are dealt to about items / kAdjItems
+// workgroups in all, so that a chunk's sums go to memory once for several
+// blocks (200 trees of depth 6, 20k rows, values and adjoint: 1.17 ms with
+// 2, 1.19 with 8, 1.20 with 32).
+constexpr int kAdjRows = 512;
+constexpr int kAdjItems = 2;
+
+template <typename T, int DMAX, int NH, bool STORE_G, int NN, int TOP = -1>
 void launch_adj_one(const HostTable& h, const DeviceTable& d, const PathArrays& a,
-                    const Bucket& bk, const float* X, const void* G, int64_t M, int64_t ldx,
+                    const BucketSpan& sp, const float* X, const void* G, int64_t M, int64_t ldx,
                     double* grad_leaf, const ValuesShape& shape, hipStream_t s,
                     int64_t part_stride) {
   const int F = h.F;
   const int nsb = (int)((M + kSamplesPerBlock - 1) / kSamplesPerBlock);
-  const RowSplit rs = row_split(h, a, bk, nsb, shape);
-  const int64_t grid = (int64_t)nsb * rs.n_chunks;
+  RowSplit rs = row_split(h, a, sp, nsb, shape);
+  const void* fn = (const void*)adjoint_kernel<T, DMAX, NH, STORE_G, NN, TOP>;
+  const size_t limit = raise_lds_limit(fn);
+  const size_t tile = (size_t)rs.tile_f * kTileStride;
+  const size_t tiles = (((tile * sizeof(float) + 15) & ~(size_t)15) + tile * sizeof(T) + 15) &
+                       ~(size_t)15;
+  if (tiles > limit + 15) fail(QTS_E_UNSUPPORTED, "internal: the sample tile does not fit in LDS");
+  // rows whose leaf sums fit next to the tiles (a chunk of under 128 would
+  // load the tiles too often: then the rows add to memory)
+  const int fit = tiles >= limit ? 0 : (int)((limit - tiles) / (2 * sizeof(double)));
+  int part_rows = 0;
+  if (rs.segs != nullptr) {
+    if (fit >= kSegMaxRows) part_rows = kSegMaxRows;
+  } else if (fit >= 128) {
+    rs.chunk = std::min({rs.chunk, kAdjRows, fit});
+    rs.n_chunks = n_chunks_of(sp, rs.chunk);
+    part_rows = rs.chunk;
+  }
+  const int64_t want = std::max(1, shape.items / kAdjItems);
+  const int n_groups = part_stride > 0 || part_rows == 0
+      ? nsb : (int)std::max<int64_t>(1, std::min<int64_t>(nsb, want / rs.n_chunks));
+  const int64_t grid = (int64_t)n_groups * rs.n_chunks;
   if (grid > 0x7fffffff) fail(QTS_E_UNSUPPORTED, "grid too large");
-  size_t xs = ((size_t)rs.tile_f * kTileStride * sizeof(float) + 15) & ~(size_t)15;
-  const size_t lds = xs + (size_t)rs.tile_f * kTileStride * sizeof(T);
-  const int threads = 64 * shape.waves_per_block;
+  const size_t lds = std::min(limit, tiles + 2 * (size_t)part_rows * sizeof(double));
+  const int threads = 64 * (shape.tuned ? shape.waves_per_block : resident_waves(fn, lds));
   const T* b = std::is_same<T, float>::value ? (const T*)a.b32 : (const T*)a.b64;
   const T* cb = std::is_same<T, float>::value ? (const T*)a.cb32 : (const T*)a.cb64;
   NodeConsts<T> nc;
   if constexpr (std::is_same<T, float>::value) nc = NN == 8 ? d.n32 : d.n32_4;
   else nc = NN == 8 ? d.n64 : d.n64_4;
-  if (lds > raise_lds_limit((const void*)adjoint_kernel<T, DMAX, NH, STORE_G, NN>))
-    fail(QTS_E_UNSUPPORTED, "internal: the sample tile does not fit in LDS");
-  hipLaunchKernelGGL((adjoint_kernel<T, DMAX, NH, STORE_G, NN>), dim3((unsigned)grid),
-                     dim3(threads), lds, s, a.hdr, rs.feat, a.lo, a.hi, b, cb, a.side, a.share,
-                     X, (const T*)G, M, ldx, F, rs.tile_f, bk.path_begin, bk.path_end, rs.chunk,
-                     nsb, rs.segs, a.seg_feat, h.n_groups, bk.group, grad_leaf, part_stride,
-                     short_rows_of<T>(a, bk), nc);
+  const WalkPtrs<T> w = walk_of<T>(a, sp);
+  hipLaunchKernelGGL((adjoint_kernel<T, DMAX, NH, STORE_G, NN, TOP>), dim3((unsigned)grid),
+                     dim3(threads), lds, s, a.hdr, rs.feat, a.lo, a.hi, b, cb, a.side, X,
+                     (const T*)G, M, ldx, F, rs.tile_f, sp.path_begin(), sp.path_end(),
+                     rs.chunk, part_rows, nsb, n_groups, rs.segs, a.seg_feat, h.n_groups,
+                     bucket_index(a, sp), grad_leaf, part_stride, short_rows_of<T>(a, sp), w.rows, w.coef, nc);
   check_hip(hipGetLastError(), "adjoint_kernel launch");
 }
 
 }  // namespace
 
 void launch_adjoint(const HostTable& h, const DeviceTable& d, const PathArrays& a,
-                    const Bucket& bk, bool fp64, const float* X, const void* G, int64_t M,
+                    const BucketSpan& sp, bool fp64, const float* X, const void* G, int64_t M,
                     int64_t ldx, double* grad_leaf, const ValuesShape& shape, int nodes,
                     hipStream_t s, int64_t part_stride) {
-  if (nodes == 4 && bk.dmax == 8) {
-    if (!fp64) launch_adj_one<float, 8, 4, true, 4>(h, d, a, bk, X, G, M, ldx, grad_leaf, shape, s, part_stride);
-    else launch_adj_one<double, 8, 4, false, 4>(h, d, a, bk, X, G, M, ldx, grad_leaf, shape, s, part_stride);
+  auto go = [&](auto t, auto dmax, auto nh, auto store, auto nn, auto top) {
+    launch_adj_one<decltype(t), decltype(dmax)::value, decltype(nh)::value,
+                   decltype(store)::value, decltype(nn)::value, decltype(top)::value>(
+        h, d, a, sp, X, G, M, ldx, grad_leaf, shape, s, part_stride);
+  };
+  using std::false_type;
+  using std::true_type;
+#define QTS_N(n) std::integral_constant<int, n>{}
+  if (sp.dmax() == 8) {
+    auto short_rows = [&](auto top) {
+      if (nodes == 4) {
+        if (!fp64) go(0.f, QTS_N(8), QTS_N(4), true_type{}, QTS_N(4), top);
+        else go(0.0, QTS_N(8), QTS_N(4), false_type{}, QTS_N(4), top);
+      } else if (!fp64) {
+        go(0.f, QTS_N(8), QTS_N(8), true_type{}, QTS_N(8), top);
+      } else {
+        go(0.0, QTS_N(8), QTS_N(8), true_type{}, QTS_N(8), top);
+      }
+    };
+    switch (sp.list[0].top) {
+      case 0: short_rows(QTS_N(0)); break;
+      case 1: short_rows(QTS_N(1)); break;
+      case 2: short_rows(QTS_N(2)); break;
+      case 3: short_rows(QTS_N(3)); break;
+      default: short_rows(QTS_N(4)); break;
+    }
     return;
   }
   if (!fp64) {
-    switch (bk.dmax) {
-      case 8: launch_adj_one<float, 8, 8, true, 8>(h, d, a, bk, X, G, M, ldx, grad_leaf, shape, s, part_stride); break;
-      case 16: launch_adj_one<float, 16, 8, true, 8>(h, d, a, bk, X, G, M, ldx, grad_leaf, shape, s, part_stride); break;
-      case 32: launch_adj_one<float, 32, 8, false, 8>(h, d, a, bk, X, G, M, ldx, grad_leaf, shape, s, part_stride); break;
-      default: launch_adj_one<float, 64, 4, false, 8>(h, d, a, bk, X, G, M, ldx, grad_leaf, shape, s, part_stride); break;
+    switch (sp.dmax()) {
+      case 16: go(0.f, QTS_N(16), QTS_N(8), true_type{}, QTS_N(8), QTS_N(-1)); break;
+      case 32: go(0.f, QTS_N(32), QTS_N(8), false_type{}, QTS_N(8), QTS_N(-1)); break;
+      default: go(0.f, QTS_N(64), QTS_N(4), false_type{}, QTS_N(8), QTS_N(-1)); break;
     }
   } else {
-    switch (bk.dmax) {
-      case 8: launch_adj_one<double, 8, 4, false, 8>(h, d, a, bk, X, G, M, ldx, grad_leaf, shape, s, part_stride); break;
-      case 16: launch_adj_one<double, 16, 4, false, 8>(h, d, a, bk, X, G, M, ldx, grad_leaf, shape, s, part_stride); break;
-      case 32: launch_adj_one<double, 32, 4, false, 8>(h, d, a, bk, X, G, M, ldx, grad_leaf, shape, s, part_stride); break;
-      default: launch_adj_one<double, 64, 1, false, 8>(h, d, a, bk, X, G, M, ldx, grad_leaf, shape, s, part_stride); break;
+    switch (sp.dmax()) {
+      case 16: go(0.0, QTS_N(16), QTS_N(4), false_type{}, QTS_N(8), QTS_N(-1)); break;
+      case 32: go(0.0, QTS_N(32), QTS_N(4), false_type{}, QTS_N(8), QTS_N(-1)); break;
+      default: go(0.0, QTS_N(64), QTS_N(1), false_type{}, QTS_N(8), QTS_N(-1)); break;
     }
   }
+#undef QTS_N
 }
 
 // The grouped walk's rows and node-sum coefficients of one bucket, 64 threads
@@ -1762,6 +2107,15 @@ __device__ __forceinline__ void fill_walk_row(const ShortRow<double>& r, const P
     w.lo0 = r.lo[0] < side[sidx].lo_b ? r.lo[0] : side[sidx].lo_b;
     w.hi0 = side[sidx].hi_b;
     mok_b = side[sidx].mok_b != 0 ? 1 : 0;
+  }
+  w.b0[0] = (T)r.b[0];
+  w.b0[1] = (T)r.cb[0];
+  w.b0[2] = w.b0[3] = T(0);
+  if (r.d > 0 && sidx >= 0) {
+    w.b0[0] = (T)side[sidx].b_a;
+    w.b0[1] = (T)side[sidx].cb_a;
+    w.b0[2] = (T)side[sidx].b_b;
+    w.b0[3] = (T)side[sidx].cb_b;
   }
   w.pack = r.d | r.share << 4 | (r.mok & 0xff) << 8 | mok_b << 16;
   for (int i = 0; i < 3; ++i) {
@@ -1874,42 +2228,60 @@ void launch_slot0(const PathArrays& a, int32_t n_rows, const double* leaf_val, b
 }
 
 void launch_values(const HostTable& h, const DeviceTable& d, const PathArrays& a,
-                   const Bucket& bk, bool fp64, const float* X, int64_t M, int64_t ldx,
+                   const BucketSpan& sp, bool fp64, const float* X, int64_t M, int64_t ldx,
                    const void* slot0, double* acc, void* direct, const ValuesShape& shape,
-                   int nodes, hipStream_t s, bool deterministic) {
-  if (nodes == 4 && bk.dmax == 8) {
-    if (!fp64) launch_one<float, 8, 4, true, 4>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic);
-    else launch_one<double, 8, 4, false, 4>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic);
-    return;
-  }
-  if (bk.dmax == 8) {
-    auto go = [&](auto top) {
-      constexpr int kTop = decltype(top)::value;
-      if (!fp64) launch_one<float, 8, 8, true, 8, kTop>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic);
-      else launch_one<double, 8, 8, true, 8, kTop>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic);
+                   int nodes, hipStream_t s, bool per_row, bool deterministic) {
+  auto go = [&](auto t, auto dmax, auto nh, auto store, auto nn, auto walk) {
+    launch_one<decltype(t), decltype(dmax)::value, decltype(nh)::value, decltype(store)::value,
+               decltype(nn)::value, decltype(walk)::value>(
+        h, d, a, sp, X, M, ldx, slot0, acc, direct, shape, s, deterministic);
+  };
+  using std::false_type;
+  using std::true_type;
+#define QTS_N(n) std::integral_constant<int, n>{}
+  if (sp.dmax() == 8) {
+    auto short_rows = [&](auto top) {
+      const auto walk = QTS_N(kPerRow + 3 + decltype(top)::value);
+      if (nodes == 4) {
+        if (!fp64) go(0.f, QTS_N(8), QTS_N(4), true_type{}, QTS_N(4), walk);
+        else go(0.0, QTS_N(8), QTS_N(4), false_type{}, QTS_N(4), walk);
+      } else if (fp64) {
+        go(0.0, QTS_N(8), QTS_N(8), true_type{}, QTS_N(8), top);
+      } else if (per_row) {
+        go(0.f, QTS_N(8), QTS_N(8), true_type{}, QTS_N(8), walk);
+      } else {
+        go(0.f, QTS_N(8), QTS_N(8), true_type{}, QTS_N(8), top);
+      }
     };
-    switch (bk.top) {
-      case 0: go(std::integral_constant<int, 0>{}); break;
-      case 1: go(std::integral_constant<int, 1>{}); break;
-      case 2: go(std::integral_constant<int, 2>{}); break;
-      case 3: go(std::integral_constant<int, 3>{}); break;
-      default: go(std::integral_constant<int, 4>{}); break;
+    switch (sp.list[0].top) {
+      case 0: short_rows(QTS_N(0)); break;
+      case 1: short_rows(QTS_N(1)); break;
+      case 2: short_rows(QTS_N(2)); break;
+      case 3: short_rows(QTS_N(3)); break;
+      default: short_rows(QTS_N(4)); break;
     }
     return;
   }
-  if (!fp64) {
-    switch (bk.dmax) {
-      case 16: launch_one<float, 16, 8, true, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
-      case 32: launch_one<float, 32, 8, false, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
-      default: launch_one<float, 64, 4, false, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
+  if (!fp64 && !per_row) {
+    switch (sp.dmax()) {
+      case 16: go(0.f, QTS_N(16), QTS_N(8), true_type{}, QTS_N(8), QTS_N(kBatched)); break;
+      case 32: go(0.f, QTS_N(32), QTS_N(8), true_type{}, QTS_N(8), QTS_N(kBatched)); break;
+      default: go(0.f, QTS_N(64), QTS_N(8), true_type{}, QTS_N(8), QTS_N(kBatched)); break;
+    }
+  } else if (!fp64) {
+    switch (sp.dmax()) {
+      case 16: go(0.f, QTS_N(16), QTS_N(8), true_type{}, QTS_N(8), QTS_N(kPerRow)); break;
+      case 32: go(0.f, QTS_N(32), QTS_N(8), false_type{}, QTS_N(8), QTS_N(kPerRow)); break;
+      default: go(0.f, QTS_N(64), QTS_N(4), false_type{}, QTS_N(8), QTS_N(kPerRow)); break;
     }
   } else {
-    switch (bk.dmax) {
-      case 16: launch_one<double, 16, 4, false, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
-      case 32: launch_one<double, 32, 4, false, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
-      default: launch_one<double, 64, 2, false, 8>(h, d, a, bk, X, M, ldx, slot0, acc, direct, shape, s, deterministic); break;
+    switch (sp.dmax()) {
+      case 16: go(0.0, QTS_N(16), QTS_N(4), false_type{}, QTS_N(8), QTS_N(kPerRow)); break;
+      case 32: go(0.0, QTS_N(32), QTS_N(4), false_type{}, QTS_N(8), QTS_N(kPerRow)); break;
+      default: go(0.0, QTS_N(64), QTS_N(2), false_type{}, QTS_N(8), QTS_N(kPerRow)); break;
     }
   }
+#undef QTS_N
 }
 
 }  // namespace qts

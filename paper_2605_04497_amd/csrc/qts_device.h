@@ -74,6 +74,7 @@ struct alignas(8) WalkRow {
   int32_t xol[3];  // slots top + 1 .. top + 3
   float lol[3], hil[3];
   T bl[3], cbl[3];
+  T b0[4];         // slot 0's b and 1 - b of leaf A, then of leaf B (0 for a single path)
   int32_t xot[4];  // slots 1 .. top
   float lot[4], hit[4];
   T bt[4], cbt[4];
@@ -135,6 +136,12 @@ struct DeviceTable {
   ShortRow<double>* msrow64 = nullptr;
   // the same rows for the grouped walk, and their node-sum coefficients
   ShortWalk walk, mwalk;
+  // per bucket of each table: its first row and its output group (several
+  // outputs only)
+  int32_t* bkt_begin = nullptr;
+  int32_t* bkt_group = nullptr;
+  int32_t* mbkt_begin = nullptr;
+  int32_t* mbkt_group = nullptr;
   // feature-compacted segments (wide_features only), plain and merged tables
   int32_t* lfeat = nullptr;
   Segment* segs = nullptr;
@@ -204,19 +211,21 @@ struct PathArrays {
   const ShortRow<float>* srow32;  // capacity-8 rows (features as the kernel indexes its tile)
   const ShortRow<double>* srow64;
   ShortWalk walk;
+  const int32_t* bkt_begin;  // per bucket (several outputs only; else null)
+  const int32_t* bkt_group;
 };
 
 inline PathArrays plain_arrays(const DeviceTable& d, const HostTable& h) {
   const bool w = !h.compact.segs.empty();
   return PathArrays{d.hdr, d.feat, d.lo, d.hi, d.b32, d.cb32, d.b64, d.cb64, nullptr, d.share,
                     w ? &h.compact : nullptr, d.lfeat, d.segs, d.seg_feat, d.srow32, d.srow64,
-                    d.walk};
+                    d.walk, d.bkt_begin, d.bkt_group};
 }
 inline PathArrays merged_arrays(const DeviceTable& d, const HostTable& h) {
   const bool w = !h.mcompact.segs.empty();
   return PathArrays{d.mhdr, d.mfeat, d.mlo, d.mhi, d.mb32, d.mcb32, d.mb64, d.mcb64, d.side,
                     d.mshare, w ? &h.mcompact : nullptr, d.mlfeat, d.msegs, d.mseg_feat,
-                    d.msrow32, d.msrow64, d.mwalk};
+                    d.msrow32, d.msrow64, d.mwalk, d.mbkt_begin, d.mbkt_group};
 }
 
 // Slot 0 of a first-order row with its leaf value folded in, built per call
@@ -238,7 +247,20 @@ struct Slot0 {
 struct ValuesShape {
   int waves_per_block = 8;  // wavefronts sharing one 64-sample tile
   int items = 16384;        // target number of (sample block, path chunk) work items
+  bool tuned = false;       // false: resident_waves chooses the wavefronts at launch
 };
+
+// The buckets of one launch: n consecutive buckets of one capacity (one per
+// output group), from list[0], which is bucket `index` of its table.
+struct BucketSpan {
+  const Bucket* list;
+  int n;
+  int index;
+  int32_t dmax() const { return list[0].dmax; }
+  int32_t path_begin() const { return list[0].path_begin; }
+  int32_t path_end() const { return list[n - 1].path_end; }
+};
+std::vector<BucketSpan> bucket_spans(const std::vector<Bucket>& bks, bool one_each);
 
 // Launch shape of the interactions kernel for one capacity class.
 struct PairShape {
@@ -328,9 +350,54 @@ __device__ __forceinline__ double wave_sum_last(double v) {
   return v;
 }
 
+// v with its lanes permuted by a DPP control that reads valid lanes only
+// (quad_perm, row_ror, row_half_mirror).
+template <int CTRL>
+__device__ __forceinline__ double dpp_lanes(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// a summed over lanes l and l ^ 32 in lanes 0..31, b likewise in 32..63.
+__device__ __forceinline__ double fold32(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// a summed over lanes l and l ^ 16 in the even rows of 16 lanes, b in the odd ones.
+__device__ __forceinline__ double fold16(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// Sums over the wavefront of 8 values v, one per group of 8 lanes, from
+// w0 = fold16(fold32(v0, v1), fold32(v2, v3)) and w1 likewise of v4..v7: lanes
+// 8 k .. 8 k + 7 hold the sum of v[wave_sum8_index(lane)].  Each exchange
+// halves the values a lane still carries, so 8 sums take 35 instructions
+// where 8 reductions take 144.
+__device__ __forceinline__ int wave_sum8_index(int lane) {
+  const int row = lane >> 4;
+  return ((lane >> 3) & 1) * 4 + (row == 1 ? 2 : row == 2 ? 1 : row);
+}
+__device__ __forceinline__ double wave_sum8(double w0, double w1, int lane) {
+  w0 += dpp_lanes<0x128>(w0);  // row_ror:8
+  w1 += dpp_lanes<0x128>(w1);
+  double z = (lane & 8) ? w1 : w0;
+  z += dpp_lanes<0x141>(z);  // row_half_mirror
+  z += dpp_lanes<0xb1>(z);   // lanes 1, 0, 3, 2 of each quad
+  z += dpp_lanes<0x4e>(z);   // lanes 2, 3, 0, 1
+  return z;
+}
+
 // Raise a kernel's dynamic-LDS limit on the current device (once per kernel
 // and device; thread-safe); returns the usable dynamic LDS bytes.
 size_t raise_lds_limit(const void* fn);
+// Wavefronts per workgroup (8, 6 or 4) that keep the most wavefronts of fn
+// resident on a CU, given its VGPRs and `lds` bytes per workgroup; the larger
+// workgroup on a tie (it stages its tiles for more wavefronts).
+int resident_waves(const void* fn, size_t lds);
 
 void launch_fill_zero(double* p, int64_t n, hipStream_t s);
 // Seeded uniform values in [-3, 3) (inputs for timing launch shapes).
@@ -358,7 +425,7 @@ void launch_short_walk(const PathArrays& a, const Bucket& bk, const NodeConsts<d
                        hipStream_t s);
 size_t slot0_bytes(int32_t n_rows, bool fp64);
 
-// Accumulate phi (FP64, [M,F], pre-zeroed) over the paths of one bucket.
+// Accumulate phi (FP64, [M,F], pre-zeroed) over the paths of a span of buckets.
 // `a` is plain_arrays() or, with `bk` from HostTable::mbuckets, merged_arrays();
 // slot0 is launch_slot0's output for the same arrays and precision.  With
 // `direct` non-null (see values_direct) phi is written there instead.
@@ -370,10 +437,13 @@ size_t slot0_bytes(int32_t n_rows, bool fp64);
 // Wide feature spaces (wide_features(F): the table's work items are
 // segments) take feature-major layouts: X is [F][ldx] (ldx >= M) and acc
 // [n_groups][F][M]; `direct` is not used there.
+// per_row: FP32 takes the walks that form every slot's sum per row (calls with
+// leaf values of their own, i.e. training: the FP64-typed gradients that
+// follow from phi then keep the rounding they have had).
 void launch_values(const HostTable& h, const DeviceTable& d, const PathArrays& a,
-                   const Bucket& bk, bool fp64, const float* X, int64_t M, int64_t ldx,
+                   const BucketSpan& sp, bool fp64, const float* X, int64_t M, int64_t ldx,
                    const void* slot0, double* acc, void* direct, const ValuesShape& shape,
-                   int nodes, hipStream_t s, bool deterministic = false);
+                   int nodes, hipStream_t s, bool per_row = false, bool deterministic = false);
 // True when a first-order call over `bks` (the table in use) with M samples
 // and this launch shape is one bucket walked as one chunk: each sample block
 // has a single workgroup, which may then write phi itself (launch_values with
@@ -381,7 +451,7 @@ void launch_values(const HostTable& h, const DeviceTable& d, const PathArrays& a
 // no cast).
 bool values_direct(const std::vector<Bucket>& bks, int64_t M, const ValuesShape& shape);
 
-// Adjoint: add J^T G over the rows of one bucket into grad_leaf (pre-zeroed);
+// Adjoint: add J^T G over the rows of a span of buckets into grad_leaf (pre-zeroed);
 // a merged row adds to both of its leaves.
 // G is [M, F] float (fp64 = false) or double; wide feature spaces take X as
 // [F][ldx] and G as [n_groups][F][M] (feature-major, as launch_values).
@@ -390,7 +460,7 @@ bool values_direct(const std::vector<Bucket>& bks, int64_t M, const ValuesShape&
 // without atomics (every leaf belongs to one row), and the caller adds the
 // blocks in order (launch_sum_rows).
 void launch_adjoint(const HostTable& h, const DeviceTable& d, const PathArrays& a,
-                    const Bucket& bk, bool fp64, const float* X, const void* G, int64_t M,
+                    const BucketSpan& sp, bool fp64, const float* X, const void* G, int64_t M,
                     int64_t ldx, double* grad_leaf, const ValuesShape& shape, int nodes,
                     hipStream_t s, int64_t part_stride = 0);
 

@@ -44,7 +44,8 @@ struct Bucket {
   int64_t elems;       // sum of d over the bucket's paths
   int32_t group = 0;   // output group of the bucket's trees
   int32_t srow_begin = -1;  // capacity 8: index of its first row in the short-row records
-  int32_t top = 0;          // capacity 8: max(0, longest row - 4), see values_rows_grouped
+  int32_t top = 0;          // max(0, longest row of the table's capacity-8 buckets - 4),
+                            // see values_rows_grouped
 };
 
 // Sibling record of a merged path.  Two leaves A (left) and B (right) of one
