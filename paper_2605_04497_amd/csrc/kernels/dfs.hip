@@ -14,11 +14,11 @@
 // f was split above); a factor that vanishes identically (b = o = 0) makes
 // the subtree's polynomials zero, and the guards keep its terms exactly zero.
 //
-// dfs_pairs_kernel: the pair pass.  A workgroup owns one sample (its pair
-// triangle and phi row in LDS, FP64, as in the path form); lane = internal
+// dfs_pairs_kernel: the pair pass.  A workgroup owns up to four samples (their
+// pair triangles and phi rows in LDS, FP64, as in the path form); lane = internal
 // node (rows sorted by length in tiles of 64, slot-major inside a tile).  A
 // row adds phi_f += sum_m y_v(m) and, for every feature j split above v,
-// SII_fj += c_j sum_m y_v(m) / F_j(t_m): one update per (node, feature).
+// SII_fj += sum_m y_v(m) c_j / F_j(t_m): one update per (node, feature).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -60,15 +60,16 @@ __device__ __forceinline__ bool follows(float x, float lo, float hi, bool mok) {
 }  // namespace
 
 constexpr int kDfsSamples = 8;  // samples per wavefront of the walk (8 lanes each)
+constexpr int kDfsWindow = 64;  // events staged together
 
 // LDS of the walk: the sample rows of the workgroup's 8 samples (stride F+1),
-// then per wave the two stacks [level][64] of C and of the left subtree's H
-// and the stage of 64 events' node data.
+// then per wave the stack [level][64] (where it is in LDS) and the stage of 64
+// events' node data.
 __host__ __device__ inline size_t staged_event_bytes(size_t tsize) {
   return ((4 * sizeof(int32_t) + (kDfsCoef + 2) * tsize) + 15) & ~(size_t)15;
 }
 __host__ __device__ inline size_t dfs_wave_lds(int levels, size_t tsize) {
-  return (((size_t)2 * levels * 64 * tsize + 15) & ~(size_t)15) + 64 * staged_event_bytes(tsize);
+  return (((size_t)levels * 64 * tsize + 15) & ~(size_t)15) + kDfsWindow * staged_event_bytes(tsize);
 }
 __host__ __device__ inline size_t dfs_walk_lds(int F, int levels, int waves, size_t tsize) {
   const size_t xs = (((size_t)kDfsSamples * (F + 1) * sizeof(float)) + 15) & ~(size_t)15;
@@ -96,6 +97,13 @@ struct alignas(16) StagedEvent {
   T lv[2];           // values of leaf children (0 for internal ones)
 };
 
+// The walk is a chain of dependent steps, bound by the wavefronts in flight,
+// and those by LDS.  The stack holds one value per level: a node's C while its
+// left subtree is walked (needed again for the right one), then that subtree's
+// H.  100 trees of up to 32 levels and 512 leaves, 1003 samples, FP32: 2.86 ms
+// with a stack for each (7 wavefronts per CU), 1.90 with one (13).  The stack in
+// registers, indexed by the level, allows 16 but took 2.2 ms: its indexed
+// moves lengthen every step.
 template <typename T>
 __global__ void __launch_bounds__(1024)
 dfs_walk_kernel(const DfsNode* __restrict__ nodes, const T* __restrict__ coef,
@@ -125,9 +133,9 @@ dfs_walk_kernel(const DfsNode* __restrict__ nodes, const T* __restrict__ coef,
   const bool valid = sl < mb;
   const size_t xs_bytes = (((size_t)kDfsSamples * xstride * sizeof(float)) + 15) & ~(size_t)15;
   unsigned char* wbase = smem + xs_bytes + (size_t)wave * dfs_wave_lds(levels, sizeof(T));
-  T* cst = reinterpret_cast<T*>(wbase);
-  T* hst = cst + (size_t)levels * 64;
-  StagedEvent<T>* stage = reinterpret_cast<StagedEvent<T>*>(hst + (size_t)levels * 64);
+  T* stack = reinterpret_cast<T*>(wbase) + lane;
+  StagedEvent<T>* stage =
+      reinterpret_cast<StagedEvent<T>*>(reinterpret_cast<T*>(wbase) + (size_t)levels * 64);
   T tm = nc.t[0], wm = nc.w[0];
 #pragma unroll
   for (int k = 1; k < kNodes; ++k) {
@@ -145,8 +153,8 @@ dfs_walk_kernel(const DfsNode* __restrict__ nodes, const T* __restrict__ coef,
   // sample: above the node, left edge, right edge).  Pass 2 walks the
   // window's events in order, reading each event's data back from the stage
   // (a broadcast) and its sample's bits from the event's lane.
-  for (int w0 = 0; w0 < n_ev; w0 += 64) {
-    const int nwin = min(64, n_ev - w0);
+  for (int w0 = 0; w0 < n_ev; w0 += kDfsWindow) {
+    const int nwin = min(kDfsWindow, n_ev - w0);
     {
       const int e = ev[w0 + min(lane, nwin - 1)];
       const int r = e >> 2;
@@ -160,7 +168,7 @@ dfs_walk_kernel(const DfsNode* __restrict__ nodes, const T* __restrict__ coef,
       for (int k = 0; k < kDfsCoef; ++k) se.coef[k] = coef[(size_t)r * kDfsCoef + k];
       se.lv[0] = lvals[2 * (size_t)r];
       se.lv[1] = lvals[2 * (size_t)r + 1];
-      stage[lane] = se;
+      if (kDfsWindow == 64 || lane < kDfsWindow) stage[lane] = se;
       uint32_t bits = 0;
 #pragma unroll
       for (int qq = 0; qq < kDfsSamples; ++qq) {
@@ -188,7 +196,7 @@ dfs_walk_kernel(const DfsNode* __restrict__ nodes, const T* __restrict__ coef,
         if (kind == kDfsEnter) {
           const T bl = w.coef[2], cbl = w.coef[3];
           const T Fl = fmaD(tm, (mine & 2u) ? cbl : -bl, bl);
-          cst[level * 64 + lane] = C;
+          stack[level * 64] = C;
           // C times F_f^u / F_f^v; a vanishing F_f^v leaves the subtree at zero
           const T rv = rcpD(Fv);
           C = Fv == T(0) ? T(0) : C * Fl * rv;
@@ -196,8 +204,8 @@ dfs_walk_kernel(const DfsNode* __restrict__ nodes, const T* __restrict__ coef,
         } else if (kind == kDfsMiddle) {
           const T br = w.coef[4], cbr = w.coef[5];
           const T Fr = fmaD(tm, (mine & 4u) ? cbr : -br, br);
-          const T Cv = cst[level * 64 + lane];
-          hst[level * 64 + lane] = H;
+          const T Cv = stack[level * 64];
+          stack[level * 64] = H;
           const T rv = rcpD(Fv);
           C = Fv == T(0) ? T(0) : Cv * Fr * rv;
           H = w.lv[1] * C;
@@ -207,7 +215,7 @@ dfs_walk_kernel(const DfsNode* __restrict__ nodes, const T* __restrict__ coef,
           const T bl = w.coef[2], cbl = w.coef[3], br = w.coef[4], cbr = w.coef[5];
           const T Fl = fmaD(tm, ol ? cbl : -bl, bl);
           const T Fr = fmaD(tm, orr ? cbr : -br, br);
-          const T HL = hst[level * 64 + lane];
+          const T HL = stack[level * 64];
           const T nl = ol ? w.coef[6] : (ov ? -bl : T(0));
           const T nr = orr ? w.coef[7] : (ov ? -br : T(0));
           const T il = rcpD(Fl * Fv), ir = rcpD(Fr * Fv);
@@ -249,7 +257,15 @@ dfs_leaf_values_kernel(const DfsNode* __restrict__ nodes, int32_t n,
   out[2 * (size_t)r + 1] = rr >= 0 ? (T)leaf_val[rr] : T(0);
 }
 
-template <typename T>
+// The pair pass for S consecutive samples per workgroup.  r_j^v = c_j / F_j
+// depends on the sample only through its follow bit: followed, it is
+// (1 - b_j) / (b_j + t_m (1 - b_j)), whose reciprocals (a quarter of the FMA
+// rate) are formed once per (row, feature) for all S samples; not followed, it
+// is -1 / (1 - t_m), one sum D per (row, sample) for all features.
+// Bound by VALU issue at S = 1 and by the LDS adds at S = 4.  100 trees of up
+// to 32 features and 512 leaves, 64 features, 1003 samples, FP32: 2.17 ms with
+// the reciprocals per sample, 1.41 here.
+template <typename T, int S>
 __global__ void __launch_bounds__(1024)
 dfs_pairs_kernel(const int32_t* __restrict__ row_f, const int32_t* __restrict__ row_d,
                  const int32_t* __restrict__ tile_base, const int32_t* __restrict__ tile_d,
@@ -263,18 +279,19 @@ dfs_pairs_kernel(const int32_t* __restrict__ row_f, const int32_t* __restrict__ 
   extern __shared__ __align__(16) unsigned char smem[];
   const int64_t ntri = (int64_t)F * (F - 1) / 2;
   const int64_t base0 = (int64_t)r0 * (r0 - 1) / 2;
-  const int64_t ntri_r = (int64_t)r1 * (r1 - 1) / 2 - base0;
-  double* phis = reinterpret_cast<double*>(smem);  // [F]
-  double* tris = phis + F;                         // [ntri_r]
-  float* xrow = reinterpret_cast<float*>(tris + ntri_r);  // [F]
-  const int sl = (int)(blockIdx.x % (unsigned)mb);
-  const int ch = (int)(blockIdx.x / (unsigned)mb);
-  const int64_t s = s0 + sl;
-  for (int i = threadIdx.x; i < F; i += blockDim.x) {
-    xrow[i] = X[s * ldx + i];
+  const int ntri_r = (int)((int64_t)r1 * (r1 - 1) / 2 - base0);
+  float* xrow = reinterpret_cast<float*>(smem);                    // [F][S]
+  double* phis = reinterpret_cast<double*>(smem + (((size_t)F * S * sizeof(float) + 15) & ~(size_t)15));  // [S][F]
+  double* tris = phis + S * F;                                     // [S][ntri_r]
+  const int nsg = (mb + S - 1) / S;
+  const int sl0 = (int)(blockIdx.x % (unsigned)nsg) * S;
+  const int ch = (int)(blockIdx.x / (unsigned)nsg);
+  for (int i = threadIdx.x; i < S * F; i += blockDim.x) {
+    const int q = i / F, f = i - q * F;
+    xrow[f * S + q] = sl0 + q < mb ? X[(s0 + sl0 + q) * ldx + f] : 0.0f;
     phis[i] = 0.0;
   }
-  for (int64_t e = threadIdx.x; e < ntri_r; e += blockDim.x) tris[e] = 0.0;
+  for (int e = threadIdx.x; e < S * ntri_r; e += blockDim.x) tris[e] = 0.0;
   __syncthreads();
 
   const int lane = threadIdx.x & 63;
@@ -285,25 +302,33 @@ dfs_pairs_kernel(const int32_t* __restrict__ row_f, const int32_t* __restrict__ 
   for (int tile = tb0 + wave; tile < tb1; tile += nw) {
     const int row = tile * 64 + lane;
     const int f = row_f[row];
-    const int d = row_d[row];
-    T y[kNodes];
-    T ysum = T(0);
-    const T* yp = Y + ((int64_t)sl * n_rows + row) * kNodes;
+    const int d = f >= 0 ? row_d[row] : 0;
+    T y[S][kNodes], D[S];
 #pragma unroll
-    for (int k = 0; k < kNodes; ++k) {
-      y[k] = f >= 0 ? yp[k] : T(0);
-      ysum += y[k];
+    for (int q = 0; q < S; ++q) {
+      // samples past the batch repeat its last one and add nothing
+      const T* yp = Y + ((int64_t)min(sl0 + q, mb - 1) * n_rows + row) * kNodes;
+      const bool on = f >= 0 && sl0 + q < mb;
+      T ysum = T(0);
+#pragma unroll
+      for (int k = 0; k < kNodes; ++k) {
+        y[q][k] = on ? yp[k] : T(0);
+        ysum += y[q][k];
+      }
+      D[q] = nc.r[0] * y[q][0];
+#pragma unroll
+      for (int m = 1; m < kNodes; ++m) D[q] = fmaD(nc.r[m], y[q][m], D[q]);
+      if (with_phi && on && ysum != T(0))
+        __hip_atomic_fetch_add(&phis[q * F + f], (double)ysum, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    if (with_phi && f >= 0 && ysum != T(0))
-      __hip_atomic_fetch_add(&phis[f], (double)ysum, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
     const int eb = __builtin_amdgcn_readfirstlane(tile_base[tile]);
     const int td = __builtin_amdgcn_readfirstlane(tile_d[tile]);
     // slots in groups of four: every load of a group issues before its first
     // use, so the wave waits for memory once per group, not once per slot
     for (int k0 = 0; k0 < td; k0 += 4) {
       int fm[4];
-      float l[4], u[4], xv[4];
+      float l[4], u[4], xv[4][S];
       T bq[4], cq[4];
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
@@ -315,38 +340,48 @@ dfs_pairs_kernel(const int32_t* __restrict__ row_f, const int32_t* __restrict__ 
         cq[w] = cbb[e];
       }
 #pragma unroll
-      for (int w = 0; w < 4; ++w) xv[w] = xrow[fm[w] & kFeatureMask];
+      for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int q = 0; q < S; ++q) xv[w][q] = xrow[(fm[w] & kFeatureMask) * S + q];
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        const int k = k0 + w;
-        const T b = bq[w];
-        const bool o = follows(xv[w], l[w], u[w], (fm[w] & kMissingOkBit) != 0);
-        const T c = o ? cq[w] : -b;
-        // a factor that vanishes identically zeroes every leaf below (y = 0)
-        if (k < d && f >= 0 && !(b == T(0) && c == T(0))) {
-          T acc = y[0] * rcpD(fmaD(nc.t[0], c, b));
+        if (k0 + w < d) {
+          // b + t (1 - b) > 0 at the nodes, also where b = 0; a factor that
+          // vanishes identically (not followed, b = 0) has y = 0, so D = 0
+          T rf[kNodes];
 #pragma unroll
-          for (int m = 1; m < kNodes; ++m) acc = fmaD(y[m], rcpD(fmaD(nc.t[m], c, b)), acc);
-          const T v = c * acc;
+          for (int m = 0; m < kNodes; ++m) rf[m] = rcpD(fmaD(nc.t[m], cq[w], bq[w]));
           const int j = fm[w] & kFeatureMask;
+          const bool mok = (fm[w] & kMissingOkBit) != 0;
           const int a = min(f, j), zf = max(f, j);
-          if (zf >= r0 && zf < r1 && v != T(0))
-            __hip_atomic_fetch_add(&tris[(int64_t)zf * (zf - 1) / 2 + a - base0], (double)v,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          const int idx = (int)((int64_t)zf * (zf - 1) / 2 - base0) + a;
+          const bool here = zf >= r0 && zf < r1;
+#pragma unroll
+          for (int q = 0; q < S; ++q) {
+            T E = y[q][0] * rf[0];
+#pragma unroll
+            for (int m = 1; m < kNodes; ++m) E = fmaD(y[q][m], rf[m], E);
+            const T v = follows(xv[w][q], l[w], u[w], mok) ? cq[w] * E : D[q];
+            if (here && v != T(0))
+              __hip_atomic_fetch_add(&tris[q * ntri_r + idx], (double)v, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
         }
       }
     }
   }
   __syncthreads();
-  const int64_t orow = s * ng + grp;
-  if (with_phi)
-    for (int i = threadIdx.x; i < F; i += blockDim.x) {
-      const double v = phis[i];
-      if (v != 0.0) unsafeAtomicAdd(&phi64[orow * F + i], v);
+  for (int q = 0; q < S && sl0 + q < mb; ++q) {
+    const int64_t orow = (s0 + sl0 + q) * ng + grp;
+    if (with_phi)
+      for (int i = threadIdx.x; i < F; i += blockDim.x) {
+        const double v = phis[q * F + i];
+        if (v != 0.0) unsafeAtomicAdd(&phi64[orow * F + i], v);
+      }
+    for (int e = threadIdx.x; e < ntri_r; e += blockDim.x) {
+      const double v = tris[q * ntri_r + e];
+      if (v != 0.0) unsafeAtomicAdd(&tri64[orow * ntri + base0 + e], v);
     }
-  for (int64_t e = threadIdx.x; e < ntri_r; e += blockDim.x) {
-    const double v = tris[e];
-    if (v != 0.0) unsafeAtomicAdd(&tri64[orow * ntri + base0 + e], v);
   }
 }
 
@@ -538,8 +573,8 @@ void walk_t(const HostTable& h, const DeviceDfs& d, const NodeConsts<T>& nc,
     check_hip(hipGetLastError(), "dfs_leaf_values_kernel launch");
   }
   const size_t limit = raise_lds_limit((const void*)dfs_walk_kernel<T>);
-  // as many waves (trees) per workgroup as the stacks allow, up to 16: the
-  // walk is bound by the latency of its sequential steps, which more waves hide
+  // as many waves (trees) per workgroup as the LDS allows, up to 16: the walk
+  // is bound by the latency of its sequential steps, which more waves hide
   int waves = 16;
   while (waves > 1 && dfs_walk_lds(F, levels, waves, sizeof(T)) > limit) --waves;
   const size_t lds = dfs_walk_lds(F, levels, waves, sizeof(T));
@@ -551,39 +586,43 @@ void walk_t(const HostTable& h, const DeviceDfs& d, const NodeConsts<T>& nc,
   if (grid > 0x7fffffff) fail(QTS_E_UNSUPPORTED, "depth-first walk grid too large");
   const T* coef = std::is_same<T, float>::value ? (const T*)d.coef32 : (const T*)d.coef64;
   hipLaunchKernelGGL((dfs_walk_kernel<T>), dim3((unsigned)grid), dim3(64 * waves), lds, s,
-                     d.nodes, coef, (const T*)lvals, d.events, d.tree_first, d.tree_nodes,
-                     d.n_trees, X, s0, mb, ldx, F, levels, nsg, d.n_rows, Y, nc);
+                     d.nodes, coef, (const T*)lvals, d.events, d.tree_first, d.tree_nodes, d.n_trees, X, s0,
+                     mb, ldx, F, levels, nsg, d.n_rows, Y, nc);
   check_hip(hipGetLastError(), "dfs_walk_kernel launch");
 }
 
-template <typename T>
-void pairs_t(const HostTable& h, const DeviceDfs& d, const NodeConsts<T>& nc, const float* X,
+// LDS of the pair pass: x rows, phi rows and n_tri triangle entries per sample.
+size_t dfs_pairs_lds(int F, int64_t n_tri, int S) {
+  return (((size_t)F * S * sizeof(float) + 15) & ~(size_t)15) +
+         (size_t)S * ((size_t)F + (size_t)n_tri) * sizeof(double);
+}
+
+template <typename T, int S>
+void pairs_s(const HostTable& h, const DeviceDfs& d, const NodeConsts<T>& nc, const float* X,
              int64_t s0, int32_t mb, int64_t ldx, const T* Y, double* tri64, double* phi64,
-             int32_t tiles_per_chunk, hipStream_t s) {
+             int32_t chunk, hipStream_t s) {
   const int F = h.F;
-  const void* fn = (const void*)dfs_pairs_kernel<T>;
-  const size_t limit = raise_lds_limit(fn);
-  const size_t fixed = (size_t)F * sizeof(double) + (size_t)F * sizeof(float);
+  const size_t limit = raise_lds_limit((const void*)dfs_pairs_kernel<T, S>);
+  const size_t fixed = dfs_pairs_lds(F, 0, S);
   if (fixed >= limit) fail(QTS_E_UNSUPPORTED, "n_features too large for the interactions kernel");
   // triangle rows [r0, r1) whose FP64 entries fit beside the fixed part
-  const int64_t cap = (int64_t)((limit - fixed) / sizeof(double));
+  const int64_t cap = (int64_t)((limit - fixed) / (S * sizeof(double)));
   if (cap < F) fail(QTS_E_UNSUPPORTED, "n_features too large for the interactions kernel");
+  const T* b = std::is_same<T, float>::value ? (const T*)d.b32 : (const T*)d.b64;
+  const T* cb = std::is_same<T, float>::value ? (const T*)d.cb32 : (const T*)d.cb64;
   for (int g = 0; g < h.n_groups; ++g) {
     const int t0 = d.group_tile[g], t1 = d.group_tile[g + 1];
     if (t1 <= t0) continue;
-    const int chunk = std::max(1, tiles_per_chunk);
     const int64_t n_chunks = (t1 - t0 + chunk - 1) / chunk;
-    const int64_t grid = (int64_t)mb * n_chunks;
+    const int64_t grid = (int64_t)((mb + S - 1) / S) * n_chunks;
     if (grid > 0x7fffffff) fail(QTS_E_UNSUPPORTED, "depth-first pair grid too large");
-    const T* b = std::is_same<T, float>::value ? (const T*)d.b32 : (const T*)d.b64;
-    const T* cb = std::is_same<T, float>::value ? (const T*)d.cb32 : (const T*)d.cb64;
     bool first = true;
     int r0 = 0;
     while (r0 < F) {
       int r1 = r0 + 1;
       while (r1 < F && tri_h(r1 + 1) - tri_h(r0) <= cap) ++r1;
-      const size_t lds = fixed + (size_t)(tri_h(r1) - tri_h(r0)) * sizeof(double);
-      hipLaunchKernelGGL((dfs_pairs_kernel<T>), dim3((unsigned)grid), dim3(1024), lds, s,
+      const size_t lds = dfs_pairs_lds(F, tri_h(r1) - tri_h(r0), S);
+      hipLaunchKernelGGL((dfs_pairs_kernel<T, S>), dim3((unsigned)grid), dim3(1024), lds, s,
                          d.row_f, d.row_d, d.tile_base, d.tile_d, d.feat, d.lo, d.hi, b, cb, t0,
                          t1, chunk, Y, d.n_rows, X, s0, mb, ldx, F, r0, r1, (int)first,
                          h.n_groups, g, tri64, phi64, nc);
@@ -592,6 +631,23 @@ void pairs_t(const HostTable& h, const DeviceDfs& d, const NodeConsts<T>& nc, co
       r0 = r1;
     }
   }
+}
+
+// Samples per workgroup: as many (4, 2 or 1) as have their whole triangles in
+// LDS together, and leave at least two workgroups per CU.
+template <typename T>
+void pairs_t(const HostTable& h, const DeviceDfs& d, const NodeConsts<T>& nc, const float* X,
+             int64_t s0, int32_t mb, int64_t ldx, const T* Y, double* tri64, double* phi64,
+             int32_t tiles_per_chunk, hipStream_t s) {
+  const int chunk = std::max(1, tiles_per_chunk);
+  const int64_t n_chunks = std::max<int64_t>(1, d.n_rows / 64 / chunk);
+  auto fits = [&](int S) {
+    return dfs_pairs_lds(h.F, tri_h(h.F), S) <= (size_t)kMaxLdsBytes &&
+           (mb + S - 1) / S * n_chunks >= 512;
+  };
+  if (fits(4)) pairs_s<T, 4>(h, d, nc, X, s0, mb, ldx, Y, tri64, phi64, chunk, s);
+  else if (fits(2)) pairs_s<T, 2>(h, d, nc, X, s0, mb, ldx, Y, tri64, phi64, chunk, s);
+  else pairs_s<T, 1>(h, d, nc, X, s0, mb, ldx, Y, tri64, phi64, chunk, s);
 }
 
 // The third-order pass adds into the sample's tensor range in LDS and

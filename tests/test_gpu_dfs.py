@@ -188,3 +188,21 @@ def test_auto_traversal_keeps_parity(q, oracle_mod):
         print("auto traversal %s: pairs_dfs=%d" % (precision, info["pairs_dfs"]), flush=True)
         check(e.shap_interactions(X, precision).double().cpu().numpy(), Phi_o, precision,
               "auto traversal")
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("F,M", [(10, 2051), (130, 515), (160, 260)])
+def test_dfs_pair_pass_samples_per_workgroup(q, oracle_mod, F, M, precision):
+    """The pair pass takes four samples per workgroup, two or one as their
+    triangles fit in LDS (F = 10, 130 and 160), with a last workgroup of fewer."""
+    print("case", F, M, precision, flush=True)
+    wl = synth.make_workload("c5_deep", T=40, M=M, n_train=4000, F=F)
+    e = q.Ensemble(wl.ensemble)
+    e.set_pair_traversal("dfs")
+    X = torch.from_numpy(wl.X).cuda()
+    Phi, phi = e.shap_interactions(X, precision, with_phi=True)
+    rows = [0, 1, 2, 3, M // 2, M - 2, M - 1]
+    want_phi, want = oracle_mod.shap_interactions(wl.ensemble, wl.X[rows], n=8)
+    check(Phi[rows].double().cpu().numpy(), want, precision, "Phi")
+    check(phi[rows].double().cpu().numpy(), want_phi, precision, "phi")
+    e.close()
