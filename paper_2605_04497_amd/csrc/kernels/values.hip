@@ -1697,7 +1697,7 @@ __device__ __forceinline__ void adjoint_rows_grouped(
 // L2).  With the inert slots left out (119 VGPRs instead of 136 at depth 6,
 // four waves per SIMD), four rows' sums folded together over the wave and
 // four wavefronts' worth of registers per SIMD in use, 200 trees of depth 6,
-// 50 features, 20k rows, FP32 take 0.57 ms; 1.59 before.  part_rows = 0: no room for the sums next to the tiles, every row adds
+// 50 features, 20k rows, FP32 take 0.6 ms; 1.6 before.  part_rows = 0: no room for the sums next to the tiles, every row adds
 // to memory.  TOP: the bucket's (capacity 8); FP64 at 8 nodes takes the grouped
 // walk with it, the others adjoint_rows_shared with ND = TOP + 3.
 // Three waves per SIMD (168 VGPRs) where the instance is within a few
