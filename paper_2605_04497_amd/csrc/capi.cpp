@@ -699,7 +699,15 @@ void issue_values(const qts_ensemble* ens, const float* X, int64_t M, int64_t ld
   const PathArrays arr = ens->merge_siblings ? merged_arrays(ens->dev, ens->host)
                                              : plain_arrays(ens->dev, ens->host);
   const std::vector<Bucket>& bks = ens->merge_siblings ? h.mbuckets : h.buckets;
-  launch_slot0(arr, value_rows(ens), leaf, fp64, slot0, ln.main);
+  // one launch per capacity, over all output groups (7 outputs, 350 trees of
+  // depth 6, 4099 rows: 340 us with a launch per group, 232 with one)
+  const std::vector<BucketSpan> spans = bucket_spans(bks, ens->deterministic);
+  bool use_slot0 = false;  // a span whose walk reads the Slot0 records
+  auto lane = [&](const BucketSpan& sp) {
+    return !ens->deterministic && values_lane(sp, M, h.F, nodes_of(ens));
+  };
+  for (const BucketSpan& sp : spans) use_slot0 |= !lane(sp);
+  if (use_slot0) launch_slot0(arr, value_rows(ens), leaf, fp64, slot0, ln.main);
   // a call with leaf values of its own is a training step's (launch_values)
   const bool per_row = leaf != ens->dev.leaf_val;
   // wide feature spaces: X transposed into the scratch, the accumulator
@@ -730,7 +738,7 @@ void issue_values(const qts_ensemble* ens, const float* X, int64_t M, int64_t ld
     // one stream, buckets and chunks in order, adds without atomics
     launch_fill_zero(a, n, ln.main);
     TimedScope ts(0, timed ? ln.main : nullptr, timed);
-    for (const BucketSpan& sp : bucket_spans(bks, true))
+    for (const BucketSpan& sp : spans)
       launch_values(h, ens->dev, arr, sp, fp64, Xk, M, ldk, slot0, a, nullptr,
                     ens->vshape[pol_index(ens)][fp64 ? 1 : 0][cap_index(sp.dmax())],
                     nodes_of(ens), ln.main, per_row, true);
@@ -740,7 +748,11 @@ void issue_values(const qts_ensemble* ens, const float* X, int64_t M, int64_t ld
   }
   if (direct_call(ens, M, fp64)) {
     TimedScope ts(0, timed ? ln.main : nullptr, timed);
-    launch_values(h, ens->dev, arr, bucket_spans(bks, true)[0], fp64, X, M, ldx, slot0, nullptr, phi,
+    if (lane(spans[0]))
+      launch_values_lane(h, ens->dev, arr, spans[0], fp64, X, M, ldx, leaf, nullptr, phi, false,
+                         ln.main);
+    else
+      launch_values(h, ens->dev, arr, spans[0], fp64, X, M, ldx, slot0, nullptr, phi,
                   ens->vshape[pol_index(ens)][fp64 ? 1 : 0][cap_index(bks[0].dmax)],
                   nodes_of(ens), ln.main, per_row);
     ts.done();
@@ -748,12 +760,14 @@ void issue_values(const qts_ensemble* ens, const float* X, int64_t M, int64_t ld
   }
   launch_fill_zero(a, n, ln.main);
   TimedScope ts(0, timed ? ln.main : nullptr, timed);
-  // one launch per capacity, over all output groups (7 outputs, 350 trees of
-  // depth 6, 4099 rows: 340 us with a launch per group, 232 with one)
-  const std::vector<BucketSpan> spans = bucket_spans(bks, false);
   ln.fork((int)spans.size());
   for (size_t i = 0; i < spans.size(); ++i) {
     const BucketSpan& sp = spans[i];
+    if (lane(sp)) {
+      launch_values_lane(h, ens->dev, arr, sp, fp64, Xk, M, ldk, leaf, a, nullptr, fmajor,
+                         ln.pick((int)i));
+      continue;
+    }
     launch_values(h, ens->dev, arr, sp, fp64, Xk, M, ldk, slot0, a, nullptr,
                   ens->vshape[pol_index(ens)][fp64 ? 1 : 0][cap_index(sp.dmax())], nodes_of(ens),
                   ln.pick((int)i), per_row);

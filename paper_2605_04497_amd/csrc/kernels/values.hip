@@ -2174,6 +2174,196 @@ void launch_short_walk(const PathArrays& a, const Bucket& bk, const NodeConsts<d
   check_hip(hipGetLastError(), "short_walk_kernel launch");
 }
 
+// First order of a few samples over rows of at most 8 features: a lane takes a
+// row, a workgroup one sample and kLaneRows rows.  With samples across lanes a
+// call of one sample uses one lane of 64, and is bound by the latency of the
+// rows that a wavefront walks one after another; splitting the rows over more
+// workgroups runs into their adds to the same few phi entries.
+// The arithmetic of a row is values_rows_shared's, operation by operation, so
+// a row's terms have the same bits (slot 0's factor is formed here, from the
+// current leaf values, and no Slot0 records are needed).
+constexpr int kLaneRows = 512;
+
+template <typename T, int ND>
+__global__ void __launch_bounds__(kLaneRows)
+values_lane_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
+                   const float* __restrict__ lo, const float* __restrict__ hi,
+                   const T* __restrict__ bb, const T* __restrict__ cbb,
+                   const double* __restrict__ b64, const double* __restrict__ cb64,
+                   const SidePath* __restrict__ side, const double* __restrict__ leaf_val,
+                   const float* __restrict__ X, int64_t M, int64_t ldx, int32_t F,
+                   int32_t fmajor, int32_t path_begin, int32_t path_end, int32_t ng,
+                   BucketIndex bx, double* __restrict__ acc, void* __restrict__ direct,
+                   NodeConsts<T> nc) {
+  constexpr int N = 8, kLastP = ND < 7 ? ND : 6;
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* phis = reinterpret_cast<double*>(smem);  // [F]
+  float* xrow = reinterpret_cast<float*>(phis + F);
+  const int64_t s = (int64_t)blockIdx.x % M;
+  const int ch = (int)((int64_t)blockIdx.x / M);
+  const ItemRows ir = item_rows(nullptr, nullptr, ch, path_begin, path_end, kLaneRows, F, bx);
+  for (int i = threadIdx.x; i < F; i += blockDim.x) {
+    xrow[i] = fmajor ? X[(int64_t)i * ldx + s] : X[s * ldx + i];
+    phis[i] = 0.0;
+  }
+  const int p = min(ir.p0 + (int)threadIdx.x, ir.p1 - 1);
+  const PathHdr h = hdr[p];
+  int fw[ND + 1];
+  float l[ND + 1], u[ND + 1];
+  T b[ND + 1], cb[ND + 1];
+#pragma unroll
+  for (int k = 0; k <= ND; ++k) {
+    fw[k] = feat[h.off + k];
+    l[k] = lo[h.off + k];
+    u[k] = hi[h.off + k];
+    b[k] = bb[h.off + k];
+    cb[k] = cbb[h.off + k];
+  }
+  // slot 0 as slot0_kernel forms it
+  const int sidx = side == nullptr ? -1 : h.tree;
+  T bm = T(0), cA = T(0), cB = T(0);
+  float loB = l[0], hiB = u[0];
+  bool mokB = (fw[0] & kMissingOkBit) != 0;
+  if (h.d > 0 && sidx >= 0) {
+    const SidePath sp = side[sidx];
+    const double va = leaf_val[h.leaf], vb = leaf_val[sp.leaf_b];
+    bm = (T)(va * sp.b_a + vb * sp.b_b);
+    cA = (T)(va * sp.cb_a - vb * sp.b_b);
+    cB = (T)(vb * sp.cb_b - va * sp.b_a);
+    loB = sp.lo_b;
+    hiB = sp.hi_b;
+    mokB = sp.mok_b != 0;
+  } else if (h.d > 0) {
+    const double v = leaf_val[h.leaf];
+    const double vm = v * b64[h.off];
+    bm = (T)vm;
+    cA = (T)(v * cb64[h.off]);
+    cB = (T)(-vm);
+  }
+  __syncthreads();
+  auto follows = [&](float x, float lv, float uv, bool miss) {
+    return (miss ? !(x < lv) : (x >= lv)) & !(x >= uv);
+  };
+  T c[ND + 1], P[ND + 1][N];
+#pragma unroll
+  for (int m = 0; m < N; ++m) P[0][m] = node8_w(nc, m);
+#pragma unroll
+  for (int k = 0; k <= ND; ++k) {
+    const float x = xrow[fw[k] & kFeatureMask];
+    const bool in = follows(x, l[k], u[k], (fw[k] & kMissingOkBit) != 0);
+    if (k == 0) {
+      c[0] = in ? cA : (follows(x, loB, hiB, mokB) ? cB : -bm);
+      b[0] = bm;
+    } else {
+      c[k] = in ? cb[k] : -b[k];
+    }
+    if (k >= 1 && k <= kLastP) {
+#pragma unroll
+      for (int m = 0; m < N; ++m) P[k][m] = P[k - 1][m] * fmaT(node8_t(nc, m), c[k], b[k]);
+    }
+  }
+  T one = T(1);
+  asm volatile("" : "+v"(one));
+  const bool on = ir.p0 + (int)threadIdx.x < ir.p1;
+  auto add = [&](int k, T v) {
+    if (on)
+      __hip_atomic_fetch_add(&phis[fw[k] & kFeatureMask], (double)v, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  {
+    auto g = [&](int m) { return ND < 7 ? one : fmaT(node8_t(nc, m), c[ND], b[ND]); };
+    T dot = P[kLastP][0] * g(0);
+#pragma unroll
+    for (int m = 1; m < N; ++m) dot = fmaT(P[kLastP][m], g(m), dot);
+    add(0, c[0] * dot);
+  }
+  T S[N];
+#pragma unroll
+  for (int m = 0; m < N; ++m) S[m] = fmaT(node8_t(nc, m), c[0], b[0]);
+#pragma unroll
+  for (int j = ND; j >= 1; --j) {
+    if (j < h.d) {
+      T dot = P[j - 1][0] * S[0];
+#pragma unroll
+      for (int m = 1; m < N; ++m) dot = fmaT(P[j - 1][m], S[m], dot);
+      add(j, c[j] * dot);
+    }
+    if (j > 1) {
+#pragma unroll
+      for (int m = 0; m < N; ++m) S[m] *= fmaT(node8_t(nc, m), c[j], b[j]);
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < F; i += blockDim.x) {
+    const double v = phis[i];
+    if (direct != nullptr) {
+      const int64_t o = (s * ng + ir.grp) * F + i;
+      if (sizeof(T) == 8) static_cast<double*>(direct)[o] = v;
+      else static_cast<float*>(direct)[o] = (float)v;
+    } else if (v != 0.0) {
+      const int64_t o = fmajor ? ((int64_t)ir.grp * F + i) * M + s : (s * ng + ir.grp) * F + i;
+      unsafeAtomicAdd(&acc[o], v);
+    }
+  }
+}
+
+// The lane kernel's time grows with samples x rows, the others' hardly with up
+// to 64 samples.  Microseconds a call (samples in lanes | rows in lanes):
+//   1000 trees of depth 8 (128k rows), FP32: 1 sample 62 | 17, 8: 64 | 57,
+//   16: 66 | 77; FP64: 1: 119 | 16, 16: 124 | 124;
+//   500 trees of depth 6 (16k rows), FP32: 1: 24 | 18, 32: 25 | 20, 48: 26 | 25.
+bool values_lane(const BucketSpan& sp, int64_t M, int F, int nodes) {
+  const int64_t rows = sp.path_end() - sp.path_begin();
+  return sp.dmax() == 8 && nodes == 8 && (M <= 12 || (M <= 64 && M * rows <= (int64_t)1 << 19)) &&
+         (size_t)F * (sizeof(double) + sizeof(float)) <= (size_t)kMaxLdsBytes;
+}
+
+template <typename T, int ND>
+static void launch_lane_one(const HostTable& h, const DeviceTable& d, const PathArrays& a,
+                            const BucketSpan& sp, const float* X, int64_t M, int64_t ldx,
+                            const double* leaf_val, double* acc, void* direct, bool fmajor,
+                            hipStream_t s) {
+  const void* fn = (const void*)values_lane_kernel<T, ND>;
+  const size_t lds = (size_t)h.F * (sizeof(double) + sizeof(float));
+  if (lds > raise_lds_limit(fn)) fail(QTS_E_UNSUPPORTED, "internal: n_features too large");
+  const int64_t grid = M * n_chunks_of(sp, kLaneRows);
+  if (grid > 0x7fffffff) fail(QTS_E_UNSUPPORTED, "grid too large");
+  const T *b, *cb;
+  NodeConsts<T> nc;
+  if constexpr (std::is_same<T, float>::value) {
+    b = a.b32;
+    cb = a.cb32;
+    nc = d.n32;
+  } else {
+    b = a.b64;
+    cb = a.cb64;
+    nc = d.n64;
+  }
+  hipLaunchKernelGGL((values_lane_kernel<T, ND>), dim3((unsigned)grid), dim3(kLaneRows), lds, s,
+                     a.hdr, a.feat, a.lo, a.hi, b, cb, a.b64, a.cb64, a.side, leaf_val, X, M, ldx,
+                     h.F, (int32_t)fmajor, sp.path_begin(), sp.path_end(), h.n_groups,
+                     bucket_index(a, sp), acc, direct, nc);
+  check_hip(hipGetLastError(), "values_lane_kernel launch");
+}
+
+void launch_values_lane(const HostTable& h, const DeviceTable& d, const PathArrays& a,
+                        const BucketSpan& sp, bool fp64, const float* X, int64_t M, int64_t ldx,
+                        const double* leaf_val, double* acc, void* direct, bool fmajor,
+                        hipStream_t s) {
+  auto go = [&](auto nd) {
+    constexpr int kNd = decltype(nd)::value;
+    if (fp64) launch_lane_one<double, kNd>(h, d, a, sp, X, M, ldx, leaf_val, acc, direct, fmajor, s);
+    else launch_lane_one<float, kNd>(h, d, a, sp, X, M, ldx, leaf_val, acc, direct, fmajor, s);
+  };
+  switch (sp.list[0].top) {
+    case 0: go(std::integral_constant<int, 3>{}); break;
+    case 1: go(std::integral_constant<int, 4>{}); break;
+    case 2: go(std::integral_constant<int, 5>{}); break;
+    case 3: go(std::integral_constant<int, 6>{}); break;
+    default: go(std::integral_constant<int, 7>{}); break;
+  }
+}
+
 // Slot 0 of every first-order row with the current leaf values folded in.
 template <typename T>
 __global__ void __launch_bounds__(256)

@@ -444,6 +444,13 @@ void launch_values(const HostTable& h, const DeviceTable& d, const PathArrays& a
                    const BucketSpan& sp, bool fp64, const float* X, int64_t M, int64_t ldx,
                    const void* slot0, double* acc, void* direct, const ValuesShape& shape,
                    int nodes, hipStream_t s, bool per_row = false, bool deterministic = false);
+// A span's rows for a few samples, a lane per row (values_lane says when);
+// forms slot 0 from leaf_val itself.  fmajor: X and acc feature-major.
+bool values_lane(const BucketSpan& sp, int64_t M, int F, int nodes);
+void launch_values_lane(const HostTable& h, const DeviceTable& d, const PathArrays& a,
+                        const BucketSpan& sp, bool fp64, const float* X, int64_t M, int64_t ldx,
+                        const double* leaf_val, double* acc, void* direct, bool fmajor,
+                        hipStream_t s);
 // True when a first-order call over `bks` (the table in use) with M samples
 // and this launch shape is one bucket walked as one chunk: each sample block
 // has a single workgroup, which may then write phi itself (launch_values with

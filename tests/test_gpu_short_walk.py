@@ -71,3 +71,27 @@ def test_long_walk_matches_oracle(q, oracle_mod, depth, F, leaf, precision):
                 got = e.shap_values(Xd[:m], precision).cpu().numpy().astype(np.float64)
                 check(got, want[:m], precision, "M=%d merge=%s" % (m, merge))
     e.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("F,K,M", [(20, 1, 1), (20, 3, 12), (20, 1, 13), (300, 1, 5), (300, 2, 64)])
+def test_few_samples_match_oracle(q, oracle_mod, F, K, M, precision):
+    """A lane per row: one sample to the rule's edges, output groups, wide
+    feature spaces (feature-major accumulators), leaf values of the caller's,
+    and a table of more than one workgroup's rows."""
+    print("case", F, K, M, precision, flush=True)
+    over = dict(groups=K) if K > 1 else {}
+    wl = synth.make_workload("c2_values", T=12 * K, M=M, n_train=4000, F=F, **over)
+    e = q.Ensemble(wl.ensemble)
+    X = wl.X.copy()
+    X[::2, ::3] = np.nan
+    Xd = torch.from_numpy(X).cuda()
+    v = np.random.default_rng(3).normal(size=wl.ensemble.n_leaves())
+    values = oracle_mod.shap_values_grouped if K > 1 else oracle_mod.shap_values
+    for leaf in (None, v):
+        ens = wl.ensemble if leaf is None else wl.ensemble.with_leaf_values(leaf)
+        want = values(ens, X, n=8).reshape(M, -1)
+        lv = None if leaf is None else torch.from_numpy(leaf).cuda()
+        got = e.shap_values(Xd, precision, leaf_values=lv).double().cpu().numpy()
+        check(got.reshape(M, -1), want, precision, "leaf override %s" % (leaf is not None))
+    e.close()
