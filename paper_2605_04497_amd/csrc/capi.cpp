@@ -1408,7 +1408,8 @@ size_t interactions3_scratch_bytes(const qts_ensemble* ens, int64_t M, bool fp64
                       (fp64 ? sizeof(double) : sizeof(float));
     return ab + yb + lb;
   }
-  return fp64 ? 0 : sizeof(double) * (size_t)(MK * T3);
+  if (fp64 || triples_direct(ens->host, ens->pair_classes, M)) return 0;
+  return sizeof(double) * (size_t)(MK * T3);
 }
 
 // The launches of one third-order call on stream s, with `scratch` of
@@ -1439,10 +1440,14 @@ void issue_interactions3(const qts_ensemble* ens, const float* X, int64_t M, int
     ts.done();
     return;
   }
+  if (triples_direct(ens->host, ens->pair_classes, M)) {
+    launch_triples(ens->host, ens->dev, ens->pair_classes, fp64, X, M, ldx, leaf, nullptr, out, s);
+    ts.done();
+    return;
+  }
   double* acc = fp64 ? static_cast<double*>(out) : (double*)scratch;
   launch_fill_zero(acc, MK * T3, s);
-  for (const PairClass& pc : ens->pair_classes)
-    launch_triples(ens->host, ens->dev, pc, fp64, X, M, ldx, leaf, acc, s);
+  launch_triples(ens->host, ens->dev, ens->pair_classes, fp64, X, M, ldx, leaf, acc, nullptr, s);
   if (!fp64) launch_narrow_f64_f32(acc, MK * T3, static_cast<float*>(out), s);
   ts.done();
 }
@@ -1806,8 +1811,8 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
           float t_paths = 1e30f;
           try {
             t_paths = time_ms(1, [&] {
-              for (const PairClass& pc : ens->pair_classes)
-                launch_triples(h, d, pc, fp64, X, m3, F, d.leaf_val, (double*)a3.p, s);
+              launch_triples(h, d, ens->pair_classes, fp64, X, m3, F, d.leaf_val, (double*)a3.p,
+                             nullptr, s);
             });
           } catch (const Error&) {
             // the path form's kernels do not fit this feature count

@@ -157,3 +157,27 @@ def test_triples_chains_of_64(q, oracle_mod):
         assert e.info["max_unique"] == 64
         err = check(got, want, precision, "chains of 64")
         print("chains of 64 triples %s: %.2e" % (precision, err), flush=True)
+
+
+@pytest.mark.parametrize("T,F,M", [
+    (6, 9, 515),    # one workgroup per sample, which writes its tensor itself
+    (6, 62, 513),   # the same in two ranges of the tensor
+    (80, 9, 7),     # several workgroups per sample, added into zeroed output
+    (40, 9, 511),   # two per sample, just below the line
+])
+def test_triples_short_rows_by_sample_count(q, oracle_mod, T, F, M):
+    """Rows of both lane-per-row classes in one launch, either side of the
+    sample count from which a workgroup takes all rows of its sample.  The
+    output is filled with NaN first."""
+    wl = synth.make_workload("c4_adjoint", T=T, F=F, M=M, n_train=20000)
+    rows = [0, 1, M // 2, M - 1]
+    want = packed(oracle_mod.shap_sii3(wl.ensemble, wl.X[rows], n=8))
+    e = q.Ensemble(wl.ensemble)
+    Xd = torch.from_numpy(np.ascontiguousarray(wl.X)).cuda()
+    for precision, dt in (("fp32", torch.float32), ("fp64", torch.float64)):
+        print("case", T, F, M, precision, flush=True)
+        out = torch.full((M, want.shape[1]), float("nan"), dtype=dt, device="cuda")
+        e.shap_interactions3(Xd, precision, out=out)
+        got = out.double().cpu().numpy()
+        assert np.isfinite(got).all()
+        check(got[rows], want, precision, "%d rows" % M)
