@@ -1745,7 +1745,7 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
           float best_ms = 1e30f;
           for (int max_chunk : {8192, 32768, 131072})
             for (int fill : {1024, 4096}) {
-              const PairShape cand{max_chunk, fill};
+              const PairShape cand{max_chunk, fill, true};
               const float ms = time_ms(1, [&] {
                 launch_pairs(h, d, pc, fp64, X, Mp, F, d.leaf_val, tri64, phi64, cand,
                              ens->node_policy == QTS_NODES_EXACT, s);
@@ -1757,6 +1757,7 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
             }
           tune_cache_put(key, best.max_chunk, best.fill);
         }
+        best.tuned = true;
         out[i] = best;
       }
       // QTS_PAIRS_AUTO: time a whole interactions pass both ways on the same

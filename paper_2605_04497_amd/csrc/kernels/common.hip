@@ -41,14 +41,18 @@ FnLimits fn_limits(const void* fn) {
 
 size_t raise_lds_limit(const void* fn) { return fn_limits(fn).lds; }
 
-int resident_waves(const void* fn, size_t lds) {
+int resident_groups(const void* fn, int threads, size_t lds) {
   constexpr int kSimds = 4, kVgprs = 512, kMostWaves = 8;
   const int regs = std::max(8, (fn_limits(fn).vgprs + 7) / 8 * 8);
   const int per_cu = kSimds * std::min(kMostWaves, kVgprs / regs);
   const int by_lds = (int)std::max<size_t>(1, kMaxLdsBytes / std::max<size_t>(lds, 1024));
+  return std::min(by_lds, std::max(1, per_cu / std::max(1, threads / 64)));
+}
+
+int resident_waves(const void* fn, size_t lds) {
   int best = 8, most = 0;
   for (int w : {8, 6, 4}) {
-    const int n = std::min(by_lds, std::max(1, per_cu / w)) * w;
+    const int n = resident_groups(fn, 64 * w, lds) * w;
     if (n > most) {
       most = n;
       best = w;

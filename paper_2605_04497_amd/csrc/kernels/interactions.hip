@@ -1102,18 +1102,40 @@ std::vector<std::pair<int, int>> row_ranges(int F, size_t budget) {
   return out;
 }
 
-int pair_chunk(int np, int64_t M, const PairShape& shape, int64_t* n_chunks_out) {
-  // chunks of at most max_chunk paths, and at least `fill` work items when
-  // there are few samples (chunks of no fewer than 1024 paths)
+// Paths per (sample, chunk) work item of np paths, `step` of them taken at a
+// time by a workgroup: at most max_chunk, and `fill` work items or fewer when
+// there are few samples.  A timed shape says how many; otherwise the count
+// with the shortest run, in rounds of the workgroups that fit on the chip,
+// each of them as long as its paths and its tensor range, which it zeroes and
+// passes on with global atomics (32768 entries: about the time of one pass of
+// the eight-slot class).
+// 100 trees of depth 3 to 20, 200 features (159 KB, one workgroup per CU),
+// 512 samples, FP32: 3.23 ms with four chunks per sample in each class, 3.05
+// with two, 2.89 with the one chosen here (two rounds of 256 workgroups).
+int pair_chunk(int np, int64_t M, const PairShape& shape, const void* fn, int threads, int step,
+               size_t lds, int64_t* n_chunks_out) {
   const int64_t max_chunk = std::max(1024, shape.max_chunk);
-  int64_t n_chunks = (np + max_chunk - 1) / max_chunk;
+  const int64_t least = std::max<int64_t>(1, (np + max_chunk - 1) / max_chunk);
   const int64_t fill = (std::max(1, shape.fill) + M - 1) / M;
-  n_chunks = std::max<int64_t>(n_chunks, std::min<int64_t>(fill, (np + 1023) / 1024));
-  n_chunks = std::max<int64_t>(1, n_chunks);
+  const int64_t most = std::max(least, std::min<int64_t>(fill, (np + 1023) / 1024));
+  int64_t n_chunks = most;
+  if (!shape.tuned) {
+    constexpr int64_t kCus = 256;
+    const int64_t slots = kCus * resident_groups(fn, threads, lds);
+    const int64_t range = (int64_t)(lds / sizeof(double)) / 512;  // in 64ths of a pass
+    int64_t best = INT64_MAX;
+    for (int64_t n = least; n <= most; ++n) {
+      const int64_t passes = ((np + n - 1) / n + step - 1) / step;
+      const int64_t cost = ((M * n + slots - 1) / slots) * (passes * 64 + range);
+      if (cost < best) {
+        best = cost;
+        n_chunks = n;
+      }
+    }
+  }
   *n_chunks_out = n_chunks;
   return (int)((np + n_chunks - 1) / n_chunks);
 }
-
 
 template <typename T>
 const T* table_b(const DeviceTable& d) {
@@ -1136,10 +1158,6 @@ void launch_pairs_fast(const HostTable& h, const DeviceTable& d, const PairClass
                        const float* X, int64_t M, int64_t ldx, const double* leaf_val,
                        double* tri64, double* phi64, const PairShape& shape, hipStream_t s) {
   const int F = h.F;
-  int64_t n_chunks = 1;
-  const int chunk = pair_chunk(pc.np, M, shape, &n_chunks);
-  const int64_t grid = M * n_chunks;
-  if (grid > 0x7fffffff) fail(QTS_E_UNSUPPORTED, "interactions grid too large");
   const void* fn = (const void*)pairs_kernel<T, C, NH, MERGE, NN, LS>;
   const size_t limit = raise_lds_limit(fn);
   const size_t fixed = pairs_fixed_lds(F, sizeof(T), false);
@@ -1147,6 +1165,10 @@ void launch_pairs_fast(const HostTable& h, const DeviceTable& d, const PairClass
   bool first = true;
   for (const auto& rg : row_ranges(F, limit - fixed)) {
     const size_t lds = fixed + (size_t)(tri_row_h(rg.second) - tri_row_h(rg.first)) * 8;
+    int64_t n_chunks = 1;
+    const int chunk = pair_chunk(pc.np, M, shape, fn, 512, 512 / LS, lds, &n_chunks);
+    const int64_t grid = M * n_chunks;
+    if (grid > 0x7fffffff) fail(QTS_E_UNSUPPORTED, "interactions grid too large");
     hipLaunchKernelGGL((pairs_kernel<T, C, NH, MERGE, NN, LS>), dim3((unsigned)grid), dim3(512), lds, s,
                        d.pr_d + pc.pbase, d.pr_leaf + pc.pbase, d.pr_side + pc.pbase,
                        d.pr_feat + pc.base,
@@ -1164,10 +1186,6 @@ void launch_pairs_generic(const HostTable& h, const DeviceTable& d, const PairCl
                           const float* X, int64_t M, int64_t ldx, const double* leaf_val,
                           double* tri64, double* phi64, const PairShape& shape, hipStream_t s) {
   const int F = h.F;
-  int64_t n_chunks = 1;
-  const int chunk = pair_chunk(pc.np, M, shape, &n_chunks);
-  const int64_t grid = M * n_chunks;
-  if (grid > 0x7fffffff) fail(QTS_E_UNSUPPORTED, "interactions grid too large");
   const void* fn = (const void*)pairs_generic_kernel<T>;
   const size_t limit = raise_lds_limit(fn);
   const size_t fixed = pairs_fixed_lds(F, sizeof(T), true);
@@ -1175,6 +1193,11 @@ void launch_pairs_generic(const HostTable& h, const DeviceTable& d, const PairCl
   bool first = true;
   for (const auto& rg : row_ranges(F, limit - fixed)) {
     const size_t lds = fixed + (size_t)(tri_row_h(rg.second) - tri_row_h(rg.first)) * 8;
+    int64_t n_chunks = 1;
+    const int chunk = pair_chunk(pc.np, M, shape, fn, kGenericThreads,
+                                 kGenericThreads / 64, lds, &n_chunks);
+    const int64_t grid = M * n_chunks;
+    if (grid > 0x7fffffff) fail(QTS_E_UNSUPPORTED, "interactions grid too large");
     hipLaunchKernelGGL((pairs_generic_kernel<T>), dim3((unsigned)grid), dim3(kGenericThreads),
                        lds, s, d.pr_d + pc.pbase, d.pr_leaf + pc.pbase, d.pr_feat + pc.base,
                        d.pr_lo + pc.base, d.pr_hi + pc.base, table_b<T>(d) + pc.base,

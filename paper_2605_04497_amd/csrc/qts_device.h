@@ -266,6 +266,7 @@ std::vector<BucketSpan> bucket_spans(const std::vector<Bucket>& bks, bool one_ea
 struct PairShape {
   int max_chunk = 65536;  // most paths per (sample, chunk) work item
   int fill = 2048;        // least work items when there are few samples
+  bool tuned = false;     // timed on this ensemble
 };
 
 inline size_t values_lds_bytes(int F) {
@@ -398,6 +399,8 @@ size_t raise_lds_limit(const void* fn);
 // resident on a CU, given its VGPRs and `lds` bytes per workgroup; the larger
 // workgroup on a tie (it stages its tiles for more wavefronts).
 int resident_waves(const void* fn, size_t lds);
+// Workgroups of fn resident on a CU.
+int resident_groups(const void* fn, int threads, size_t lds);
 
 void launch_fill_zero(double* p, int64_t n, hipStream_t s);
 // Seeded uniform values in [-3, 3) (inputs for timing launch shapes).
