@@ -274,7 +274,7 @@ pairs_kernel(const int32_t* __restrict__ pd, const int32_t* __restrict__ pleaf,
       bv[j] = bb[e];
       cbv[j] = cbb[e];
     }
-    // MERGE: the class may hold merged rows (capacity <= kPairMergeMax)
+    // MERGE: the class may hold merged rows (at most kPairMergeMax features)
     SidePath sp{};
     if (MERGE) sp = pside[pc];
     const bool merged = MERGE && valid && sp.leaf_b >= 0;
@@ -503,15 +503,7 @@ pairs_kernel(const int32_t* __restrict__ pd, const int32_t* __restrict__ pleaf,
                   if (kb + u < C && inr[k]) lds_add(&tris[rb[k] + fi], (double)pr[u]);
                 }
               } else {
-                int idx[4];
-                bool ok[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                  const int k = kb + u < C ? kb + u : 1;
-                  idx[u] = rb[k] + fi;
-                  ok[u] = kb + u < C && inr[k];
-                }
-                group_add<LS>(tris, pr, idx, ok, q);
+                group_add_own<LS, C>(tris, pr, rbs, kb, fi, q);
               }
             }
           }
@@ -1328,24 +1320,29 @@ void launch_pairs(const HostTable& h, const DeviceTable& d, const PairClass& pc,
       default: return launch_pairs_fast<double, 12, 3, true, 6>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
     }
   }
-  // register-resident instances exist where they do not spill.  Up to FP32
-  // C = 20 and FP64 C = 8 a lane holds all eight nodes.  FP64 C = 12 and 16
-  // take two node passes (one pass on two lanes measured slower: the FP64
-  // selects and swaps cost more VALU time than the atomics they save), FP64
-  // C = 20 two lanes and two passes (half the atomics of four passes on one
-  // lane).  Longer classes take two or four lanes per path, which beats the
-  // wave-per-path generic kernel; the longest (FP32 64, FP64 36 and up, which
-  // would spill) run the generic kernel
+  // Up to FP32 C = 20 and FP64 C = 8 a lane holds all eight nodes.  FP64
+  // C = 12 and 16 take two node passes (one pass on two lanes measured slower:
+  // the FP64 selects and swaps cost more VALU time than the atomics they
+  // save), FP64 C = 20 two lanes and two passes (half the atomics of four
+  // passes on one lane).  Longer classes take two or four lanes per path,
+  // which beats the wave-per-path generic kernel; the longest (FP32 64, FP64
+  // 36 and up, which would spill) run the generic kernel.
+  // Up to 32 slots the rows are merged sibling pairs (kPairMergeMax): half the
+  // atomics, which bound these classes.  100 trees of depth 3 to 20, 200
+  // features: 512 samples FP32 2.89 -> 2.32 ms against merging up to 16
+  // (C = 20 spills 44 bytes; on two lanes, without: 2.40), 128 samples FP64
+  // 1.64 -> 1.22 ms (C = 20 on four lanes: 1.30).  100 trees of depth 32, 64
+  // features, 301 samples FP32: 4.3 -> 2.86 ms (C = 28 on four lanes: 2.99).
   if (!fp64) {
     switch (pc.cap) {
       case 4: return launch_pairs_fast<float, 4, 8, true>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
       case 8: return launch_pairs_fast<float, 8, 8, true>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
       case 12: return launch_pairs_fast<float, 12, 8, true>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
       case 16: return launch_pairs_fast<float, 16, 8, true>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
-      case 20: return launch_pairs_fast<float, 20, 8, false>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
-      case 24: return launch_pairs_fast<float, 24, 4, false, 8, 2>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
-      case 28: return launch_pairs_fast<float, 28, 4, false, 8, 2>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
-      case 32: return launch_pairs_fast<float, 32, 2, false, 8, 4>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
+      case 20: return launch_pairs_fast<float, 20, 8, true>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
+      case 24: return launch_pairs_fast<float, 24, 4, true, 8, 2>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
+      case 28: return launch_pairs_fast<float, 28, 4, true, 8, 2>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
+      case 32: return launch_pairs_fast<float, 32, 2, true, 8, 4>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
       case 36: return launch_pairs_fast<float, 36, 2, false, 8, 4>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
       case 40: return launch_pairs_fast<float, 40, 2, false, 8, 4>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
       case 48: return launch_pairs_fast<float, 48, 2, false, 8, 4>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
@@ -1357,10 +1354,10 @@ void launch_pairs(const HostTable& h, const DeviceTable& d, const PairClass& pc,
     case 8: return launch_pairs_fast<double, 8, 8, true>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
     case 12: return launch_pairs_fast<double, 12, 4, true>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
     case 16: return launch_pairs_fast<double, 16, 4, true>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
-    case 20: return launch_pairs_fast<double, 20, 2, false, 8, 2>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
-    case 24: return launch_pairs_fast<double, 24, 2, false, 8, 4>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
-    case 28: return launch_pairs_fast<double, 28, 2, false, 8, 4>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
-    case 32: return launch_pairs_fast<double, 32, 2, false, 8, 4>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
+    case 20: return launch_pairs_fast<double, 20, 2, true, 8, 2>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
+    case 24: return launch_pairs_fast<double, 24, 2, true, 8, 4>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
+    case 28: return launch_pairs_fast<double, 28, 2, true, 8, 4>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
+    case 32: return launch_pairs_fast<double, 32, 2, true, 8, 4>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
     default: return launch_pairs_generic<double>(h, d, pc, X, M, ldx, lv, tri64, phi64, sh, s);
   }
 }

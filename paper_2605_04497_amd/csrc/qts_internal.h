@@ -139,7 +139,7 @@ HostTable build_host_table(const qts_tree_arrays& t, int32_t n_features, int32_t
 // slot 0); the remaining slots are sorted by feature (a single path: all of
 // them).  Slots past a row's end are inert (feature 0, no bounds,
 // missing_ok, b = 1, 1-b = 0).
-constexpr int kPairMergeMax = 16;
+constexpr int kPairMergeMax = 32;  // the longest instances that take them
 struct PairClass {
   int32_t cap;    // slots per path
   int32_t np;     // paths in the class

@@ -239,3 +239,22 @@ def test_every_class_with_many_rows(q, oracle_mod):
         assert e.info["max_unique"] == 64
         check(Phi, Phi_o, precision, "chains Phi")
         check(phi, phi_o, precision, "chains phi")
+
+
+@pytest.mark.parametrize("D", [17, 20, 21, 24, 25, 28, 29, 32, 33])
+def test_long_merged_rows(q, oracle_mod, D):
+    """70 chains of D features, so the merged sibling pair at the end of every
+    chain makes more than one wave of merged rows of D features (33: the
+    shortest that stay two rows), on one and two triangle ranges."""
+    rng = np.random.default_rng(900 + D)
+    F = 40 if D % 2 else 210
+    ens = _random_chains(rng, 70, F, D)
+    X = rng.standard_normal((5, F)).astype(np.float32) * 0.6
+    X[1, ::7] = np.nan
+    phi_o, Phi_o = oracle_mod.shap_interactions(ens, X, n=8)
+    for precision in ("fp32", "fp64"):
+        print("case", D, precision, flush=True)
+        Phi, phi, e = _run(q, ens, X, precision)
+        assert (e.info["n_pair_rows"] < e.info["n_paths"]) == (D <= 32)
+        check(Phi, Phi_o, precision, "%d merged Phi" % D)
+        check(phi, phi_o, precision, "%d merged phi" % D)
