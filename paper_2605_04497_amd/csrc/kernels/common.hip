@@ -51,7 +51,7 @@ int resident_groups(const void* fn, int threads, size_t lds) {
 
 int resident_waves(const void* fn, size_t lds) {
   int best = 8, most = 0;
-  for (int w : {8, 6, 4}) {
+  for (int w : {8, 4}) {
     const int n = resident_groups(fn, 64 * w, lds) * w;
     if (n > most) {
       most = n;

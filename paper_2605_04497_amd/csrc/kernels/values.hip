@@ -1814,18 +1814,10 @@ namespace {
 // Paths per work item: about 32 rounds of the ~512 resident workgroups
 // (small tail), chunks of at least 256 paths so the per-item tile load and
 // flush stay small next to the path work.
-// A launch that would leave the chip idle (under 4 workgroups per CU) takes
-// chunks of down to 32 rows instead: its time is a wavefront's walk through
-// its rows one after another (95 ragged trees of depth up to 30, 37 rows: 283
-// -> 70 us a call).
-int values_chunk(int n_paths, int nsb, int items, bool fill = true) {
+int values_chunk(int n_paths, int nsb, int items) {
   const int64_t want_items = items > 0 ? items : 16384;
   int64_t n_chunks = (want_items + nsb - 1) / nsb;
   n_chunks = std::max<int64_t>(1, std::min<int64_t>(n_chunks, (n_paths + 255) / 256));
-  constexpr int64_t kFill = 1024;
-  if (fill && n_chunks > 1 && n_chunks * nsb < kFill)
-    n_chunks = std::max(n_chunks,
-                        std::min<int64_t>((kFill + nsb - 1) / nsb, (n_paths + 31) / 32));
   return (int)((n_paths + n_chunks - 1) / n_chunks);
 }
 
@@ -1890,10 +1882,10 @@ BucketIndex bucket_index(const PathArrays& a, const BucketSpan& sp) {
 }
 
 RowSplit row_split(const HostTable& h, const PathArrays& a, const BucketSpan& sp, int nsb,
-                   const ValuesShape& shape, bool fill = true) {
+                   const ValuesShape& shape) {
   RowSplit r{a.feat, nullptr, 0, 0, h.F};
   if (a.compact == nullptr) {
-    r.chunk = values_chunk(sp.path_end() - sp.path_begin(), nsb, shape.items, fill);
+    r.chunk = values_chunk(sp.path_end() - sp.path_begin(), nsb, shape.items);
     r.n_chunks = n_chunks_of(sp, r.chunk);
     return r;
   }
@@ -1931,24 +1923,67 @@ WalkPtrs<T> walk_of(const PathArrays& a, const BucketSpan& sp) {
   return {w.rows + bk.srow_begin, w.coef + (int64_t)bk.srow_begin * kShortCoef};
 }
 
+// The first-order kernel's chunk where no timed shape says it: the split with
+// the shortest run, in rounds of the workgroups that fit on the chip.  A CU's
+// round is, for each of its workgroups, the chunk's rows (170 clocks for a row
+// of up to 8 features over 64 samples in FP32, by feature beyond them, 2.5
+// times that in FP64) and the tile, staged and passed on with FP64 atomics at
+// 270 clocks a feature over 64 samples.  Chunks of 32 rows or more.  Past
+// four rounds a gain of less than a fifth is inside the model's error: then
+// the chunks stay (20000 rows, 200 trees of depth 6, values and adjoint: 1.16
+// ms, 1.19 without this).
+// us a call with chunks of at least 256 rows, with chunks of 32 rows up to
+// 1024 workgroups, and here: 1770 rows, 940 trees of depth 4, 188 features:
+// 165, 178, 103; 606 rows, 938 of depth 3, 114 features: 36, 66, 32; 5537
+// rows, 28 of depth 5, 9 features: 55, 25, 23; 4934 rows, 336 of depth 7, 65
+// features: 488, 488, 440.
+int chunk_by_rounds(const BucketSpan& sp, int nsb, int F, bool fp64, int groups, int chunk0) {
+  const int64_t rows = sp.path_end() - sp.path_begin();
+  const int64_t slots = (int64_t)256 * groups;
+  const int64_t row = (int64_t)170 * std::max(8, sp.dmax()) / 8 * (fp64 ? 5 : 2) / 2;
+  const int64_t tile = (int64_t)270 * F;
+  int64_t best = INT64_MAX;
+  int out = chunk0;
+  auto look = [&](int64_t chunk) {
+    const int64_t items = (int64_t)nsb * n_chunks_of(sp, (int)chunk);
+    const int64_t cost = ((items + slots - 1) / slots) * (chunk * row + tile);
+    if (cost < best) {
+      best = cost;
+      out = (int)chunk;
+    }
+  };
+  look(chunk0);
+  if ((int64_t)nsb * n_chunks_of(sp, chunk0) > 4 * slots) best -= best / 5;
+  for (int64_t k : {1, 2, 3, 4, 6, 8, 12, 16}) {
+    const int64_t n = k * slots / nsb - (sp.n > 1 ? sp.n / 2 : 0);
+    if (n >= 1) look(std::min(rows, std::max<int64_t>(32, (rows + n - 1) / n)));
+  }
+  return out;
+}
+
 template <typename T, int DMAX, int NH, bool STORE_G, int NN, int WALK = kPerRow>
 void launch_one(const HostTable& h, const DeviceTable& d, const PathArrays& a,
                 const BucketSpan& sp, const float* X, int64_t M, int64_t ldx, const void* slot0, double* acc,
                 void* direct, const ValuesShape& shape, hipStream_t s, bool det) {
   const int F = h.F;
   const int nsb = (int)((M + kSamplesPerBlock - 1) / kSamplesPerBlock);
-  // (deterministic: a chunk is a launch)
-  const RowSplit rs = row_split(h, a, sp, nsb, shape, !det);
+  RowSplit rs = row_split(h, a, sp, nsb, shape);
   const BucketIndex bx = bucket_index(a, sp);
   const int32_t row0 = sp.path_begin(), row1 = sp.path_end();
-  const int64_t grid = (int64_t)nsb * rs.n_chunks;
-  if (grid > 0x7fffffff) fail(QTS_E_UNSUPPORTED, "grid too large");
   const size_t lds = values_lds_bytes(rs.tile_f);
   // deterministic: one wave per workgroup (no LDS atomics between waves), and
   // one launch per chunk, so each launch has one workgroup per (sample, feature)
   const void* fn = (const void*)values_kernel<T, DMAX, NH, STORE_G, NN, WALK>;
   const int threads =
       det ? 64 : 64 * (shape.tuned ? shape.waves_per_block : resident_waves(fn, lds));
+  // (deterministic: a chunk is a launch; direct: one chunk has all rows)
+  if (!det && !shape.tuned && rs.segs == nullptr && direct == nullptr) {
+    rs.chunk = chunk_by_rounds(sp, nsb, F, std::is_same<T, double>::value,
+                               resident_groups(fn, threads, lds), rs.chunk);
+    rs.n_chunks = n_chunks_of(sp, rs.chunk);
+  }
+  const int64_t grid = (int64_t)nsb * rs.n_chunks;
+  if (grid > 0x7fffffff) fail(QTS_E_UNSUPPORTED, "grid too large");
   const T* b = std::is_same<T, float>::value ? (const T*)a.b32 : (const T*)a.b64;
   const T* cb = std::is_same<T, float>::value ? (const T*)a.cb32 : (const T*)a.cb64;
   NodeConsts<T> nc;
@@ -2000,6 +2035,15 @@ void launch_adj_one(const HostTable& h, const DeviceTable& d, const PathArrays& 
   const int F = h.F;
   const int nsb = (int)((M + kSamplesPerBlock - 1) / kSamplesPerBlock);
   RowSplit rs = row_split(h, a, sp, nsb, shape);
+  // a launch that would leave the chip idle (under 4 workgroups per CU) takes
+  // chunks of down to 32 rows: its time is a wavefront's walk through its rows
+  // one after another
+  constexpr int kFill = 1024;
+  if (rs.segs == nullptr && nsb * rs.n_chunks < kFill) {
+    const int rows = sp.path_end() - sp.path_begin(), n = (kFill + nsb - 1) / nsb;
+    rs.chunk = std::min(rs.chunk, std::max(32, (rows + n - 1) / n));
+    rs.n_chunks = n_chunks_of(sp, rs.chunk);
+  }
   const void* fn = (const void*)adjoint_kernel<T, DMAX, NH, STORE_G, NN, TOP>;
   const size_t limit = raise_lds_limit(fn);
   const size_t tile = (size_t)rs.tile_f * kTileStride;

@@ -95,3 +95,26 @@ def test_few_samples_match_oracle(q, oracle_mod, F, K, M, precision):
         got = e.shap_values(Xd, precision, leaf_values=lv).double().cpu().numpy()
         check(got.reshape(M, -1), want, precision, "leaf override %s" % (leaf is not None))
     e.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("T,F,K,M", [
+    (3, 9, 1, 70),      # one chunk
+    (9, 12, 1, 65),     # chunks of 32 rows
+    (60, 190, 1, 130),  # one workgroup per CU
+    (61, 9, 7, 1100),   # outputs of unequal row counts in one launch
+    (40, 60, 1, 3000),  # several rounds
+])
+def test_row_chunks_match_oracle(q, oracle_mod, T, F, K, M, precision):
+    """Splits of the rows between workgroups, from a single chunk to several
+    rounds of them, with a ragged last chunk."""
+    print("case", T, F, K, M, precision, flush=True)
+    over = dict(groups=K) if K > 1 else {}
+    wl = synth.make_workload("c2_values", T=T, M=M, n_train=4000, F=F, **over)
+    e = q.Ensemble(wl.ensemble)
+    rows = np.unique(np.r_[0:4, M // 2, M - 3:M])
+    values = oracle_mod.shap_values_grouped if K > 1 else oracle_mod.shap_values
+    want = values(wl.ensemble, wl.X[rows], n=8).reshape(len(rows), -1)
+    got = e.shap_values(torch.from_numpy(wl.X).cuda(), precision).double().cpu().numpy()
+    check(got.reshape(M, -1)[rows], want, precision, "row chunks")
+    e.close()
