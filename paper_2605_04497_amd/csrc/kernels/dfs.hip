@@ -639,8 +639,11 @@ template <typename T>
 void pairs_t(const HostTable& h, const DeviceDfs& d, const NodeConsts<T>& nc, const float* X,
              int64_t s0, int32_t mb, int64_t ldx, const T* Y, double* tri64, double* phi64,
              int32_t tiles_per_chunk, hipStream_t s) {
-  const int chunk = std::max(1, tiles_per_chunk);
-  const int64_t n_chunks = std::max<int64_t>(1, d.n_rows / 64 / chunk);
+  // few samples: chunks down to a tile per wavefront, up to 512 workgroups
+  const int64_t n_tiles = d.n_rows / 64;
+  const int chunk = (int)std::max<int64_t>(
+      1, std::min<int64_t>(tiles_per_chunk, std::max<int64_t>(16, n_tiles * mb / 512)));
+  const int64_t n_chunks = std::max<int64_t>(1, n_tiles / chunk);
   auto fits = [&](int S) {
     return dfs_pairs_lds(h.F, tri_h(h.F), S) <= (size_t)kMaxLdsBytes &&
            (mb + S - 1) / S * n_chunks >= 512;
