@@ -795,6 +795,14 @@ bool use_dfs3(const qts_ensemble* ens, bool fp64) {
 // sample and internal node) fit this much scratch.
 constexpr size_t kDfsScratchBytes = (size_t)4 << 30;
 
+// Whether the depth-first forms take the ensemble: one wavefront's FP64 walk
+// with two values per level fits in LDS (the walk itself keeps one).
+bool dfs_fits(const HostTable& h) {
+  const size_t level = 64 * sizeof(double);
+  return dfs_walk_lds_bytes(h.F, h.max_depth, true) + (size_t)(h.max_depth + 1) * level <=
+         (size_t)kMaxLdsBytes;
+}
+
 int32_t dfs_batch(const qts_ensemble* ens, int64_t M, bool fp64) {
   const size_t per = (size_t)ens->dfs.n_rows * kNodes * (fp64 ? sizeof(double) : sizeof(float));
   int64_t mb = per == 0 ? M : (int64_t)(kDfsScratchBytes / per);
@@ -1564,7 +1572,7 @@ int qts_set_pair_traversal(qts_ensemble* ens, int32_t traversal) {
     std::lock_guard<std::mutex> lock(ens->graphs.mu);
     if (traversal != QTS_PAIRS_PATHS) {
       require_device(ens);
-      if (dfs_walk_lds_bytes(ens->host.F, ens->host.max_depth, true) > (size_t)kMaxLdsBytes)
+      if (!dfs_fits(ens->host))
         fail(QTS_E_UNSUPPORTED, "the depth-first walk's stacks do not fit in LDS");
       build_dfs(ens);
     }
@@ -1764,8 +1772,7 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
       // rows (at most one depth-first batch) and keep the faster form
       // (the depth-first tables are built here on first use, where its walk
       // fits in LDS; otherwise the path form stays)
-      if (ens->pair_traversal == QTS_PAIRS_AUTO && !ens->dfs.built &&
-          dfs_walk_lds_bytes((int)F, h.max_depth, true) <= (size_t)kMaxLdsBytes)
+      if (ens->pair_traversal == QTS_PAIRS_AUTO && !ens->dfs.built && dfs_fits(h))
         build_dfs(ens);
       if (ens->pair_traversal == QTS_PAIRS_AUTO && ens->dfs.built) {
         const std::string key = tune_key(device, "traversal", fp64, pol, h, 0, 0,
