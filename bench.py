@@ -206,23 +206,10 @@ def pmc_summary(paths):
                 kn, len(d["dispatches"]), ms,
                 "  ".join("%s=%.4e" % kv for kv in sorted(d["counters"].items()))))
             if kn not in TUNER_KERNELS:
-                flops[0] += 64.0 * d["counters"].get("SQ_INSTS_VALU_FLOPS_FP32", 0.0)
+                flops[0] += (64.0 * d["counters"].get("SQ_INSTS_VALU_FLOPS_FP32", 0.0) +
+                             512.0 * d["counters"].get("SQ_INSTS_VALU_MFMA_MOPS_F32", 0.0))
                 flops[1] += 64.0 * d["counters"].get("SQ_INSTS_VALU_FLOPS_FP64", 0.0)
         print("executed flops (x64, tuner kernels excluded): fp32 %.4e fp64 %.4e" % tuple(flops))
-
-
-def shared_kernel_flops(rows, elements, shared, kept):
-    """FP32 flops (FMA = 2) per sample of the first-order kernel for rows of at
-    most 8 features at 8 nodes: a row of d features whose first s slots after
-    slot 0 are reused from the previous row costs
-      16 (8 - s)          factor FMAs of the slots it evaluates (padding included)
-      8 (6 - min(s, 6))   prefix products over slots 1..6 not kept from the
-                          previous row
-      16 d                a 15-flop node sum and a scale per feature
-      48                  suffix products over slots 7..2
-    = 224 + 16 d - 16 s - 8 min(s, 6); summed over the table:
-    224 R + 16 E - 16 S - 8 K (K: min(s, 6) summed, qts_info's prefix_kept)."""
-    return 224.0 * rows + 16.0 * elements - 16.0 * shared - 8.0 * kept
 
 
 def pair_flops(d):
@@ -916,11 +903,7 @@ def main():
                         1, torch)
         e.set_sibling_merge(True)
         plain = {"value": units / (rp["ms_per_step"] * 1e-3), "ms_per_step": rp["ms_per_step"],
-                 "kernel_ms": rp["kernel_ms"], "dtype": "f32",
-                 "alu_tflops": float(M) * shared_kernel_flops(
-                     float(e.info["n_paths"]), n_el, float(e.info["n_path_shared"]),
-                     float(e.info["n_path_prefix_kept"]))
-                 / (rp["kernel_ms"] * 1e-3) / 1e12}
+                 "kernel_ms": rp["kernel_ms"], "dtype": "f32"}
         log("fp32 without sibling merging: %.3f ms/step" % rp["ms_per_step"])
     exact = None
     if not args.no_extras:
@@ -938,16 +921,12 @@ def main():
                  "note": "4-node rule for paths of at most 8 unique features (all of this "
                          "workload): exact for first order, same values up to rounding"}
         log("fp32 with the exact node policy: %.3f ms/step" % rx["ms_per_step"])
-    # the arithmetic the kernel runs (every row of this workload has at most 8
-    # features: one bucket, the shared-prefix walk); flops above is the
-    # per-element count of the method without merging or reuse
-    n_shared = float(e.info["n_value_shared"] if not args.no_merge else e.info["n_path_shared"])
-    n_kept = float(e.info["n_value_prefix_kept"] if not args.no_merge
-                   else e.info["n_path_prefix_kept"])
-    n_rows = float(e.info["n_value_paths"] if not args.no_merge else e.info["n_paths"])
-    assert e.info["max_unique"] <= 8
-    kernel_flops = float(M) * shared_kernel_flops(n_rows, n_vel, n_shared, n_kept)
-    achieved = kernel_flops / (r32["kernel_ms"] * 1e-3) / 1e12
+    # the flops the call executes, from its counters (flops above is the
+    # per-element count of the method without merging or sharing)
+    ex = executed("values", "fp32", r32["kernel_ms"] * 1e-3)
+    if args.no_merge or M != 100000:
+        ex = None
+    achieved = ex["executed_tflops"] if ex else None
     result = {
         "metric": METRIC,
         "value": units / (r32["ms_per_step"] * 1e-3),
@@ -988,27 +967,24 @@ def main():
                  "kernel_ms": r64["kernel_ms"], "dtype": "f64",
                  "speedup_fp32_over_fp64": r64["ms_per_step"] / r32["ms_per_step"]},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS,
-                     "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_TFLOPS,
+                     "unit": "TFLOP/s",
+                     "frac": achieved / PEAK_FP32_TFLOPS if achieved else None,
                      "traffic": measured_traffic(e.launch_shape("values", "fp32", 0)),
                      "traffic_unit": "bytes per launch (HBM, rocprofv3 FETCH_SIZE x2 + WRITE_SIZE)",
-                     "flops_per_launch": kernel_flops,
-                     "flops_model": "executed FP32 flops per (sample, row) of d features with s "
-                                    "reused slots: 224 + 16 d - 16 s - 8 min(s, 6) (8 nodes, "
-                                    "FMA = 2 flops); matches SQ_INSTS_VALU_FLOPS_FP32 x 64",
-                     "rows": n_rows, "elements_per_sample": n_vel,
-                     "shared_slots_per_sample": n_shared,
-                     "kept_prefix_levels_per_sample": n_kept,
+                     "flops_per_launch": ex["flops_per_call"] if ex else None,
+                     "flops_source": "vector and matrix flops of one call, from its counters "
+                                     "(null for kernels other than those they were taken on)",
                      "peak_note": "published MI355X FP32 vector peak; plain FP32 FMAs and "
                                   "multiplies on vector-register operands issue at up to 1.71 "
                                   "wave instructions per CU per clock in probes on this GPU "
                                   "(2 at this peak), so it applies without packed instructions",
-                     "kernel": "values_kernel<float, 8, 8, true, 8>", "kernel_ms": r32["kernel_ms"],
+                     "kernel": "values_kernel (grouped walk of rows of at most 8 features)", "kernel_ms": r32["kernel_ms"],
                      "kernel_ms_scope": "event pair around each graph replay (zero-fill, "
                                         "values kernel, cast)" if not args.eager else
                                         "event pair around the values kernel launches",
                      "method_flops_per_launch": flops,
                      "method_flops_note": "51 flops per (sample, element) of the rows walked, "
-                                          "without the slot reuse: a work count, not a "
+                                          "without the sharing: a work count, not a "
                                           "roofline figure"},
     }
     if not args.no_extras:

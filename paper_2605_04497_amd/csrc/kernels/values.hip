@@ -25,14 +25,19 @@
 // The leaf value is folded into slot 0 (Slot0: F_0 scaled by val, built per
 // call in FP64), so a row needs no multiply by val; a merged sibling pair is
 // the same form with a combined slot-0 factor.
-// Rows of at most 8 features reuse the factors and prefix products of the
-// slots they share with the previous row (values_rows_shared,
-// adjoint_rows_shared).  Longer rows (values_rows_long, values_paths) run in
-// batches of eight slots: slots past the end of a row get c = 0 and b = 1, a
-// factor of exactly 1, so whole batches run without
-// branches; the prefix products are kept only at batch checkpoints and
-// rebuilt batch by batch in the backward sweep, which bounds the registers;
-// NH < NN splits the nodes over several passes (the node sum is additive).
+// With the model's own leaf values and 8 nodes the rows are walked by their
+// node products, phi_j = sum_m H(m) c_j / F_j(m) with the quotients from
+// tables, H summed over neighbouring rows that share the slot
+// (values_rows_grouped: up to 8 features; values_rows_batched: longer rows,
+// FP32), and a few samples by a lane per row (values_lane_kernel).  The other
+// calls walk row by row (WALK = kPerRow): rows of at most 8 features reuse the
+// factors and prefix products of the slots they share with the previous row
+// (values_rows_shared, adjoint_rows_shared); longer rows (values_rows_long,
+// values_paths) run in batches of eight slots: slots past the end of a row get
+// c = 0 and b = 1, a factor of exactly 1, so whole batches run without
+// branches; the prefix products are kept only at batch checkpoints and rebuilt
+// batch by batch in the backward sweep, which bounds the registers; NH < NN
+// splits the nodes over several passes (the node sum is additive).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -606,9 +611,9 @@ __device__ __forceinline__ acc_v4 node_sums4(float A, const float (&H)[8], acc_v
 // Bound by VALU issue: compares, selects and address adds read scalar
 // registers (1.3 clocks of a CU per wave instruction), the factor and product
 // FMAs do not (0.65), FP64 takes 1.3, four slots' node sums 19.  500 trees of
-// depth 8, 100 features, 100k rows, FP32: 24.7 ms with suffix products and
-// node sums per slot, 23.1 here; 300 such trees, 5003 rows, FP64: 3.43 and
-// 2.10 ms.
+// depth 8, 100 features, 100k rows, FP32: 24.5 ms with suffix products and
+// node sums per slot, 23.0 here; 300 such trees, 5003 rows, FP64: 3.43 and
+// 2.15 ms.
 template <typename T, int TOP, bool NANS>
 __device__ __forceinline__ void values_rows_grouped(
     const WalkRow<T>* __restrict__ rows, const T* __restrict__ coef, int row0,
@@ -835,7 +840,7 @@ __device__ __forceinline__ void values_rows_grouped(
 // node_sums4.
 // Batches of 8: 99 VGPRs at 32 slots, four waves per SIMD.  Batches of 4
 // evaluate fewer shared slots again but keep twice the state (187 VGPRs, two
-// waves): 100 trees of up to 32 features and 512 leaves, 10k rows, 5.70 ms
+// waves): 100 trees of up to 32 features and 512 leaves, 10k rows, 6.3 ms
 // against 10.6 ms; the suffix products per row and slot that this replaces
 // took 12.2 ms.
 template <int DMAX, bool NANS>
@@ -1697,8 +1702,8 @@ __device__ __forceinline__ void adjoint_rows_grouped(
 // L2).  With the inert slots left out (119 VGPRs instead of 136 at depth 6,
 // four waves per SIMD), four rows' sums folded together over the wave and
 // four wavefronts' worth of registers per SIMD in use, 200 trees of depth 6,
-// 50 features, 20k rows, FP32 take 0.6 ms; 1.6 before.  part_rows = 0: no room for the sums next to the tiles, every row adds
-// to memory.  TOP: the bucket's (capacity 8); FP64 at 8 nodes takes the grouped
+// 50 features, 20k rows, FP32 take 0.6 ms; 1.6 before.  part_rows = 0: no room
+// for the sums next to the tiles, every row adds to memory.  TOP: the bucket's (capacity 8); FP64 at 8 nodes takes the grouped
 // walk with it, the others adjoint_rows_shared with ND = TOP + 3.
 // Three waves per SIMD (168 VGPRs) where the instance is within a few
 // registers of them.
