@@ -1769,7 +1769,8 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
         out[i] = best;
       }
       // QTS_PAIRS_AUTO: time a whole interactions pass both ways on the same
-      // rows (at most one depth-first batch) and keep the faster form
+      // rows (the depth-first form on at most one of its batches) and keep the
+      // form with less time per row
       // (the depth-first tables are built here on first use, where its walk
       // fits in LDS; otherwise the path form stays)
       if (ens->pair_traversal == QTS_PAIRS_AUTO && !ens->dfs.built && dfs_fits(h))
@@ -1786,14 +1787,14 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
                          (fp64 ? sizeof(double) : sizeof(float)), s);
           const float t_paths = time_ms(1, [&] {
             for (size_t i = 0; i < ens->pair_classes.size(); ++i)
-              launch_pairs(h, d, ens->pair_classes[i], fp64, X, md, F, d.leaf_val, tri64, phi64,
+              launch_pairs(h, d, ens->pair_classes[i], fp64, X, Mp, F, d.leaf_val, tri64, phi64,
                            out[i], ens->node_policy == QTS_NODES_EXACT, s);
           });
           const float t_dfs = time_ms(1, [&] {
             launch_dfs_walk(h, ens->dfs, d, fp64, d.leaf_val, X, 0, md, F, y.p, lv.p, s);
             launch_dfs_pairs(h, ens->dfs, d, fp64, X, 0, md, F, y.p, tri64, phi64, 128, s);
           });
-          choice = t_dfs < t_paths ? 1 : 0;
+          choice = t_dfs * (float)Mp < t_paths * (float)md ? 1 : 0;
           tune_cache_put(key, choice, 0);
         }
         ens->dfs_faster[pi] = choice == 1;
