@@ -62,8 +62,8 @@ def measured_traffic(shape):
     return TRAFFIC["fetch_bytes"] + TRAFFIC["write_bytes"]
 FLOPS_PER_ELEMENT = 51  # per (sample, path, unique feature): 8 nodes x 6 + 3
 
-# Executed flops per call of the other legs' kernels: SQ_INSTS_VALU_FLOPS_FP32
-# (or _FP64) x 64 summed over one call's dispatches, from rocprofv3 --pmc runs
+# Executed flops per call of each leg's kernels: SQ_INSTS_VALU_FLOPS_FP32 (or
+# _FP64) x 64 and SQ_INSTS_VALU_MFMA_MOPS_F32 x 512 over one call's dispatches, from rocprofv3 --pmc runs
 # of `bench.py --only <leg>` (profiles/ holds the commands and counts).  Valid
 # only for the kernel sources they were measured on (SHA-256 prefix over the
 # kernel files); otherwise the executed figures are reported as null.
@@ -71,27 +71,27 @@ KERNEL_SOURCES = ("paper_2605_04497_amd/csrc/kernels/values.hip",
                   "paper_2605_04497_amd/csrc/kernels/interactions.hip",
                   "paper_2605_04497_amd/csrc/kernels/dfs.hip",
                   "paper_2605_04497_amd/csrc/kernels/common.hip")
-EXECUTED_FLOPS_SHA = "51c12ee84f59c8f8"
+EXECUTED_FLOPS_SHA = "5421d367ce192d86"
 # (leg, precision) -> (FP32 flops, FP64 flops) per call
 EXECUTED_FLOPS = {
-    ("values", "fp32"): (2.9722e+12, 2.3578e+06),
-    ("values", "fp64"): (1.0722e+08, 4.3635e+12),
-    ("interactions", "fp32"): (2.0298e+12, 3.7527e+09),
-    ("interactions", "fp64"): (1.0476e+08, 3.0189e+12),
-    ("interactions_dfs", "fp32"): (8.7750e+11, 1.3826e+08),
-    ("interactions_dfs", "fp64"): (3.8014e+08, 2.0795e+12),
-    ("adjoint", "fp32"): (3.8300e+10, 1.7949e+09),
-    ("adjoint", "fp64"): (1.2013e+07, 5.8223e+10),
-    ("deep_values", "fp32"): (4.5586e+11, 6.7738e+05),
-    ("deep_values", "fp64"): (3.9215e+07, 5.2106e+11),
-    ("deep_interactions", "fp32"): (2.9683e+12, 3.7794e+08),
-    ("deep_interactions", "fp64"): (1.7664e+08, 3.8937e+12),
-    ("deep_interactions_dfs", "fp32"): (5.6340e+11, 2.0386e+08),
-    ("deep_interactions_dfs", "fp64"): (2.5984e+08, 1.3728e+12),
-    ("deep_third_order", "fp32"): (8.2126e+11, 2.2150e+07),
-    ("deep_third_order", "fp64"): (1.4848e+08, 9.4479e+11),
-    ("deep_third_order_dfs", "fp32"): (1.8750e+11, 3.3869e+05),
-    ("deep_third_order_dfs", "fp64"): (7.5008e+06, 2.3076e+11),
+    ("values", "fp32"): (2.2088e+12, 1.1433e+09),
+    ("values", "fp64"): (3.0889e+08, 2.2295e+12),
+    ("interactions", "fp32"): (1.5295e+12, 5.2878e+09),
+    ("interactions", "fp64"): (1.5499e+07, 2.2244e+12),
+    ("interactions_dfs", "fp32"): (9.6252e+11, 2.4891e+08),
+    ("interactions_dfs", "fp64"): (3.7070e+08, 2.0964e+12),
+    ("adjoint", "fp32"): (2.9985e+10, 4.1160e+08),
+    ("adjoint", "fp64"): (1.6019e+07, 2.4037e+10),
+    ("deep_values", "fp32"): (2.3721e+11, 6.0534e+06),
+    ("deep_values", "fp64"): (4.0501e+07, 5.2066e+11),
+    ("deep_interactions", "fp32"): (1.9467e+12, 5.1808e+09),
+    ("deep_interactions", "fp64"): (8.9600e+07, 2.5530e+12),
+    ("deep_interactions_dfs", "fp32"): (3.8001e+11, 2.5019e+08),
+    ("deep_interactions_dfs", "fp64"): (8.6080e+07, 6.8065e+11),
+    ("deep_third_order", "fp32"): (5.7114e+11, 5.0862e+09),
+    ("deep_third_order", "fp64"): (1.4541e+08, 6.6197e+11),
+    ("deep_third_order_dfs", "fp32"): (1.8750e+11, 5.7147e+06),
+    ("deep_third_order_dfs", "fp64"): (7.5328e+06, 2.3077e+11),
 }
 
 # One call of each leg for the counter runs (`--flop-call LEG:PREC` under
@@ -135,7 +135,8 @@ def executed(leg, precision, seconds):
     peak = PEAK_FP32_TFLOPS if precision == "fp32" else PEAK_FP64_TFLOPS
     return {"executed_tflops": tf, "frac_of_peak": tf / peak, "peak_tflops": peak,
             "flops_per_call": {"fp32": fl[0], "fp64": fl[1]},
-            "source": "SQ_INSTS_VALU_FLOPS_FP32/_FP64 x 64 over one call's dispatches, "
+            "source": "SQ_INSTS_VALU_FLOPS_FP32/_FP64 x 64 and MFMA_MOPS_F32 x 512 over one "
+                      "call's dispatches, "
                       "rocprofv3 --pmc of bench.py --flop-call %s:%s" % (leg, precision)}
 
 
