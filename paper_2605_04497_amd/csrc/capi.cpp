@@ -311,10 +311,8 @@ void short_walk(size_t n, hipStream_t s, ShortWalk& w) {
     }
     return p;
   };
-  w.row32 = (WalkRow<float>*)alloc(n * sizeof(WalkRow<float>));
-  w.row64 = (WalkRow<double>*)alloc(n * sizeof(WalkRow<double>));
-  w.coef32 = (float*)alloc(n * kShortCoef * sizeof(float));
-  w.coef64 = (double*)alloc(n * kShortCoef * sizeof(double));
+  w.rows = (WalkRow*)alloc(n * sizeof(WalkRow));
+  w.coef = (double*)alloc(n * kShortCoef * sizeof(double));
 }
 
 void keep_trees(const qts_tree_arrays& t, qts_ensemble::Trees& k) {
@@ -393,9 +391,8 @@ void free_device(DeviceTable& d) {
                   d.mb64,   d.mcb64,   d.side,    d.pr_side, d.share,   d.mshare,
                   d.lfeat,  d.segs,    d.seg_feat, d.mlfeat, d.msegs,  d.mseg_feat,
                   d.srow32, d.srow64,  d.msrow32, d.msrow64,
-                  d.walk.row32, d.walk.row64, d.walk.coef32, d.walk.coef64,
-                  d.bkt_begin, d.bkt_group, d.mbkt_begin, d.mbkt_group,
-                  d.mwalk.row32, d.mwalk.row64, d.mwalk.coef32, d.mwalk.coef64};
+                  d.walk.rows, d.walk.coef, d.mwalk.rows, d.mwalk.coef,
+                  d.bkt_begin, d.bkt_group, d.mbkt_begin, d.mbkt_group};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   d = DeviceTable{};

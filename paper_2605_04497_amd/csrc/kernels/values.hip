@@ -25,19 +25,20 @@
 // The leaf value is folded into slot 0 (Slot0: F_0 scaled by val, built per
 // call in FP64), so a row needs no multiply by val; a merged sibling pair is
 // the same form with a combined slot-0 factor.
-// With the model's own leaf values and 8 nodes the rows are walked by their
-// node products, phi_j = sum_m H(m) c_j / F_j(m) with the quotients from
-// tables, H summed over neighbouring rows that share the slot
-// (values_rows_grouped: up to 8 features; values_rows_batched: longer rows,
-// FP32), and a few samples by a lane per row (values_lane_kernel).  The other
-// calls walk row by row (WALK = kPerRow): rows of at most 8 features reuse the
-// factors and prefix products of the slots they share with the previous row
-// (values_rows_shared, adjoint_rows_shared); longer rows (values_rows_long,
-// values_paths) run in batches of eight slots: slots past the end of a row get
-// c = 0 and b = 1, a factor of exactly 1, so whole batches run without
-// branches; the prefix products are kept only at batch checkpoints and rebuilt
-// batch by batch in the backward sweep, which bounds the registers; NH < NN
-// splits the nodes over several passes (the node sum is additive).
+// At 8 nodes, rows of at most 8 features in FP64 and, with the model's own leaf
+// values, longer rows in FP32 are walked by their node products, phi_j = sum_m
+// H(m) c_j / F_j(m) with quotients that do not depend on the sample, H summed
+// over neighbouring rows that share the slot (values_rows_grouped,
+// values_rows_batched).  A few samples take a lane per row
+// (values_lane_kernel).  The other calls walk row by row (WALK >= kPerRow):
+// rows of at most 8 features reuse the factors and prefix products of the slots
+// they share with the previous row (values_rows_shared, adjoint_rows_shared);
+// longer rows (values_rows_long, adjoint_paths) run in batches of eight slots:
+// slots past the end of a row get c = 0 and b = 1, a factor of exactly 1, so
+// whole batches run without branches; the prefix products are kept only at
+// batch checkpoints and rebuilt batch by batch in the backward sweep, which
+// bounds the registers; NH < NN splits the nodes over several passes (the node
+// sum is additive).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -584,24 +585,26 @@ __device__ __forceinline__ acc_v4 node_sums4(float A, const float (&H)[8], acc_v
   return acc;
 }
 
-// First order over rows of at most TOP + 4 <= 8 features at the 8-node rule.
-// With H(m) = w_m prod_k F_k(m) over all the row's slots, slot j adds
+// First order over rows of at most TOP + 4 <= 8 features at the 8-node rule, in
+// FP64.  With H(m) = w_m prod_k F_k(m) over all the row's slots, slot j adds
 //   sum_m c_j w_m prod_{k != j} F_k(m) = sum_m H(m) c_j / F_j(m),
 // and c_j / F_j depends on the sample only through its follow bit:
 //   followed: e_j(m) = (1 - b_j) / (b_j + t_m (1 - b_j)), a table per slot;
 //   not:      r(m) = -1 / (1 - t_m), the same for every slot.
 // So a row needs the running product, one node sum per slot against
 // sample-independent coefficients, and one sum D for all slots not followed;
-// no suffix products and no factors kept.  FP32 takes the node sums on the
-// matrix unit: four slots' coefficients are the 4x1 block of a 4x4x1 product
-// and a lane's sample keeps its lane; the row's 64 coefficients are one
-// coalesced load.  FP64 reads them as scalar operands.
+// no suffix products and no factors kept.
 // Slots 1..TOP are the row's root side.  While consecutive rows share all of
 // them, their H are summed and slots 1..TOP take their node sums once for
 // the run of rows (with full trees of depth TOP + 4: 8 rows); slots TOP + 1
-// .. TOP + 3 and D fill one 4-wide product per row.  P[k], the prefix product
-// through slot k, is kept from row to row, so only slots past the shared
-// count are evaluated.
+// .. TOP + 3, slot 0 and D are summed for every row.  P[k], the prefix product
+// through slot k, is kept from row to row for k >= TOP, so of the slots below
+// the root side only those past the shared count are evaluated.
+// (FP32 keeps values_rows_shared: a run's H would be summed in FP32, where
+// every row's term goes into the FP64 accumulator by itself there, and with
+// FP64 sums of H the walk is the slower one: 500 trees of depth 8, 100
+// features, 100k rows, FP32: 23.0 ms with FP32 sums, 24.8 with FP64 sums,
+// values_rows_shared 24.4.)
 //
 // The row loop is pipelined by hand.  Scalar loads and LDS reads share one
 // wait counter and scalar loads return out of order, so a wait for one is a
@@ -609,20 +612,16 @@ __device__ __forceinline__ acc_v4 node_sums4(float A, const float (&H)[8], acc_v
 // are in, and the next row's x are read before this row's sums are added.
 //
 // Bound by VALU issue: compares, selects and address adds read scalar
-// registers (1.3 clocks of a CU per wave instruction), the factor and product
-// FMAs do not (0.65), FP64 takes 1.3, four slots' node sums 19.  500 trees of
-// depth 8, 100 features, 100k rows, FP32: 24.5 ms with suffix products and
-// node sums per slot, 23.0 here; 300 such trees, 5003 rows, FP64: 3.43 and
-// 2.15 ms.
-template <typename T, int TOP, bool NANS>
+// registers, and FP64 takes 1.3 clocks of a CU per wave instruction.  300 trees
+// of depth 8, 100 features, 5003 rows: 3.43 ms with suffix products and node
+// sums per slot, 2.17 here.
+template <int TOP, bool NANS>
 __device__ __forceinline__ void values_rows_grouped(
-    const WalkRow<T>* __restrict__ rows, const T* __restrict__ coef, int row0,
-    const Slot0<T>* __restrict__ z0, const float* xs, double* as, int pb, int pe, int wave,
-    int nw, int lane, const NodeConsts<T>& nc) {
+    const WalkRow* __restrict__ rows, const double* __restrict__ coef, int row0,
+    const Slot0<double>* __restrict__ z0, const float* xs, double* as, int pb, int pe, int wave,
+    int nw, int lane, const NodeConsts<double>& nc) {
+  using T = double;
   constexpr int N = 8, ND = TOP + 3;
-  constexpr bool kF32 = sizeof(T) == 4;
-  // FP64 keeps the prefix products from slot TOP on only (registers)
-  constexpr bool kKeepTop = kF32;
   const int run = (pe - pb + nw - 1) / nw;
   const int p_first = pb + wave * run;
   const int p_last = min(pe, p_first + run);
@@ -632,11 +631,10 @@ __device__ __forceinline__ void values_rows_grouped(
   T Hs[TOP > 0 ? N : 1];  // sum of H over the rows since slots 1..TOP changed
   int xo_top[TOP > 0 ? TOP : 1];
   int d_top = 0, p_top = p_first;
-  float a_top = 0.f;
 #pragma unroll
   for (int k = 0; k <= ND; ++k) in_k[k] = 0;
 #pragma unroll
-  for (int m = 0; m < N; ++m) P[0][m] = node8_w(nc, m);
+  for (int m = 0; m < N; ++m) P[0][m] = nc.w[m];
 #pragma unroll
   for (int m = 0; m < (TOP > 0 ? N : 1); ++m) Hs[m] = T(0);
   const char* xl = reinterpret_cast<const char*>(xs + lane);
@@ -645,7 +643,7 @@ __device__ __forceinline__ void values_rows_grouped(
     return *reinterpret_cast<const float*>(xl + off);
   };
   auto add = [&](int xo, T v) __attribute__((always_inline)) {
-    __hip_atomic_fetch_add(reinterpret_cast<double*>(al + 2 * xo), (double)v, __ATOMIC_RELAXED,
+    __hip_atomic_fetch_add(reinterpret_cast<double*>(al + 2 * xo), v, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_WORKGROUP);
   };
   // lanes whose x lies in [l, u) (u = NaN: no bound), or is missing and miss
@@ -659,21 +657,14 @@ __device__ __forceinline__ void values_rows_grouped(
       T D = nc.r[0] * Hs[0];
 #pragma unroll
       for (int m = 1; m < N; ++m) D = fmaT(nc.r[m], Hs[m], D);
-      if constexpr (kF32) {
-        const acc_v4 E = node_sums4<0>(a_top, Hs, acc_v4{0.f, 0.f, 0.f, 0.f});
+      const T* e = coef + (int64_t)(p_top - row0) * kShortCoef;
 #pragma unroll
-        for (int k = 0; k < TOP; ++k)
-          if (k + 1 < d_top) add(xo_top[k], pick(in_k[k + 1], D, E[k]));
-      } else {
-        const T* e = coef + (int64_t)(p_top - row0) * kShortCoef;
+      for (int k = 0; k < TOP; ++k) {
+        if (k + 1 < d_top) {
+          T E = ldu(e + 8 * k) * Hs[0];
 #pragma unroll
-        for (int k = 0; k < TOP; ++k) {
-          if (k + 1 < d_top) {
-            T E = ldu(e + 8 * k) * Hs[0];
-#pragma unroll
-            for (int m = 1; m < N; ++m) E = fmaT(ldu(e + 8 * k + m), Hs[m], E);
-            add(xo_top[k], pick(in_k[k + 1], D, E));
-          }
+          for (int m = 1; m < N; ++m) E = fmaT(ldu(e + 8 * k + m), Hs[m], E);
+          add(xo_top[k], pick(in_k[k + 1], D, E));
         }
       }
     }
@@ -683,7 +674,7 @@ __device__ __forceinline__ void values_rows_grouped(
     const T bv = to_vgpr(b);
     const T c = pick(in_k[k], -bv, to_vgpr(cb));
 #pragma unroll
-    for (int m = 0; m < N; ++m) P[k][m] = P[k - 1][m] * fmaT(node8_t(nc, m), c, bv);
+    for (int m = 0; m < N; ++m) P[k][m] = P[k - 1][m] * fmaT(nc.t[m], c, bv);
   };
   struct Rec {  // the part of a row that every row reads (scalar registers)
     int32_t pack, xo0;
@@ -693,7 +684,7 @@ __device__ __forceinline__ void values_rows_grouped(
     T b[3], cb[3], bm, cA, cB;
   };
   auto load = [&](int p) __attribute__((always_inline)) {
-    const WalkRow<T>* w = rows + (p - row0);
+    const WalkRow* w = rows + (p - row0);
     Rec r;
     const row_v16 a = ldu(reinterpret_cast<const row_v16*>(w));  // 14 words are the row's
     r.pack = a[0];
@@ -717,18 +708,11 @@ __device__ __forceinline__ void values_rows_grouped(
   };
   Rec r = load(p_first);
   float x[4] = {x_at(r.xo0), x_at(r.xo[0]), x_at(r.xo[1]), x_at(r.xo[2])};
-  float a_row = 0.f, a_next = 0.f;
-  const T* coef_l = coef + lane;
-  if constexpr (kF32) a_next = coef_l[(int64_t)(p_first - row0) * kShortCoef];
   for (int p = p_first; p < p_last; ++p) {
     const int d = r.pack & 15;
     const int s = p == p_first ? 0 : (r.pack >> 4) & 15;
     const int mok = r.pack >> 8;
     const int p_next = min(p + 1, p_last - 1);
-    if constexpr (kF32) {
-      a_row = a_next;
-      a_next = coef_l[(int64_t)(p_next - row0) * kShortCoef];
-    }
     // follow bits of slot 0 and of slots TOP + 1 .. ND (shared ones come out
     // as they are), and slot 0's c
     uint64_t in0 = inside(x[0], r.lo0, r.hi0, NANS && (mok & 0x101) != 0);
@@ -744,7 +728,7 @@ __device__ __forceinline__ void values_rows_grouped(
 #pragma unroll
           for (int m = 0; m < N; ++m) Hs[m] = T(0);
         }
-        const WalkRow<T>* w = rows + (p - row0);
+        const WalkRow* w = rows + (p - row0);
         float xt[TOP], lt[TOP], ut[TOP];
         T bt[TOP], cbt[TOP];
 #pragma unroll
@@ -759,14 +743,11 @@ __device__ __forceinline__ void values_rows_grouped(
         for (int k = 0; k < TOP; ++k) xt[k] = x_at(xo_top[k]);
 #pragma unroll
         for (int k = 0; k < TOP; ++k) {
-          if (!kKeepTop || k + 1 > s) {
-            in_k[k + 1] = inside(xt[k], lt[k], ut[k], ((mok >> (k + 1)) & 1) != 0);
-            extend(k + 1, bt[k], cbt[k]);
-          }
+          in_k[k + 1] = inside(xt[k], lt[k], ut[k], ((mok >> (k + 1)) & 1) != 0);
+          extend(k + 1, bt[k], cbt[k]);
         }
         d_top = d;
         p_top = p;
-        a_top = a_row;
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -783,24 +764,18 @@ __device__ __forceinline__ void values_rows_grouped(
 #pragma unroll
     for (int m = 1; m < N; ++m) q0 += P[ND][m];
 #pragma unroll
-    for (int m = 0; m < N; ++m) H[m] = P[ND][m] * fmaT(node8_t(nc, m), c0, bv0);
+    for (int m = 0; m < N; ++m) H[m] = P[ND][m] * fmaT(nc.t[m], c0, bv0);
     // slots TOP + 1 .. ND, and D
     T E[4];
-    if constexpr (kF32) {
-      const acc_v4 a4 = node_sums4<1>(a_row, H, acc_v4{0.f, 0.f, 0.f, 0.f});
+    E[3] = nc.r[0] * H[0];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) E[i] = a4[i];
-    } else {
-      E[3] = nc.r[0] * H[0];
+    for (int m = 1; m < N; ++m) E[3] = fmaT(nc.r[m], H[m], E[3]);
+    const T* e = coef + (int64_t)(p - row0) * kShortCoef + 8 * TOP;
 #pragma unroll
-      for (int m = 1; m < N; ++m) E[3] = fmaT(nc.r[m], H[m], E[3]);
-      const T* e = coef + (int64_t)(p - row0) * kShortCoef + 8 * TOP;
+    for (int i = 0; i < 3; ++i) {
+      E[i] = ldu(e + 8 * i) * H[0];
 #pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        E[i] = ldu(e + 8 * i) * H[0];
-#pragma unroll
-        for (int m = 1; m < N; ++m) E[i] = fmaT(ldu(e + 8 * i + m), H[m], E[i]);
-      }
+      for (int m = 1; m < N; ++m) E[i] = fmaT(ldu(e + 8 * i + m), H[m], E[i]);
     }
     __builtin_amdgcn_sched_barrier(0);
     x[0] = x_at(rn.xo0);
@@ -1266,7 +1241,7 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
               const Segment* __restrict__ segs, const int32_t* __restrict__ seg_feat,
               int32_t ng, BucketIndex bx, double* __restrict__ acc, void* __restrict__ direct,
               int32_t direct_fp64, int32_t plain_add, const ShortRow<T>* __restrict__ srows,
-              const WalkRow<T>* __restrict__ wrows, const T* __restrict__ wcoef,
+              const WalkRow* __restrict__ wrows, const double* __restrict__ wcoef,
               NodeConsts<T> nc) {
   extern __shared__ __align__(16) unsigned char smem[];
   float* xs = reinterpret_cast<float*>(smem);
@@ -1326,11 +1301,11 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
 
   if constexpr (DMAX == 8 && WALK < kPerRow) {
     if (any_nan)
-      values_rows_grouped<T, WALK, true>(wrows, wcoef, path_begin, z0, xs, as, pb, pe, wave, nw,
-                                         lane, nc);
+      values_rows_grouped<WALK, true>(wrows, wcoef, path_begin, z0, xs, as, pb, pe, wave, nw,
+                                      lane, nc);
     else
-      values_rows_grouped<T, WALK, false>(wrows, wcoef, path_begin, z0, xs, as, pb, pe, wave, nw,
-                                          lane, nc);
+      values_rows_grouped<WALK, false>(wrows, wcoef, path_begin, z0, xs, as, pb, pe, wave, nw,
+                                       lane, nc);
   } else if constexpr (WALK == kBatched) {
     if (any_nan)
       values_rows_batched<DMAX, true>(hdr, feat, lo, hi, bb, cbb, z0, share, xs, as, pb, pe,
@@ -1539,12 +1514,12 @@ __device__ __forceinline__ void adjoint_rows_shared(
 // row loop is pipelined as in values_rows_grouped.
 // (FP32 keeps adjoint_rows_shared: its gradient is returned in FP64 and holds
 // the rounding of every row's sums, which this order would change.)
-template <typename T, int TOP, bool NANS>
+template <int TOP, bool NANS>
 __device__ __forceinline__ void adjoint_rows_grouped(
-    const WalkRow<T>* __restrict__ rows, const T* __restrict__ coef, int row0,
-    const float* xs, const T* gs, LeafSums sums, int pb, int pe, int wave, int nw, int lane,
-    const NodeConsts<T>& nc) {
-  static_assert(sizeof(T) == 8, "offsets of the gradient tile are twice the sample tile's");
+    const WalkRow* __restrict__ rows, const double* __restrict__ coef, int row0,
+    const float* xs, const double* gs, LeafSums sums, int pb, int pe, int wave, int nw, int lane,
+    const NodeConsts<double>& nc) {
+  using T = double;  // offsets of the gradient tile are twice the sample tile's
   constexpr int N = 8, ND = TOP + 3;
   const int run = (pe - pb + nw - 1) / nw;
   const int p_first = pb + wave * run;
@@ -1590,7 +1565,7 @@ __device__ __forceinline__ void adjoint_rows_grouped(
     T b[3], cb[3], b0[4];
   };
   auto load = [&](int p) __attribute__((always_inline)) {
-    const WalkRow<T>* w = rows + (p - row0);
+    const WalkRow* w = rows + (p - row0);
     Rec r;
     const row_v16 a = ldu(reinterpret_cast<const row_v16*>(w));  // 14 words are the row's
     r.pack = a[0];
@@ -1628,7 +1603,7 @@ __device__ __forceinline__ void adjoint_rows_grouped(
           inside(x[i].x, r.lo[i], r.hi[i], ((mok >> (TOP + 1 + i)) & 1) != 0);
     if constexpr (TOP > 0) {
       if (s < TOP) {
-        const WalkRow<T>* w = rows + (p - row0);
+        const WalkRow* w = rows + (p - row0);
         XG xt[TOP];
 #pragma unroll
         for (int k = 0; k < TOP; ++k) xt[k] = xg_at(ldu(&w->xot[k]));
@@ -1719,8 +1694,8 @@ adjoint_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat
                int32_t nsb, int32_t n_groups, const Segment* __restrict__ segs,
                const int32_t* __restrict__ seg_feat, int32_t ng, BucketIndex bx,
                double* __restrict__ grad_leaf, int64_t part_stride,
-               const ShortRow<T>* __restrict__ srows, const WalkRow<T>* __restrict__ wrows,
-               const T* __restrict__ wcoef, NodeConsts<T> nc) {
+               const ShortRow<T>* __restrict__ srows, const WalkRow* __restrict__ wrows,
+               const double* __restrict__ wcoef, NodeConsts<T> nc) {
   extern __shared__ __align__(16) unsigned char smem[];
   float* xs = reinterpret_cast<float*>(smem);
   const size_t tile_rows = (size_t)tile_f * kTileStride;
@@ -1787,11 +1762,11 @@ adjoint_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat
     const bool any_nan = __syncthreads_or(nan_seen) != 0;
     if constexpr (kGrouped) {
       if (any_nan)
-        adjoint_rows_grouped<T, TOP, true>(wrows, wcoef, path_begin, xs, gs, sums, pb, pe, wave,
-                                           nw, lane, nc);
+        adjoint_rows_grouped<TOP, true>(wrows, wcoef, path_begin, xs, gs, sums, pb, pe, wave, nw,
+                                        lane, nc);
       else
-        adjoint_rows_grouped<T, TOP, false>(wrows, wcoef, path_begin, xs, gs, sums, pb, pe, wave,
-                                            nw, lane, nc);
+        adjoint_rows_grouped<TOP, false>(wrows, wcoef, path_begin, xs, gs, sums, pb, pe, wave, nw,
+                                         lane, nc);
     } else if constexpr (DMAX == 8) {
       if (any_nan)
         adjoint_rows_shared<T, NH, TOP + 3, true>(srows, path_begin, hdr, side, xs, gs, sums, pb,
@@ -1910,22 +1885,14 @@ RowSplit row_split(const HostTable& h, const PathArrays& a, const BucketSpan& sp
   fail(QTS_E_INVALID_ARG, "internal: bucket without segments");
 }
 
-// The grouped walk's rows of a capacity-8 bucket and their coefficients.
-template <typename T>
-struct WalkPtrs {
-  const WalkRow<T>* rows = nullptr;
-  const T* coef = nullptr;
-};
-template <typename T>
-WalkPtrs<T> walk_of(const PathArrays& a, const BucketSpan& sp) {
+// The grouped walk's rows of a capacity-8 bucket and their coefficients (FP64
+// at 8 nodes).
+ShortWalk walk_of(const PathArrays& a, const BucketSpan& sp) {
   const Bucket& bk = sp.list[0];
   if (bk.dmax != 8 || bk.srow_begin < 0) return {};
-  WalkPtrs<T> w;
-  if constexpr (std::is_same<T, float>::value) w = {a.walk.row32, a.walk.coef32};
-  else w = {a.walk.row64, a.walk.coef64};
-  if (w.rows == nullptr || w.coef == nullptr)
+  if (a.walk.rows == nullptr || a.walk.coef == nullptr)
     fail(QTS_E_INVALID_ARG, "internal: no grouped-walk rows");
-  return {w.rows + bk.srow_begin, w.coef + (int64_t)bk.srow_begin * kShortCoef};
+  return {a.walk.rows + bk.srow_begin, a.walk.coef + (int64_t)bk.srow_begin * kShortCoef};
 }
 
 // The first-order kernel's chunk where no timed shape says it: the split with
@@ -1997,7 +1964,8 @@ void launch_one(const HostTable& h, const DeviceTable& d, const PathArrays& a,
   if (lds > raise_lds_limit(fn))
     fail(QTS_E_UNSUPPORTED, "internal: the sample tile does not fit in LDS");
   const ShortRow<T>* srows = short_rows_of<T>(a, sp);
-  const WalkPtrs<T> walk = walk_of<T>(a, sp);
+  const ShortWalk walk =
+      std::is_same<T, double>::value && NN == 8 ? walk_of(a, sp) : ShortWalk{};
   if (!det) {
     hipLaunchKernelGGL((values_kernel<T, DMAX, NH, STORE_G, NN, WALK>), dim3((unsigned)grid),
                        dim3(threads), lds, s, a.hdr, rs.feat, a.lo, a.hi, b, cb,
@@ -2083,7 +2051,8 @@ void launch_adj_one(const HostTable& h, const DeviceTable& d, const PathArrays& 
   NodeConsts<T> nc;
   if constexpr (std::is_same<T, float>::value) nc = NN == 8 ? d.n32 : d.n32_4;
   else nc = NN == 8 ? d.n64 : d.n64_4;
-  const WalkPtrs<T> w = walk_of<T>(a, sp);
+  const ShortWalk w =
+      std::is_same<T, double>::value && NN == 8 ? walk_of(a, sp) : ShortWalk{};
   hipLaunchKernelGGL((adjoint_kernel<T, DMAX, NH, STORE_G, NN, TOP>), dim3((unsigned)grid),
                      dim3(threads), lds, s, a.hdr, rs.feat, a.lo, a.hi, b, cb, a.side, X,
                      (const T*)G, M, ldx, F, rs.tile_f, sp.path_begin(), sp.path_end(),
@@ -2143,14 +2112,10 @@ void launch_adjoint(const HostTable& h, const DeviceTable& d, const PathArrays& 
 }
 
 // The grouped walk's rows and node-sum coefficients of one bucket, 64 threads
-// per row.  FP32 coefficients: entry 4 (8 G + m) + i is slot i + 1's when
-// G = 0 and i < top, slot top + 1 + i's when G = 1 and i < 3, and r(m) when
-// G = 1 and i = 3 (the blocks of node_sums4).  FP64: entry 8 (j - 1) + m is
-// slot j's.
-template <typename T>
+// per row; entry 8 (j - 1) + m of a row's coefficients is slot j's.
 __device__ __forceinline__ void fill_walk_row(const ShortRow<double>& r, const PathHdr& h,
-                                              const SidePath* side, int32_t top, WalkRow<T>* o) {
-  WalkRow<T> w;
+                                              const SidePath* side, int32_t top, WalkRow* o) {
+  WalkRow w;
   const int sidx = side == nullptr ? -1 : h.tree;
   int mok_b = 0;
   w.xo0 = r.xoff[0];
@@ -2162,14 +2127,14 @@ __device__ __forceinline__ void fill_walk_row(const ShortRow<double>& r, const P
     w.hi0 = side[sidx].hi_b;
     mok_b = side[sidx].mok_b != 0 ? 1 : 0;
   }
-  w.b0[0] = (T)r.b[0];
-  w.b0[1] = (T)r.cb[0];
-  w.b0[2] = w.b0[3] = T(0);
+  w.b0[0] = r.b[0];
+  w.b0[1] = r.cb[0];
+  w.b0[2] = w.b0[3] = 0.0;
   if (r.d > 0 && sidx >= 0) {
-    w.b0[0] = (T)side[sidx].b_a;
-    w.b0[1] = (T)side[sidx].cb_a;
-    w.b0[2] = (T)side[sidx].b_b;
-    w.b0[3] = (T)side[sidx].cb_b;
+    w.b0[0] = side[sidx].b_a;
+    w.b0[1] = side[sidx].cb_a;
+    w.b0[2] = side[sidx].b_b;
+    w.b0[3] = side[sidx].cb_b;
   }
   w.pack = r.d | r.share << 4 | (r.mok & 0xff) << 8 | mok_b << 16;
   for (int i = 0; i < 3; ++i) {
@@ -2177,16 +2142,16 @@ __device__ __forceinline__ void fill_walk_row(const ShortRow<double>& r, const P
     w.xol[i] = r.xoff[k];
     w.lol[i] = r.lo[k];
     w.hil[i] = r.hi[k];
-    w.bl[i] = (T)r.b[k];
-    w.cbl[i] = (T)r.cb[k];
+    w.bl[i] = r.b[k];
+    w.cbl[i] = r.cb[k];
   }
   for (int i = 0; i < 4; ++i) {
     const int k = i < top ? i + 1 : 0;
     w.xot[i] = r.xoff[k];
     w.lot[i] = r.lo[k];
     w.hit[i] = r.hi[k];
-    w.bt[i] = (T)r.b[k];
-    w.cbt[i] = (T)r.cb[k];
+    w.bt[i] = r.b[k];
+    w.cbt[i] = r.cb[k];
   }
   *o = w;
 }
@@ -2194,25 +2159,15 @@ __device__ __forceinline__ void fill_walk_row(const ShortRow<double>& r, const P
 __global__ void __launch_bounds__(256)
 short_walk_kernel(const ShortRow<double>* __restrict__ rows, const PathHdr* __restrict__ hdr,
                   const SidePath* __restrict__ side, int32_t n, int32_t top,
-                  NodeConsts<double> nc, WalkRow<float>* __restrict__ w32,
-                  WalkRow<double>* __restrict__ w64, float* __restrict__ e32,
-                  double* __restrict__ e64) {
+                  NodeConsts<double> nc, WalkRow* __restrict__ out, double* __restrict__ coef) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t row = i >> 6;
   if (row >= n) return;
   const int l = (int)i & 63;
   const ShortRow<double>& r = rows[row];
-  auto coef = [&](int j, int m) {
-    return j > 7 ? 0.0 : r.cb[j] / (r.b[j] + nc.t[m] * r.cb[j]);
-  };
-  e64[i] = coef((l >> 3) + 1, l & 7);
-  const int g = l >> 5, m = (l >> 2) & 7, k = l & 3;
-  double v = 0.0;
-  if (g == 0) v = k < top ? coef(k + 1, m) : 0.0;
-  else v = k < 3 ? coef(top + 1 + k, m) : nc.r[m];
-  e32[i] = (float)v;
-  if (l == 0) fill_walk_row(r, hdr[row], side, top, w32 + row);
-  if (l == 1) fill_walk_row(r, hdr[row], side, top, w64 + row);
+  const int j = (l >> 3) + 1, m = l & 7;
+  coef[i] = j > 7 ? 0.0 : r.cb[j] / (r.b[j] + nc.t[m] * r.cb[j]);
+  if (l == 0) fill_walk_row(r, hdr[row], side, top, out + row);
 }
 
 void launch_short_walk(const PathArrays& a, const Bucket& bk, const NodeConsts<double>& nc,
@@ -2221,10 +2176,8 @@ void launch_short_walk(const PathArrays& a, const Bucket& bk, const NodeConsts<d
   if (bk.dmax != 8 || n <= 0) return;
   const unsigned grid = (unsigned)(((int64_t)n * 64 + 255) / 256);
   hipLaunchKernelGGL(short_walk_kernel, dim3(grid), dim3(256), 0, s, a.srow64 + bk.srow_begin,
-                     a.hdr + bk.path_begin, a.side, n, bk.top, nc, a.walk.row32 + bk.srow_begin,
-                     a.walk.row64 + bk.srow_begin,
-                     a.walk.coef32 + (int64_t)bk.srow_begin * kShortCoef,
-                     a.walk.coef64 + (int64_t)bk.srow_begin * kShortCoef);
+                     a.hdr + bk.path_begin, a.side, n, bk.top, nc, a.walk.rows + bk.srow_begin,
+                     a.walk.coef + (int64_t)bk.srow_begin * kShortCoef);
   check_hip(hipGetLastError(), "short_walk_kernel launch");
 }
 
@@ -2491,10 +2444,8 @@ void launch_values(const HostTable& h, const DeviceTable& d, const PathArrays& a
         else go(0.0, QTS_N(8), QTS_N(4), false_type{}, QTS_N(4), walk);
       } else if (fp64) {
         go(0.0, QTS_N(8), QTS_N(8), true_type{}, QTS_N(8), top);
-      } else if (per_row) {
-        go(0.f, QTS_N(8), QTS_N(8), true_type{}, QTS_N(8), walk);
       } else {
-        go(0.f, QTS_N(8), QTS_N(8), true_type{}, QTS_N(8), top);
+        go(0.f, QTS_N(8), QTS_N(8), true_type{}, QTS_N(8), walk);
       }
     };
     switch (sp.list[0].top) {

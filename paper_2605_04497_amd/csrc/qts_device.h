@@ -58,7 +58,7 @@ struct alignas(16) ShortRow {
   T b[8], cb[8];    // b_j and 1 - b_j (FP64-derived), rounded to T
 };
 
-// A short row as the grouped walk of the 8-node rule reads it
+// A short row as the grouped FP64 walk of the 8-node rule reads it
 // (values_rows_grouped), built on the device from its ShortRow.  Slots 1..top
 // of the bucket (Bucket::top) are the row's root side, read only when they
 // change; slot 0 and the three slots after them are read for every row.
@@ -66,18 +66,17 @@ struct alignas(16) ShortRow {
 // of the samples inside, A takes those below `split` (a single path: split
 // is its own upper bound).  Offsets are bytes into the FP32 sample tile; the
 // FP64 accumulator's are twice those.
-template <typename T>
 struct alignas(8) WalkRow {
   int32_t pack;    // d | share << 4 | missing_ok bits of slots 0..7 << 8 | B's << 16
   int32_t xo0;
   float lo0, hi0, split;
   int32_t xol[3];  // slots top + 1 .. top + 3
   float lol[3], hil[3];
-  T bl[3], cbl[3];
-  T b0[4];         // slot 0's b and 1 - b of leaf A, then of leaf B (0 for a single path)
+  double bl[3], cbl[3];
+  double b0[4];    // slot 0's b and 1 - b of leaf A, then of leaf B (0 for a single path)
   int32_t xot[4];  // slots 1 .. top
   float lot[4], hit[4];
-  T bt[4], cbt[4];
+  double bt[4], cbt[4];
 };
 
 // Node-sum coefficients (1 - b_j) / (b_j + t_m (1 - b_j)) of a short row's
@@ -87,10 +86,8 @@ constexpr int kShortCoef = 64;
 // The grouped walk's tables of one first-order table's short rows (in the
 // order of Bucket::srow_begin); kShortCoef coefficients per row.
 struct ShortWalk {
-  WalkRow<float>* row32 = nullptr;
-  WalkRow<double>* row64 = nullptr;
-  float* coef32 = nullptr;
-  double* coef64 = nullptr;
+  WalkRow* rows = nullptr;
+  double* coef = nullptr;
 };
 
 // Device copy of the path table.  Element arrays are shared by all buckets.
@@ -443,9 +440,10 @@ size_t slot0_bytes(int32_t n_rows, bool fp64);
 // Wide feature spaces (wide_features(F): the table's work items are
 // segments) take feature-major layouts: X is [F][ldx] (ldx >= M) and acc
 // [n_groups][F][M]; `direct` is not used there.
-// per_row: FP32 takes the walks that form every slot's sum per row (calls with
-// leaf values of their own, i.e. training: the FP64-typed gradients that
-// follow from phi then keep the rounding they have had).
+// per_row: FP32 rows of more than 8 features take the walk that forms every
+// slot's sum per row (calls with leaf values of their own, i.e. training: the
+// FP64-typed gradients that follow from phi then keep the rounding they have
+// had).
 void launch_values(const HostTable& h, const DeviceTable& d, const PathArrays& a,
                    const BucketSpan& sp, bool fp64, const float* X, int64_t M, int64_t ldx,
                    const void* slot0, double* acc, void* direct, const ValuesShape& shape,
