@@ -813,11 +813,13 @@ __device__ __forceinline__ void values_rows_grouped(
 // (1 - b_j) / (b_j + t_m (1 - b_j)) are formed when it closes, one per lane:
 // lane 4 (8 g + m) + i has slot 4 g + i of the batch at node m, the blocks of
 // node_sums4.
-// Batches of 8: 99 VGPRs at 32 slots, four waves per SIMD.  Batches of 4
-// evaluate fewer shared slots again but keep twice the state (187 VGPRs, two
-// waves): 100 trees of up to 32 features and 512 leaves, 10k rows, 6.3 ms
-// against 10.6 ms; the suffix products per row and slot that this replaces
-// took 12.2 ms.
+// Hs is in FP64: a run may be as long as a subtree has rows, and FP32 sums of
+// 4000 like rows lose 2e-5.  Its node sums are FP32's, of the sum rounded once.
+// Batches of 8: 148 VGPRs at 32 slots, three waves per SIMD (64 slots: 256 and
+// 88 bytes of scratch).  100 trees of up to 32 features and 512 leaves, 10k
+// rows: 7.3 ms, 6.3 with FP32 sums (99 VGPRs, four waves); 12.2 by the suffix
+// products per row and slot that this replaces.  Batches of 4 evaluate fewer
+// shared slots again but keep twice the state (10.6 ms already with FP32 sums).
 template <int DMAX, bool NANS>
 __device__ __forceinline__ void values_rows_batched(
     const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
@@ -829,13 +831,14 @@ __device__ __forceinline__ void values_rows_batched(
   const int run = (pe - pb + nw - 1) / nw;
   const int p_first = pb + wave * run;
   const int p_last = min(pe, p_first + run);
-  float P[NB + 1][N], Hs[NB][N];
+  float P[NB + 1][N];
+  double Hs[NB][N];
   uint32_t bits[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
     bits[b] = 0;
 #pragma unroll
-    for (int m = 0; m < N; ++m) Hs[b][m] = 0.f;
+    for (int m = 0; m < N; ++m) Hs[b][m] = 0.0;
   }
 #pragma unroll
   for (int m = 0; m < N; ++m) P[0][m] = rule8_w32(m);
@@ -858,10 +861,13 @@ __device__ __forceinline__ void values_rows_batched(
     constexpr int b = decltype(bc)::value;
     const int j = off_p + BS * b + 1 + slot_lane;
     const float bj = bb[j], cj = cbb[j];
-    const float D0 = [&] {
-      float D = rule8_r32(0) * Hs[b][0];
+    float h[N];
 #pragma unroll
-      for (int m = 1; m < N; ++m) D = __builtin_fmaf(rule8_r32(m), Hs[b][m], D);
+    for (int m = 0; m < N; ++m) h[m] = (float)Hs[b][m];
+    const float D0 = [&] {
+      float D = rule8_r32(0) * h[0];
+#pragma unroll
+      for (int m = 1; m < N; ++m) D = __builtin_fmaf(rule8_r32(m), h[m], D);
       return D;
     }();
     const float den = __builtin_fmaf(t_lane, cj, bj);
@@ -873,8 +879,8 @@ __device__ __forceinline__ void values_rows_batched(
     auto emit = [&](auto full) __attribute__((always_inline)) {
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
-        const acc_v4 E = g == 0 ? node_sums4<0>(A, Hs[b], acc_v4{0.f, 0.f, 0.f, 0.f})
-                                : node_sums4<1>(A, Hs[b], acc_v4{0.f, 0.f, 0.f, 0.f});
+        const acc_v4 E = g == 0 ? node_sums4<0>(A, h, acc_v4{0.f, 0.f, 0.f, 0.f})
+                                : node_sums4<1>(A, h, acc_v4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int k = 4 * g + i;
@@ -894,7 +900,7 @@ __device__ __forceinline__ void values_rows_batched(
       for (int m = 0; m < N; ++m) Hs[b - 1][m] += Hs[b][m];
     }
 #pragma unroll
-    for (int m = 0; m < N; ++m) Hs[b][m] = 0.f;
+    for (int m = 0; m < N; ++m) Hs[b][m] = 0.0;
   };
   auto close_from = [&](int b0) __attribute__((always_inline)) {
     static_for_down<NB>([&](auto bc) __attribute__((always_inline)) {
@@ -975,7 +981,7 @@ __device__ __forceinline__ void values_rows_batched(
         for (int m = 1; m < N; ++m) q0 += P[b + 1][m];
 #pragma unroll
         for (int m = 0; m < N; ++m)
-          Hs[b][m] = __builtin_fmaf(P[b + 1][m], __builtin_fmaf(rule8_t32(m), c0, bv0), Hs[b][m]);
+          Hs[b][m] += (double)(P[b + 1][m] * __builtin_fmaf(rule8_t32(m), c0, bv0));
         add(f0, c0 * q0);
       }
     });

@@ -48,7 +48,7 @@ def chain_over_fan(n_top, levels, n_trees):
                           rep(cover), rep(value), n_top + 1, 0.0, {})
 
 
-@pytest.mark.parametrize("n_top", [7])
+@pytest.mark.parametrize("n_top", [7, 8, 12])
 def test_long_sums_stay_in_fp64(oracle_mod, n_top):
     """At these sizes a wavefront walks about 4000 alike rows one after another
     (deterministic: one wavefront per workgroup).  A path's term is a product
@@ -73,8 +73,9 @@ def test_long_sums_stay_in_fp64(oracle_mod, n_top):
         err = row_normwise(got, want)
         print("deterministic %s: %.2e" % (det, err), flush=True)
         assert err <= 2e-6, (det, err)
-    # the same values passed by the caller take the same walk: the same bits
-    lv = torch.from_numpy(ens.leaf_values()).cuda()
-    own = e.shap_values(Xd[:4096], "fp32")
-    assert torch.equal(own, e.shap_values(Xd[:4096], "fp32", leaf_values=lv))
+    if n_top < 8:
+        # the same values passed by the caller take the same walk: the same bits
+        lv = torch.from_numpy(ens.leaf_values()).cuda()
+        own = e.shap_values(Xd[:4096], "fp32")
+        assert torch.equal(own, e.shap_values(Xd[:4096], "fp32", leaf_values=lv))
     e.close()
