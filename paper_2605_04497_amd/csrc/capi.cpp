@@ -406,8 +406,8 @@ void build_nodes(DeviceTable& d) {
     d.n32.w[m] = (float)w[m];
     d.n64.t[m] = t[m];
     d.n64.w[m] = w[m];
-    d.n64.r[m] = -1.0 / s[m];
-    d.n32.r[m] = (float)d.n64.r[m];
+    d.n64.r[m] = (double)(-1.0L / (1.0L - (long double)d.n64.t[m]));
+    d.n32.r[m] = (float)(-1.0 / (1.0 - (double)d.n32.t[m]));
     // the FP32 short-row walks take the rule as instruction literals
     if (d.n32.t[m] != rule8_t32(m) || d.n32.w[m] != rule8_w32(m) ||
         d.n32.r[m] != rule8_r32(m))

@@ -2172,7 +2172,8 @@ short_walk_kernel(const ShortRow<double>* __restrict__ rows, const PathHdr* __re
   const int l = (int)i & 63;
   const ShortRow<double>& r = rows[row];
   const int j = (l >> 3) + 1, m = l & 7;
-  coef[i] = j > 7 ? 0.0 : r.cb[j] / (r.b[j] + nc.t[m] * r.cb[j]);
+  // over F as the walks form it
+  coef[i] = j > 7 ? 0.0 : r.cb[j] / __builtin_fma(nc.t[m], r.cb[j], r.b[j]);
   if (l == 0) fill_walk_row(r, hdr[row], side, top, out + row);
 }
 

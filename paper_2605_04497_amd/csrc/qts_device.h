@@ -12,7 +12,8 @@ template <typename T>
 struct NodeConsts {
   T t[kNodes];
   T w[kNodes];
-  T r[kNodes];  // -1 / (1 - t): (o - b) / F of a slot whose splits are not followed
+  T r[kNodes];  // -1 / (1 - t) of the t above: (o - b) / F of a slot whose splits are not
+                // followed (rule8_r32)
 };
 
 constexpr int kTileStride = kSamplesPerBlock + 1;  // padded LDS row (bank spread)
@@ -33,9 +34,14 @@ __host__ __device__ constexpr float rule8_w32(int m) {
   return w[m];
 }
 
-// -1 / (1 - t_m): (o - b) / F of a slot whose splits are not followed.
+// -1 / (1 - t_m): (o - b) / F of a slot whose splits are not followed, from the
+// t_m that F is formed with.  The FP32 t_8 is 1e-8 off the node, and 1 - t_8 is
+// 0.02: r of the exact node would be 5e-7 off that F's ratio, in every row
+// alike, so rows that cancel would leave it over (equal leaf values, trees of
+// up to 12 features: twice the rounding error).
 __host__ __device__ constexpr float rule8_r32(int m) {
-  constexpr float r[kNodes] = {-0x1.052f940p+0f, -0x1.1cf8e20p+0f, -0x1.4f9edc0p+0f, -0x1.b0a3960p+0f, -0x1.39821e0p+1f, -0x1.0dc6ac0p+2f, -0x1.3ac0fa0p+3f, -0x1.92eb720p+5f};
+  constexpr float r[kNodes] = {-0x1.052f94p+0f, -0x1.1cf8e2p+0f, -0x1.4f9edcp+0f, -0x1.b0a396p+0f,
+                               -0x1.39821ep+1f, -0x1.0dc6aap+2f, -0x1.3ac0fcp+3f, -0x1.92eb66p+5f};
   return r[m];
 }
 

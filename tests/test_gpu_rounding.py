@@ -1,6 +1,7 @@
-"""FP32 first order where the sums over rows are long: every path's term is
-added to the FP64 accumulators, so the error stays that of one path's
-arithmetic however many paths share a feature."""
+"""First order where rounding errors could add up: long sums over rows (every
+path's term is added to the FP64 accumulators, so the error stays that of one
+path's arithmetic however many paths share a feature), and rows that cancel
+exactly (an error that all rows share would be left over)."""
 import numpy as np
 import pytest
 
@@ -78,4 +79,33 @@ def test_long_sums_stay_in_fp64(oracle_mod, n_top):
         lv = torch.from_numpy(ens.leaf_values()).cuda()
         own = e.shap_values(Xd[:4096], "fp32")
         assert torch.equal(own, e.shap_values(Xd[:4096], "fp32", leaf_values=lv))
+    e.close()
+
+
+@pytest.mark.parametrize("precision,F,depth,n_trees", [("fp64", 10, 8, 40), ("fp64", 20, 6, 40),
+                                                       ("fp32", 12, 12, 6)])
+def test_rows_that_cancel(oracle_mod, precision, F, depth, n_trees):
+    """Equal leaf values: every feature's value is exactly 0, and what comes out
+    is rounding.  It is no more than that of the same sums term by term, in
+    which a factor of the row never meets its own quotient: FP64's reference is
+    the oracle's own, FP32's the walk that a call with leaf values of its own
+    takes.  The walks round about as often; a quarter is for their difference
+    (quotients of other nodes than the factors' give about twice)."""
+    import paper_2605_04497_amd as q
+    print("case", precision, F, depth, flush=True)
+    ens = synth.random_small_ensemble(np.random.default_rng(7), n_trees, F, depth, n_train=20000,
+                                      p_leaf=0.02)
+    ens = ens.with_leaf_values(np.ones(ens.n_leaves()))
+    X = np.random.default_rng(8).normal(size=(256, F)).astype(np.float32)
+    e = q.Ensemble(ens)
+    Xd = torch.from_numpy(X).cuda()
+    rms = lambda a: float(np.sqrt(np.mean(np.square(a))))  # noqa: E731
+    got = rms(e.shap_values(Xd, precision).double().cpu().numpy())
+    if precision == "fp64":
+        ref = rms(oracle_mod.shap_values(ens, X, n=8))
+    else:
+        lv = torch.ones(ens.n_leaves(), dtype=torch.float64, device="cuda")
+        ref = rms(e.shap_values(Xd, precision, leaf_values=lv).double().cpu().numpy())
+    print("rms %.3e, term by term %.3e" % (got, ref), flush=True)
+    assert got <= 1.25 * ref
     e.close()

@@ -67,6 +67,17 @@ def test_fp32_rule_constants(q):
     assert np.array_equal(table("rule8_w32"), np.float32(w).astype(np.float64))
 
 
+def test_fp32_rule_ratio_of_its_own_nodes(q):
+    """rule8_r32, the ratio (o - b) / F of a slot that is not followed, is that
+    of the FP32 nodes that F is formed with, not of the exact ones: -1 / (1 - t)
+    rounded once."""
+    src = open(os.path.join(ROOT, "paper_2605_04497_amd", "csrc", "qts_device.h")).read()
+    m = re.search(r"rule8_r32\(int m\) \{\s*constexpr float r\[kNodes\] = \{([^}]*)\}", src)
+    r = np.array([float.fromhex(x.strip().rstrip("f")) for x in m.group(1).split(",")])
+    t32 = np.float32(q.gauss_legendre(8)[0]).astype(np.float64)
+    assert np.array_equal(r, np.float32(-1 / (1 - t32)).astype(np.float64))
+
+
 def _phi_from_table(tab, leaf_values, X, F):
     """Re-evaluate phi from the exported table in numpy (test-only path form)."""
     x, wq = np.polynomial.legendre.leggauss(8)
