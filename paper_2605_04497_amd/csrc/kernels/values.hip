@@ -1738,7 +1738,7 @@ adjoint_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat
     // zero gradient, so they add nothing); note any NaN.  With segments (wide
     // feature spaces) X is feature-major [F][ldx] and G [ng][F][M].
     const int64_t s0 = (int64_t)sb * kSamplesPerBlock;
-    int nan_seen = 0;
+    int nan_seen = 0, g_bad = 0;
     // not loop invariants: the walk needs the registers that hoisted index
     // arithmetic would hold
     int tid = threadIdx.x, nf = ir.nf;
@@ -1752,7 +1752,9 @@ adjoint_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat
         const float v = (s < M) ? X[(int64_t)f * ldx + s] : 0.0f;
         nan_seen |= (v != v);
         xs[k * kTileStride + r] = v;
-        gs[k * kTileStride + r] = (s < M) ? G[((int64_t)ir.grp * F + f) * M + s] : T(0);  // G[grp, f, s]
+        const T g = (s < M) ? G[((int64_t)ir.grp * F + f) * M + s] : T(0);  // G[grp, f, s]
+        if (kGrouped) g_bad |= !(__builtin_fabs(g) < INFINITY);
+        gs[k * kTileStride + r] = g;
       }
     } else {
       for (int i = tid; i < tile; i += blockDim.x) {
@@ -1762,12 +1764,20 @@ adjoint_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat
         const float v = (s < M) ? X[s * ldx + k] : 0.0f;
         nan_seen |= (v != v);
         xs[k * kTileStride + r] = v;
-        gs[k * kTileStride + r] = (s < M) ? G[(s * ng + ir.grp) * F + k] : T(0);  // G[s, grp, f]
+        const T g = (s < M) ? G[(s * ng + ir.grp) * F + k] : T(0);  // G[s, grp, f]
+        if (kGrouped) g_bad |= !(__builtin_fabs(g) < INFINITY);
+        gs[k * kTileStride + r] = g;
       }
     }
-    const bool any_nan = __syncthreads_or(nan_seen) != 0;
+    const bool any_nan = __syncthreads_or(nan_seen | g_bad) != 0;
     if constexpr (kGrouped) {
-      if (any_nan)
+      if (any_nan && __syncthreads_or(g_bad) != 0)
+        // an infinite gradient makes inf - inf and 0 inf of the sums over
+        // slots and nodes that the grouped walk regroups; row by row it comes
+        // out as the infinity that it is
+        adjoint_paths<T, 8, 2, false, true, NN>(hdr, feat, lo, hi, bb, cbb, side, xs, gs, sums, pb,
+                                                pe, wave, nw, lane, tv, nc);
+      else if (any_nan)
         adjoint_rows_grouped<TOP, true>(wrows, wcoef, path_begin, xs, gs, sums, pb, pe, wave, nw,
                                         lane, nc);
       else
