@@ -48,16 +48,23 @@ struct GraphEntry {
 
 // Scratch that an ensemble keeps between its calls on the default stream: a
 // stream-ordered allocation and its release cost a call 12 us of host time (a
-// 10-tree model's call takes 14 us without them, 27 with).  Only the default
+// 10-tree model's call takes 19 us without them, 32 with).  Only the default
 // stream's calls use it (its work is ordered, and its handle never comes to
 // mean another stream), one call at a time while it is being issued, and only
-// up to kKept bytes; every other call allocates as before.
+// up to kKept bytes; every other call allocates as before.  The workspace
+// itself is stream-ordered too: growing it waits for nothing, and may run
+// while another thread captures a graph.
 struct Workspace {
   static constexpr size_t kKept = (size_t)64 << 20;
   std::mutex mu;
   void* p = nullptr;
   size_t bytes = 0;
   bool busy = false;
+  void release() {
+    if (p) (void)hipFreeAsync(p, nullptr);
+    p = nullptr;
+    bytes = 0;
+  }
 };
 
 // Per-ensemble cache of instantiated graphs (see qts_set_graph_replay).
@@ -465,17 +472,20 @@ struct Scratch {
       (void)hipFreeAsync(p, s);
     }
   }
-  // False: another call is being issued with the workspace.
+  // False: another call is being issued with the workspace, or there is no
+  // memory for its size (rounded up: the call's own may still fit).
   bool take(Workspace& w, size_t bytes) {
     std::lock_guard<std::mutex> lock(w.mu);
     if (w.busy) return false;
     if (w.bytes < bytes) {
-      if (w.p) check_hip(hipFree(w.p), "hipFree");  // waits for the calls that use it
-      w.p = nullptr;
-      w.bytes = 0;
+      w.release();  // after the calls that use it
       size_t n = (size_t)1 << 20;
       while (n < bytes) n *= 2;
-      check_hip(device_alloc(&w.p, n, nullptr, false), "hipMalloc");
+      if (device_alloc(&w.p, n, nullptr, true) != hipSuccess) {
+        (void)hipGetLastError();
+        w.p = nullptr;
+        return false;
+      }
       w.bytes = n;
     }
     w.busy = true;
@@ -1211,9 +1221,16 @@ int qts_free_ensemble(qts_ensemble* ens) {
       release_graph_cache(ens->graphs);
     }
     if (ens->on_device) {
+      if (ens->work.p) {
+        // the default stream is the current device's
+        int cur = -1;
+        (void)hipGetDevice(&cur);
+        if (cur != ens->dev.device) (void)hipSetDevice(ens->dev.device);
+        ens->work.release();
+        if (cur != ens->dev.device) (void)hipSetDevice(cur);
+      }
       free_dfs(ens->dfs);
       free_device(ens->dev);
-      if (ens->work.p) (void)hipFree(ens->work.p);
     }
     delete ens;
   });
