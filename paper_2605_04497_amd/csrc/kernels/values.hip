@@ -1009,7 +1009,7 @@ __device__ __forceinline__ void values_rows_long(
     const float* __restrict__ lo, const float* __restrict__ hi, const T* __restrict__ bb,
     const T* __restrict__ cbb, const Slot0<T>* __restrict__ z0,
     const int32_t* __restrict__ share, const float* xs, double* as, int pb, int pe, int wave,
-    int nw, int lane, const T* tv, const NodeConsts<T>& nc) {
+    int nw, int lane, const T* tv, const T* wv) {
   constexpr int NB = DMAX / 8;
   constexpr bool kKeep = NH == NN;
   const int run = (pe - pb + nw - 1) / nw;
@@ -1085,7 +1085,7 @@ __device__ __forceinline__ void values_rows_long(
       // checkpoints, recomputed from the first batch whose slots are not all
       // shared with the previous row
 #pragma unroll
-      for (int m = 0; m < NH; ++m) ck[0][m] = nc.w[m0 + m];
+      for (int m = 0; m < NH; ++m) ck[0][m] = wv[m0 + m];
       bool fresh = !kKeep;
 #pragma unroll
       for (int b = 1; b < NB; ++b) {
@@ -1260,15 +1260,15 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
   const int item = xcd_item((int)blockIdx.x, (int)gridDim.x);
   const int sb = item % nsb;
   const int ch = item / nsb;
-  const int64_t s0 = (int64_t)sb * kSamplesPerBlock;
-  const ItemRows ir = item_rows(segs, seg_feat, ch, path_begin, path_end, chunk, F, bx);
-  const int nf = ir.nf;
+  int64_t s0 = (int64_t)sb * kSamplesPerBlock;
+  ItemRows ir = item_rows(segs, seg_feat, ch, path_begin, path_end, chunk, F, bx);
+  int nf = ir.nf;
 
   // stage the sample tile transposed; zero the accumulator; note any NaN.
   // With segments (wide feature spaces) X is feature-major [F][ldx] and acc
   // [ng][F][M], so consecutive threads take consecutive samples of a feature.
   const bool fmajor = segs != nullptr;
-  const int tile = kSamplesPerBlock * nf;
+  int tile = kSamplesPerBlock * nf;
   int nan_seen = 0;
   if (fmajor) {
     for (int i = threadIdx.x; i < tile; i += blockDim.x) {
@@ -1292,6 +1292,23 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
   }
   const bool any_nan = __syncthreads_or(nan_seen) != 0;
 
+  // The FP64 walk of long rows has no scalar registers to spare: what only the flush
+  // needs waits in vector registers, and the weights of up to 16 slots do
+  // (32 slots and more: no vector registers).  Otherwise each row reads spilled
+  // ones back: 100 trees of up to 14 features, 10k rows, FP64 8.87 ms, 8.64
+  // here; up to 32 features, 4000 rows 7.94, 7.80.
+  constexpr bool kPark = DMAX > 8 && WALK == kPerRow && sizeof(T) == 8;
+  uint32_t parked[kPark ? 5 : 1];
+  if constexpr (kPark) {
+    const uint64_t fmap = reinterpret_cast<uint64_t>(ir.fmap);
+    parked[0] = (uint32_t)nf;
+    parked[1] = (uint32_t)ir.grp;
+    parked[2] = (uint32_t)sb;
+    parked[3] = (uint32_t)fmap;
+    parked[4] = (uint32_t)(fmap >> 32);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) asm volatile("" : "+v"(parked[i]));
+  }
   const int lane = threadIdx.x & 63;
   // wave-uniform loop bounds (kept in SGPRs so the path loads are scalar)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1304,6 +1321,10 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
   T tv[NN];
 #pragma unroll
   for (int m = 0; m < NN; ++m) tv[m] = to_vgpr(nc.t[m]);
+  T wv[NN];
+#pragma unroll
+  for (int m = 0; m < NN; ++m)
+    wv[m] = DMAX == 16 && sizeof(T) == 8 ? to_vgpr(nc.w[m]) : nc.w[m];
 
   if constexpr (DMAX == 8 && WALK < kPerRow) {
     if (any_nan)
@@ -1328,12 +1349,21 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
                                                        wave, nw, lane, tv, nc);
   } else if (any_nan) {
     values_rows_long<T, DMAX, NH, STORE_G, true, NN>(hdr, feat, lo, hi, bb, cbb, z0, share, xs,
-                                                     as, pb, pe, wave, nw, lane, tv, nc);
+                                                     as, pb, pe, wave, nw, lane, tv, wv);
   } else {
     values_rows_long<T, DMAX, NH, STORE_G, false, NN>(hdr, feat, lo, hi, bb, cbb, z0, share, xs,
-                                                      as, pb, pe, wave, nw, lane, tv, nc);
+                                                      as, pb, pe, wave, nw, lane, tv, wv);
   }
   __syncthreads();
+  if constexpr (kPark) {
+    nf = (int)__builtin_amdgcn_readfirstlane(parked[0]);
+    tile = kSamplesPerBlock * nf;
+    ir.grp = (int)__builtin_amdgcn_readfirstlane(parked[1]);
+    s0 = (int64_t)(int)__builtin_amdgcn_readfirstlane(parked[2]) * kSamplesPerBlock;
+    ir.fmap = reinterpret_cast<const int32_t*>(
+        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(parked[3]) |
+        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(parked[4]) << 32);
+  }
 
   // flush: consecutive threads take consecutive features of one sample.
   // direct: this workgroup is the only one of its sample block (one bucket,
