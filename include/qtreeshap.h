@@ -280,10 +280,13 @@ int qts_shap_backward(const qts_ensemble* ens, const float* X, int64_t M, int64_
  * [64, 262144]; interactions on at most 256 of them) and keeps the fastest for
  * this ensemble and precision:
  *   first-order kernel, and separately the adjoint kernel (upstream
- *     gradient uniform in [-3, 3)), per length bucket: wavefronts per
- *     workgroup {4, 6, 8} x target work items {4096 .. 65536};
+ *     gradient uniform in [-3, 3)), per length bucket (over all outputs, as a
+ *     call launches it): wavefronts per workgroup {4, 6, 8} x target work
+ *     items {4096 .. 65536};
  *   interactions, per capacity class: largest path chunk {8192, 32768,
  *     131072} x least work items {1024, 4096}.
+ * A shape is kept where it is at least 2 % faster than the choice that an
+ * untuned call makes by itself from its row count; otherwise that choice stays.
  * First-order and adjoint shapes are kept per node policy and tuned for the
  * policy in effect (qts_set_node_policy).
  * Synchronises `stream`; drops the ensemble's cached graphs.  Optional:
@@ -299,13 +302,16 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
  * kernel kind, precision and node policy, the feature and output counts, the
  * bucket or class (capacity, output group, rows) and the size class of
  * M_hint; a file that cannot be written still serves hits.  Lines are
- * "<key> -> a b"; later lines win. */
+ * "<key> -> a b"; later lines win.  Where the untuned choice stays, a is 0
+ * (first order, adjoint) or negative (interactions). */
 int qts_set_tune_cache(const char* path);
 /* Cache lookups since the last qts_set_tune_cache: hits and misses. */
 int qts_tune_cache_stats(int64_t* hits, int64_t* misses);
 
-/* The launch shape in use (first order and adjoint: for the node policy in
- * effect): kind 0 = first-order bucket `index`, kind 2 =
+/* The launch shape in use, or where an untuned call's own choice is in force a
+ * nominal one: the defaults, or for interactions after qts_autotune the fastest
+ * of the timed shapes (first order and adjoint: for the node policy in effect).
+ * kind 0 = first-order bucket `index`, kind 2 =
  * adjoint bucket `index` (0..3 for lengths <= 8, 16, 32, 64) -> (*a, *b) =
  * (wavefronts per workgroup, target work items); kind 1 = interactions
  * capacity class `index` (0 .. n_pair_classes-1) -> (largest path chunk,

@@ -120,22 +120,6 @@ thread_local std::string g_last_error;
 
 int cap_index(int dmax) { return dmax <= 8 ? 0 : dmax <= 16 ? 1 : dmax <= 32 ? 2 : 3; }
 
-// The bucket with the most rows of each capacity (launch shapes are kept per
-// capacity; with output groups several buckets share one).
-std::vector<Bucket> largest_per_capacity(const std::vector<Bucket>& bks) {
-  std::vector<Bucket> out;
-  for (const Bucket& bk : bks) {
-    bool done = false;
-    for (Bucket& o : out)
-      if (o.dmax == bk.dmax) {
-        if (bk.path_end - bk.path_begin > o.path_end - o.path_begin) o = bk;
-        done = true;
-      }
-    if (!done) out.push_back(bk);
-  }
-  return out;
-}
-
 template <class Fn>
 int guarded(Fn&& fn) {
   try {
@@ -1636,6 +1620,9 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
     // real count matters)
     const int64_t Mt = std::max<int64_t>(64, std::min<int64_t>(M_hint > 0 ? M_hint : 16384,
                                                                262144));
+    // a fixed shape takes the place of the launch's own rule where its time is
+    // under this share of the rule's (what timings of one shape differ by)
+    constexpr float kTuneGain = 0.98f;
     // tuning cache key parts: the device, and the row count's size class
     std::string device;
     {
@@ -1679,39 +1666,51 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
       return ms / reps;
     };
 
-    // first-order kernel (its shapes also serve the adjoint), per bucket
-    {
-      Scratch acc(sizeof(double) * (size_t)(Mt * K * F), s);
-      launch_fill_zero((double*)acc.p, Mt * K * F, s);
-      const std::vector<Bucket>& bks = ens->merge_siblings ? h.mbuckets : h.buckets;
-      const PathArrays arr = ens->merge_siblings ? merged_arrays(d, h) : plain_arrays(d, h);
-      Scratch slot0(slot0_bytes(value_rows(ens), fp64), s);
-      launch_slot0(arr, value_rows(ens), d.leaf_val, fp64, slot0.p, s);
-      for (const Bucket& bk : largest_per_capacity(bks)) {
-        const std::string key = tune_key(device, "values", fp64, pol, h, bk.dmax, bk.group,
-                                         bk.path_end - bk.path_begin, m_class);
+    // one first-order or adjoint kernel, per capacity: the launches that a call
+    // makes, over all outputs' buckets, with the launch's own rule first; a
+    // fixed shape is kept where it is faster by more than timing differs
+    // (cache entry "0 0": the rule)
+    const std::vector<BucketSpan> spans =
+        bucket_spans(ens->merge_siblings ? h.mbuckets : h.buckets, false);
+    const PathArrays arr = ens->merge_siblings ? merged_arrays(d, h) : plain_arrays(d, h);
+    auto tune_spans = [&](const char* kind, ValuesShape* shapes, auto&& launch) {
+      for (const BucketSpan& sp : spans) {
+        const std::string key = tune_key(device, kind, fp64, pol, h, sp.dmax(), sp.list[0].group,
+                                         sp.path_end() - sp.path_begin(), m_class);
         ValuesShape best;
-        if (!tune_cache_get(key, &best.waves_per_block, &best.items)) {
+        int a = 0, b = 0;
+        if (tune_cache_get(key, &a, &b)) {
+          if (a > 0) best = ValuesShape{a, b, true};
+        } else {
+          float rule_ms = time_ms(3, [&] { launch(sp, ValuesShape{}); });
           float best_ms = 1e30f;
           for (int waves : {4, 6, 8})
             for (int items : {4096, 8192, 16384, 32768, 65536}) {
               const ValuesShape cand{waves, items, true};
-              const float ms = time_ms(3, [&] {
-                launch_values(h, d, arr, BucketSpan{&bk, 1, 0}, fp64, X, Mt, ldt, slot0.p, (double*)acc.p, nullptr,
-                              cand, nodes_of(ens), s);
-              });
+              const float ms = time_ms(3, [&] { launch(sp, cand); });
               if (ms < best_ms) {
                 best_ms = ms;
                 best = cand;
               }
             }
-          tune_cache_put(key, best.waves_per_block, best.items);
+          rule_ms = std::min(rule_ms, time_ms(3, [&] { launch(sp, ValuesShape{}); }));
+          if (best_ms >= kTuneGain * rule_ms) best = ValuesShape{};
+          tune_cache_put(key, best.tuned ? best.waves_per_block : 0, best.tuned ? best.items : 0);
         }
-        best.tuned = true;
-        ens->vshape[pol][pi][cap_index(bk.dmax)] = best;
+        shapes[cap_index(sp.dmax())] = best;
       }
+    };
+    {
+      Scratch acc(sizeof(double) * (size_t)(Mt * K * F), s);
+      launch_fill_zero((double*)acc.p, Mt * K * F, s);
+      Scratch slot0(slot0_bytes(value_rows(ens), fp64), s);
+      launch_slot0(arr, value_rows(ens), d.leaf_val, fp64, slot0.p, s);
+      tune_spans("values", ens->vshape[pol][pi], [&](const BucketSpan& sp, const ValuesShape& sh) {
+        launch_values(h, d, arr, sp, fp64, X, Mt, ldt, slot0.p, (double*)acc.p, nullptr, sh,
+                      nodes_of(ens), s);
+      });
     }
-    // adjoint kernel, per bucket, with a synthetic upstream gradient
+    // the adjoint, with a synthetic upstream gradient
     {
       Scratch gl(sizeof(double) * (size_t)std::max<size_t>(1, h.leaf_value.size()), s);
       Scratch g32(sizeof(float) * (size_t)(Mt * K * F), s);
@@ -1720,31 +1719,11 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
       if (fp64) launch_widen_f32_f64((const float*)g32.p, (double*)g64.p, Mt * K * F, s);
       const void* G = fp64 ? g64.p : g32.p;
       launch_fill_zero((double*)gl.p, (int64_t)h.leaf_value.size(), s);
-      const std::vector<Bucket>& bks = ens->merge_siblings ? h.mbuckets : h.buckets;
-      const PathArrays arr = ens->merge_siblings ? merged_arrays(d, h) : plain_arrays(d, h);
-      for (const Bucket& bk : largest_per_capacity(bks)) {
-        const std::string key = tune_key(device, "adjoint", fp64, pol, h, bk.dmax, bk.group,
-                                         bk.path_end - bk.path_begin, m_class);
-        ValuesShape best;
-        if (!tune_cache_get(key, &best.waves_per_block, &best.items)) {
-          float best_ms = 1e30f;
-          for (int waves : {4, 6, 8})
-            for (int items : {4096, 8192, 16384, 32768, 65536}) {
-              const ValuesShape cand{waves, items, true};
-              const float ms = time_ms(3, [&] {
-                launch_adjoint(h, d, arr, BucketSpan{&bk, 1, 0}, fp64, X, G, Mt, ldt, (double*)gl.p, cand,
-                               nodes_of(ens), s);
-              });
-              if (ms < best_ms) {
-                best_ms = ms;
-                best = cand;
-              }
-            }
-          tune_cache_put(key, best.waves_per_block, best.items);
-        }
-        best.tuned = true;
-        ens->ashape[pol][pi][cap_index(bk.dmax)] = best;
-      }
+      tune_spans("adjoint", ens->ashape[pol][pi],
+                 [&](const BucketSpan& sp, const ValuesShape& sh) {
+                   launch_adjoint(h, d, arr, sp, fp64, X, G, Mt, ldt, (double*)gl.p, sh,
+                                  nodes_of(ens), s);
+                 });
     }
     // interactions, per capacity class, on at most 256 of the rows (and an
     // accumulator of at most 512 MiB)
@@ -1762,24 +1741,34 @@ int qts_autotune(qts_ensemble* ens, int64_t M_hint, qts_precision precision, voi
         const PairClass& pc = ens->pair_classes[i];
         const std::string key = tune_key(device, "pairs", fp64, pol, h, pc.cap, pc.group, pc.np,
                                          m_class);
+        // the fastest fixed shape, in force where it is faster than the launch's
+        // own rule (cache entry with a negative chunk: the rule is)
         PairShape best;
-        if (!tune_cache_get(key, &best.max_chunk, &best.fill)) {
+        int ca = 0, cb = 0;
+        if (tune_cache_get(key, &ca, &cb)) {
+          best = PairShape{std::abs(ca), cb, ca > 0};
+        } else {
+          auto time_shape = [&](const PairShape& sh) {
+            return time_ms(1, [&] {
+              launch_pairs(h, d, pc, fp64, X, Mp, F, d.leaf_val, tri64, phi64, sh,
+                           ens->node_policy == QTS_NODES_EXACT, s);
+            });
+          };
+          float rule_ms = time_shape(PairShape{});
           float best_ms = 1e30f;
           for (int max_chunk : {8192, 32768, 131072})
             for (int fill : {1024, 4096}) {
               const PairShape cand{max_chunk, fill, true};
-              const float ms = time_ms(1, [&] {
-                launch_pairs(h, d, pc, fp64, X, Mp, F, d.leaf_val, tri64, phi64, cand,
-                             ens->node_policy == QTS_NODES_EXACT, s);
-              });
+              const float ms = time_shape(cand);
               if (ms < best_ms) {
                 best_ms = ms;
                 best = cand;
               }
             }
-          tune_cache_put(key, best.max_chunk, best.fill);
+          rule_ms = std::min(rule_ms, time_shape(PairShape{}));
+          best.tuned = best_ms < kTuneGain * rule_ms;
+          tune_cache_put(key, best.tuned ? best.max_chunk : -best.max_chunk, best.fill);
         }
-        best.tuned = true;
         out[i] = best;
       }
       // QTS_PAIRS_AUTO: time a whole interactions pass both ways on the same

@@ -1106,9 +1106,10 @@ std::vector<std::pair<int, int>> row_ranges(int F, size_t budget) {
 // with two, 2.89 with the one chosen here (two rounds of 256 workgroups).
 int pair_chunk(int np, int64_t M, const PairShape& shape, const void* fn, int threads, int step,
                size_t lds, int64_t* n_chunks_out) {
-  const int64_t max_chunk = std::max(1024, shape.max_chunk);
+  const PairShape sh = shape.tuned ? shape : PairShape{};
+  const int64_t max_chunk = std::max(1024, sh.max_chunk);
   const int64_t least = std::max<int64_t>(1, (np + max_chunk - 1) / max_chunk);
-  const int64_t fill = (std::max(1, shape.fill) + M - 1) / M;
+  const int64_t fill = (std::max(1, sh.fill) + M - 1) / M;
   const int64_t most = std::max(least, std::min<int64_t>(fill, (np + 1023) / 1024));
   int64_t n_chunks = most;
   if (!shape.tuned) {

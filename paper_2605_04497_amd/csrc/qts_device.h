@@ -250,7 +250,7 @@ struct Slot0 {
 struct ValuesShape {
   int waves_per_block = 8;  // wavefronts sharing one 64-sample tile
   int items = 16384;        // target number of (sample block, path chunk) work items
-  bool tuned = false;       // false: resident_waves chooses the wavefronts at launch
+  bool tuned = false;       // false: chosen at launch (resident_waves, chunk_by_rounds)
 };
 
 // The buckets of one launch: n consecutive buckets of one capacity (one per
@@ -269,7 +269,7 @@ std::vector<BucketSpan> bucket_spans(const std::vector<Bucket>& bks, bool one_ea
 struct PairShape {
   int max_chunk = 65536;  // most paths per (sample, chunk) work item
   int fill = 2048;        // least work items when there are few samples
-  bool tuned = false;     // timed on this ensemble
+  bool tuned = false;     // false: chosen at launch (pair_chunk), within the defaults above
 };
 
 inline size_t values_lds_bytes(int F) {
