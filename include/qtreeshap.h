@@ -330,8 +330,10 @@ int qts_get_launch_shape(const qts_ensemble* ens, int32_t kind, qts_precision pr
  * kernel walks one path per such pair, carrying that combined factor (built
  * in FP64 from the current leaf values) and a leaf value of 1: the same
  * result up to rounding, with about half the work on full trees.  The
- * interactions and adjoint calls always walk every path.  Changing the
- * setting drops the ensemble's cached graphs. */
+ * adjoint walks the same pairs; the interactions calls have a table of their
+ * own.  Changing the setting drops the ensemble's cached graphs; turning
+ * merging off for the first time builds the plain rows' FP64 tables on the
+ * ensemble's device (760 bytes per path of at most 8 features). */
 int qts_set_sibling_merge(qts_ensemble* ens, int32_t enable);
 
 /* Deterministic first-order and adjoint results (off by default).  phi and

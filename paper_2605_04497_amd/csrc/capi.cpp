@@ -290,20 +290,31 @@ std::vector<ShortRow<T>> short_rows(const std::vector<PathHdr>& hdr,
   return out;
 }
 
-// Allocate the grouped walk's tables for n short rows.
-void short_walk(size_t n, hipStream_t s, ShortWalk& w) {
-  if (n == 0) return;
-  auto alloc = [&](size_t bytes) {
-    void* p = nullptr;
-    const hipError_t e = device_alloc(&p, bytes, s, false);
-    if (e != hipSuccess) {
-      (void)hipStreamSynchronize(s);  // earlier uploads may still read host vectors
-      check_hip(e, "hipMalloc");
-    }
-    return p;
-  };
-  w.rows = (WalkRow*)alloc(n * sizeof(WalkRow));
-  w.coef = (double*)alloc(n * kShortCoef * sizeof(double));
+// The grouped walk's tables of the merged or the plain first-order table: 760
+// bytes a row (371k rows in the two tables of 1000 trees of depth 8: 282 MB), so
+// only the table in use has them, built at load (merged) or when merging is
+// turned off.  Waits for the stream.
+void build_short_walk(DeviceTable& d, const HostTable& h, bool merged, hipStream_t s) {
+  ShortWalk& w = merged ? d.mwalk : d.walk;
+  const std::vector<Bucket>& bks = merged ? h.mbuckets : h.buckets;
+  size_t n = 0;
+  for (const Bucket& bk : bks)
+    if (bk.dmax == 8) n += (size_t)(bk.path_end - bk.path_begin);
+  if (n == 0 || w.coef != nullptr) return;
+  try {
+    check_hip(device_alloc((void**)&w.rows, n * sizeof(WalkRow), s, false), "hipMalloc");
+    check_hip(device_alloc((void**)&w.coef, n * kShortCoef * sizeof(double), s, false),
+              "hipMalloc");
+    const PathArrays a = merged ? merged_arrays(d, h) : plain_arrays(d, h);
+    for (const Bucket& bk : bks) launch_short_walk(a, bk, d.n64, s);
+    check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
+  } catch (...) {
+    (void)hipStreamSynchronize(s);  // earlier uploads may still read host vectors
+    if (w.rows) (void)hipFree(w.rows);
+    if (w.coef) (void)hipFree(w.coef);
+    w = ShortWalk{};
+    throw;
+  }
 }
 
 void keep_trees(const qts_tree_arrays& t, qts_ensemble::Trees& k) {
@@ -479,6 +490,34 @@ struct Scratch {
   }
   Scratch(const Scratch&) = delete;
   Scratch& operator=(const Scratch&) = delete;
+};
+
+// A stream of the ensemble's device for work that a setter does and waits for.
+// Relaxed capture mode: it neither joins nor breaks a capture under way.
+struct SetupStream {
+  hipStream_t s = nullptr;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  int before = -1;
+  explicit SetupStream(int device) {
+    check_hip(hipGetDevice(&before), "hipGetDevice");
+    check_hip(hipSetDevice(device), "hipSetDevice");
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    const hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    if (e != hipSuccess) {
+      restore();
+      check_hip(e, "hipStreamCreateWithFlags");
+    }
+  }
+  ~SetupStream() {
+    (void)hipStreamDestroy(s);
+    restore();
+  }
+  void restore() {
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipSetDevice(before);
+  }
+  SetupStream(const SetupStream&) = delete;
+  SetupStream& operator=(const SetupStream&) = delete;
 };
 
 // Optional event timing of the main kernels (see qts_set_kernel_timing).
@@ -1135,11 +1174,7 @@ int qts_load_ensemble_grouped(const qts_tree_arrays* trees, const int32_t* tree_
         d.srow64 = upload(r64, s);
         d.msrow32 = upload(m32, s);
         d.msrow64 = upload(m64, s);
-        short_walk(r64.size(), s, d.walk);
-        short_walk(m64.size(), s, d.mwalk);
-        const PathArrays plain = plain_arrays(d, h), merged = merged_arrays(d, h);
-        for (const Bucket& bk : h.buckets) launch_short_walk(plain, bk, d.n64, s);
-        for (const Bucket& bk : h.mbuckets) launch_short_walk(merged, bk, d.n64, s);
+        build_short_walk(d, h, true, s);
         check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
       }
       d.leaf_val = upload(h.leaf_value, s);
@@ -1556,6 +1591,10 @@ int qts_set_sibling_merge(qts_ensemble* ens, int32_t enable) {
   return guarded([&] {
     if (!ens) fail(QTS_E_INVALID_ARG, "null ensemble");
     std::lock_guard<std::mutex> lock(ens->graphs.mu);
+    if (enable == 0 && ens->on_device) {
+      const SetupStream setup(ens->dev.device);
+      build_short_walk(ens->dev, ens->host, false, setup.s);
+    }
     if (ens->merge_siblings != (enable != 0)) clear_graphs(ens->graphs);
     ens->merge_siblings = enable != 0;
   });

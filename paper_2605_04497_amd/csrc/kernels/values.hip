@@ -2219,13 +2219,17 @@ short_walk_kernel(const ShortRow<double>* __restrict__ rows, const PathHdr* __re
 
 void launch_short_walk(const PathArrays& a, const Bucket& bk, const NodeConsts<double>& nc,
                        hipStream_t s) {
-  const int32_t n = bk.path_end - bk.path_begin;
-  if (bk.dmax != 8 || n <= 0) return;
-  const unsigned grid = (unsigned)(((int64_t)n * 64 + 255) / 256);
-  hipLaunchKernelGGL(short_walk_kernel, dim3(grid), dim3(256), 0, s, a.srow64 + bk.srow_begin,
-                     a.hdr + bk.path_begin, a.side, n, bk.top, nc, a.walk.rows + bk.srow_begin,
-                     a.walk.coef + (int64_t)bk.srow_begin * kShortCoef);
-  check_hip(hipGetLastError(), "short_walk_kernel launch");
+  if (bk.dmax != 8) return;
+  constexpr int32_t kRows = 1 << 24;  // a launch's: 2^30 threads
+  for (int32_t p = bk.path_begin; p < bk.path_end;) {
+    const int32_t n = std::min(bk.path_end - p, kRows);
+    const int64_t r = (int64_t)bk.srow_begin + (p - bk.path_begin);
+    const unsigned grid = (unsigned)(((int64_t)n * 64 + 255) / 256);
+    hipLaunchKernelGGL(short_walk_kernel, dim3(grid), dim3(256), 0, s, a.srow64 + r, a.hdr + p,
+                       a.side, n, bk.top, nc, a.walk.rows + r, a.walk.coef + r * kShortCoef);
+    check_hip(hipGetLastError(), "short_walk_kernel launch");
+    p += n;
+  }
 }
 
 // First order of a few samples over rows of at most 8 features: a lane takes a
