@@ -194,6 +194,8 @@ int qts_gauss_legendre(int32_t n, double* t, double* one_minus_t, double* weight
  *   X            [M, ldx] float32 device rows (ldx >= F); NaN = missing.
  *   leaf_values  NULL, or [n_leaves] FP64 device array replacing the model's leaf
  *                values (phi is linear in them; used by the autograd wrapper).
+ *                In FP32, paths of more than 8 features then take another walk
+ *                (slower, other rounding) than with NULL.
  *   phi          [M, F] device output: float32 for QTS_FP32, double for QTS_FP64
  *                ([M, n_groups, F] for a grouped ensemble).
  * QTS_FP32 evaluates the quadrature in FP32 and accumulates across paths and

@@ -172,7 +172,9 @@ class Ensemble:
     def shap_values(self, X: torch.Tensor, precision: str = "fp32", leaf_values=None,
                     out=None) -> torch.Tensor:
         """phi[M, F] ([M, n_groups, F] for a multi-output model); float32 for
-        'fp32', float64 for 'fp64'."""
+        'fp32', float64 for 'fp64'.  With leaf_values, fp32 rounds differently
+        on paths of more than 8 features than with the model's own (and is
+        slower there)."""
         X, M, ldx = self._rows(X)
         lv = self._leaf(leaf_values, X.device)
         shape = self._per_sample(M, self.n_features)

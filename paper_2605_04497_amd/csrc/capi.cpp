@@ -730,7 +730,7 @@ void issue_values(const qts_ensemble* ens, const float* X, int64_t M, int64_t ld
                                              : plain_arrays(ens->dev, ens->host);
   const std::vector<Bucket>& bks = ens->merge_siblings ? h.mbuckets : h.buckets;
   // one launch per capacity, over all output groups (7 outputs, 350 trees of
-  // depth 6, 4099 rows: 340 us with a launch per group, 232 with one)
+  // depth 6, 4099 rows: 321 us with a launch per group, 272 with one)
   const std::vector<BucketSpan> spans = bucket_spans(bks, ens->deterministic);
   bool use_slot0 = false;  // a span whose walk reads the Slot0 records
   auto lane = [&](const BucketSpan& sp) {

@@ -60,7 +60,7 @@ __device__ __forceinline__ bool follows(float x, float lo, float hi, bool mok) {
 }  // namespace
 
 constexpr int kDfsSamples = 8;  // samples per wavefront of the walk (8 lanes each)
-constexpr int kDfsWindow = 64;  // events staged together
+constexpr int kDfsWindow = 64;  // events staged together, one per lane
 
 // LDS of the walk: the sample rows of the workgroup's 8 samples (stride F+1),
 // then per wave the stack [level][64] (where it is in LDS) and the stage of 64
@@ -168,7 +168,7 @@ dfs_walk_kernel(const DfsNode* __restrict__ nodes, const T* __restrict__ coef,
       for (int k = 0; k < kDfsCoef; ++k) se.coef[k] = coef[(size_t)r * kDfsCoef + k];
       se.lv[0] = lvals[2 * (size_t)r];
       se.lv[1] = lvals[2 * (size_t)r + 1];
-      if (kDfsWindow == 64 || lane < kDfsWindow) stage[lane] = se;
+      stage[lane] = se;
       uint32_t bits = 0;
 #pragma unroll
       for (int qq = 0; qq < kDfsSamples; ++qq) {

@@ -872,10 +872,6 @@ triples_kernel(const int32_t* __restrict__ pd, const int32_t* __restrict__ pleaf
   }
 }
 
-// Lane-per-row form of triples_kernel for the short classes (capacity C <= 8):
-// lane = row (slot-major table: a wave's 64 rows load coalesced), the row's
-// factors and ratios in registers, its C(C,3) triples unrolled, with the same
-// H0 form and the same LDS tensor range and flush.
 // One class's rows of the pair table.
 template <typename T>
 struct TripleRows {
@@ -890,6 +886,10 @@ struct TripleRows {
   int32_t np;
 };
 
+// Lane-per-row form of triples_kernel for the short classes (capacity C <= 8):
+// lane = row (slot-major table: a wave's 64 rows load coalesced), the row's
+// factors and ratios in registers, its C(C,3) triples unrolled, with the same
+// H0 form and the same LDS tensor range and flush.
 // Rows [p0, p1) of a class of C slots into the workgroup's tensor range.
 template <typename T, int C>
 __device__ __forceinline__ void triples_rows(const TripleRows<T>& tb, int p0, int p1,
@@ -1018,6 +1018,7 @@ triples_lane_kernel(TripleRows<T> t8, TripleRows<T> t4, int32_t n_chunks,
   }
 }
 
+// out[i] = (float)acc[i]
 __global__ void __launch_bounds__(256)
 narrow_kernel(const double* __restrict__ acc, int64_t n, float* __restrict__ out) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -1402,9 +1403,10 @@ void launch_narrow_f64_f32(const double* acc, int64_t n, float* out, hipStream_t
   check_hip(hipGetLastError(), "narrow_kernel launch");
 }
 
-// The same with the sample's triangle read once into LDS (F up to 200).  Bound
-// by HBM; the walk through memory read each column of the triangle a line per
-// entry: 512 samples of 200 features, FP32, 185 us (0.9 TB/s); 61 us here.
+// pairs_finalize_kernel with the sample's triangle read once into LDS (F up to
+// 200).  Bound by HBM; the walk through memory read each column of the
+// triangle a line per entry: 512 samples of 200 features, FP32, 185 us (0.9
+// TB/s); 61 us here.
 constexpr int kSumParts = 2;  // threads per row sum
 template <typename TO>
 __global__ void __launch_bounds__(1024)

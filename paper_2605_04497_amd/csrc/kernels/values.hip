@@ -152,9 +152,9 @@ struct LeafSums {
   }
 };
 
-// The adjoint's path loop for rows of more than 8 features and for FP64.  NANS:
-// the tile holds a NaN, so the missing-value rule is evaluated; otherwise
-// plain interval tests suffice.  phi is linear in the leaf value, so
+// The adjoint's path loop for rows of more than 8 features, and for FP64 tiles
+// with an infinite gradient.  NANS: the tile holds a NaN, so the missing-value
+// rule is evaluated; otherwise plain interval tests suffice.  phi is linear in the leaf value, so
 // d phi[s, f_j] / d val = c_j LOO_j: each lane gathers g[s, f_j] c_j LOO_j from
 // the upstream-gradient tile gs, and the wave sums its 64 samples in FP64.
 template <typename T, int DMAX, int NH, bool STORE_G, bool NANS, int NN>
@@ -1000,8 +1000,8 @@ __device__ __forceinline__ void values_rows_batched(
 // row's (share[p] = s, from the host), the c_j of the batches of 8 slots that
 // lie within them are still in registers, and so are the prefix checkpoints
 // ck[b] = w prod_{1 <= k < 8b} F_k(m) of the batches b with 8b - 1 <= s (kept
-// across rows when all nodes run in one pass).  The backward sweep is that of values_paths with the suffix
-// products started from slot 0's factor; slot 0's own leave-one-out product
+// across rows when all nodes run in one pass).  The backward sweep is that of
+// adjoint_paths with the suffix products started from slot 0's factor; slot 0's own leave-one-out product
 // is the full prefix over slots 1..d-1 (inert padding slots are factors 1).
 template <typename T, int DMAX, int NH, bool STORE_G, bool NANS, int NN>
 __device__ __forceinline__ void values_rows_long(
@@ -1706,15 +1706,23 @@ __device__ __forceinline__ void adjoint_rows_grouped(
 }
 
 // Adjoint to the leaf values: the tile holds the samples' rows and their
-// upstream gradient rows g[s, :].  A workgroup takes one chunk of rows and
-// every n_groups-th sample block, and keeps the chunk's leaf sums in LDS over
-// all of them, so a leaf costs one global atomic per workgroup instead of one
-// per sample block (whose adds to the same leaves ran one after another in
-// L2).  With the inert slots left out (119 VGPRs instead of 136 at depth 6,
-// four waves per SIMD), four rows' sums folded together over the wave and
-// four wavefronts' worth of registers per SIMD in use, 200 trees of depth 6,
-// 50 features, 20k rows, FP32 take 0.6 ms; 1.6 before.  part_rows = 0: no room
-// for the sums next to the tiles, every row adds to memory.  TOP: the bucket's (capacity 8); FP64 at 8 nodes takes the grouped
+// upstream gradient rows g[s, :].
+// Bound by VALU issue.  200 trees of depth 6, 50 features, 20k rows, FP32: 1.6 ms
+// with every slot of 8 walked, a wave sum per row and eight wavefronts whatever
+// the registers; 0.6 with the inert slots left out (119 VGPRs instead of 136,
+// four waves per SIMD), four rows' sums folded together over the wave, and
+// the wavefronts chosen by the registers.
+// A workgroup takes one chunk of rows and every n_groups-th sample block, and
+// keeps the chunk's leaf sums in LDS over them.  Up to items / kAdjItems pairs
+// of chunk and block (8192 untuned; at the size above there are 25 x 313) that
+// is one block each, and the sums save what the rows' single adds to memory
+// cost over one pass of consecutive leaves: that size, values and adjoint, 1.24
+// ms without them, 1.18 with.  Beyond it a leaf costs one global atomic per
+// workgroup, not one per sample block.  In FP32 at about 150 features the sums
+// take the CU's second workgroup (152 features, 200 trees of depth 6, 20k rows:
+// 2.15 ms, 1.61 without; 3.04 before).
+// part_rows = 0: no room for the sums next to the tiles, every row adds to
+// memory.  TOP: the bucket's (capacity 8); FP64 at 8 nodes takes the grouped
 // walk with it, the others adjoint_rows_shared with ND = TOP + 3.
 // Three waves per SIMD (168 VGPRs) where the instance is within a few
 // registers of them.
@@ -1948,13 +1956,13 @@ ShortWalk walk_of(const PathArrays& a, const BucketSpan& sp) {
 // times that in FP64) and the tile, staged and passed on with FP64 atomics at
 // 270 clocks a feature over 64 samples.  Chunks of 32 rows or more.  Past
 // four rounds a gain of less than a fifth is inside the model's error: then
-// the chunks stay (20000 rows, 200 trees of depth 6, values and adjoint: 1.16
-// ms, 1.19 without this).
-// us a call with chunks of at least 256 rows, with chunks of 32 rows up to
-// 1024 workgroups, and here: 1770 rows, 940 trees of depth 4, 188 features:
-// 165, 178, 103; 606 rows, 938 of depth 3, 114 features: 36, 66, 32; 5537
-// rows, 28 of depth 5, 9 features: 55, 25, 23; 4934 rows, 336 of depth 7, 65
-// features: 488, 488, 440.
+// the chunks stay (20000 rows, 200 trees of depth 6, values and adjoint: 1.17
+// ms, 1.20 without this; 8267 rows, 912 of depth 7, 11 features, values: 1.89 and
+// 1.86).
+// FP32, us a call with chunks of at least 256 rows, and here: 1770 rows, 940
+// trees of depth 4, 188 features: 155, 102; 606 rows, 938 of depth 3, 114
+// features: 42, 37; 5537 rows, 28 of depth 5, 9 features: 50, 24; 4934 rows, 336
+// of depth 7, 65 features: 510, 476.
 int chunk_by_rounds(const BucketSpan& sp, int nsb, int F, bool fp64, int groups, int chunk0) {
   const int64_t rows = sp.path_end() - sp.path_begin();
   const int64_t slots = (int64_t)256 * groups;
@@ -2040,9 +2048,9 @@ void launch_one(const HostTable& h, const DeviceTable& d, const PathArrays& a,
 
 // A workgroup's chunk is at most kAdjRows rows (their leaf sums in LDS, next to
 // the tiles), and the sample blocks are dealt to about items / kAdjItems
-// workgroups in all, so that a chunk's sums go to memory once for several
-// blocks (200 trees of depth 6, 20k rows, values and adjoint: 1.17 ms with
-// 2, 1.19 with 8, 1.20 with 32).
+// workgroups in all: more than that many take several blocks each.  (200 trees
+// of depth 6, 20k rows, values and adjoint: 1.17 ms with 2, where each of 7825
+// takes one block; 1.19 and 1.20 with 8 and 32, where they take 4 and 16.)
 constexpr int kAdjRows = 512;
 constexpr int kAdjItems = 2;
 
@@ -2367,9 +2375,9 @@ values_lane_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ 
 
 // The lane kernel's time grows with samples x rows, the others' hardly with up
 // to 64 samples.  Microseconds a call (samples in lanes | rows in lanes):
-//   1000 trees of depth 8 (128k rows), FP32: 1 sample 62 | 17, 8: 64 | 57,
-//   16: 66 | 77; FP64: 1: 119 | 16, 16: 124 | 124;
-//   500 trees of depth 6 (16k rows), FP32: 1: 24 | 18, 32: 25 | 20, 48: 26 | 25.
+//   1000 trees of depth 8 (128k rows), FP32: 1 sample 64 | 19, 8: 66 | 58,
+//   12: 67 | 69, 16: 66 | 82; FP64: 1: 119 | 19, 12: 120 | 101, 16: 120 | 129;
+//   500 trees of depth 6 (16k rows), FP32: 1: 26 | 17, 32: 29 | 24, 48: 30 | 29.
 bool values_lane(const BucketSpan& sp, int64_t M, int F, int nodes) {
   const int64_t rows = sp.path_end() - sp.path_begin();
   return sp.dmax() == 8 && nodes == 8 && (M <= 12 || (M <= 64 && M * rows <= (int64_t)1 << 19)) &&

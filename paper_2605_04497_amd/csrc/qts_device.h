@@ -402,8 +402,8 @@ size_t raise_lds_limit(const void* fn);
 // wavefronts of fn resident on a CU, given its VGPRs and `lds` bytes per
 // workgroup; the larger workgroup on a tie (it stages its tiles for more
 // wavefronts).  FP32, 8, 6 and 4 wavefronts, us: 4934 rows, 336 trees of depth
-// 7, 65 features (LDS for 3 workgroups) 488, 598, 528; 8267 rows, 912 of depth
-// 7, 11 features (VGPRs for 20 wavefronts) 2692, 3379, 2310.
+// 7, 65 features (LDS for 3 workgroups) 476, 710, 530; 5537 rows, 28 of depth 5,
+// 9 features (VGPRs for 20 wavefronts) 24.4, 28.3, 23.9.
 int resident_waves(const void* fn, size_t lds);
 // Workgroups of fn resident on a CU.
 int resident_groups(const void* fn, int threads, size_t lds);
