@@ -815,11 +815,11 @@ __device__ __forceinline__ void values_rows_grouped(
 // node_sums4.
 // Hs is in FP64: a run may be as long as a subtree has rows, and FP32 sums of
 // 4000 like rows lose 2e-5.  Its node sums are FP32's, of the sum rounded once.
-// Batches of 8: 148 VGPRs at 32 slots, three waves per SIMD (64 slots: 256 and
-// 88 bytes of scratch).  100 trees of up to 32 features and 512 leaves, 10k
-// rows: 7.3 ms, 6.3 with FP32 sums (99 VGPRs, four waves); 12.2 by the suffix
-// products per row and slot that this replaces.  Batches of 4 evaluate fewer
-// shared slots again but keep twice the state (10.6 ms already with FP32 sums).
+// Batches of 8: 148 VGPRs at 32 slots, held to 128 (64 slots: 256 and 88 bytes
+// of scratch).  100 trees of up to 32 features and 512 leaves, 10k rows: 7.1
+// ms, 6.3 with FP32 sums (99 VGPRs); 12.1 by the suffix products per row and
+// slot that this replaces.  Batches of 4 evaluate fewer shared slots again but
+// keep twice the state (10.6 ms already with FP32 sums).
 template <int DMAX, bool NANS>
 __device__ __forceinline__ void values_rows_batched(
     const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
@@ -1236,8 +1236,10 @@ __device__ __forceinline__ ItemRows item_rows(const Segment* segs, const int32_t
 // for kBatched.
 constexpr int kPerRow = 16, kBatched = -2;
 
+// (values_rows_batched at 32 slots: four waves per SIMD with 68 bytes of
+// scratch, 7.12 ms, against three with none, 7.38: the case named there.)
 template <typename T, int DMAX, int NH, bool STORE_G, int NN, int WALK>
-__global__ void __launch_bounds__(512)
+__global__ void __launch_bounds__(512, WALK == kBatched && DMAX == 32 ? 4 : 2)
 values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
               const float* __restrict__ lo, const float* __restrict__ hi,
               const T* __restrict__ bb, const T* __restrict__ cbb,
