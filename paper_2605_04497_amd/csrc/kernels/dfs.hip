@@ -574,12 +574,15 @@ void walk_t(const HostTable& h, const DeviceDfs& d, const NodeConsts<T>& nc,
   }
   const size_t limit = raise_lds_limit((const void*)dfs_walk_kernel<T>);
   // as many waves (trees) per workgroup as the LDS allows, up to 16: the walk
-  // is bound by the latency of its sequential steps, which more waves hide
-  int waves = 16;
+  // is bound by the latency of its sequential steps, which more waves hide; but
+  // no more than leave two workgroups per CU (60 trees of up to 20 levels, 64
+  // samples: 480 waves in 30 workgroups FP32 465 us, FP64 553; in 480 331, 401)
+  const int nsg = (mb + kDfsSamples - 1) / kDfsSamples;
+  int waves = (int)std::min<int64_t>(
+      16, std::max<int64_t>(1, (int64_t)nsg * d.n_trees / 512));
   while (waves > 1 && dfs_walk_lds(F, levels, waves, sizeof(T)) > limit) --waves;
   const size_t lds = dfs_walk_lds(F, levels, waves, sizeof(T));
   if (lds > limit) fail(QTS_E_UNSUPPORTED, "internal: tree too deep for the depth-first walk");
-  const int nsg = (mb + kDfsSamples - 1) / kDfsSamples;
   const int n_tb = (d.n_trees + waves - 1) / waves;
   const int64_t grid = (int64_t)nsg * n_tb;
   if (grid <= 0) return;
