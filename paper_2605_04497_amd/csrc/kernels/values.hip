@@ -2002,8 +2002,12 @@ void launch_one(const HostTable& h, const DeviceTable& d, const PathArrays& a,
   // deterministic: one wave per workgroup (no LDS atomics between waves), and
   // one launch per chunk, so each launch has one workgroup per (sample, feature)
   const void* fn = (const void*)values_kernel<T, DMAX, NH, STORE_G, NN, WALK>;
-  const int threads =
-      det ? 64 : 64 * (shape.tuned ? shape.waves_per_block : resident_waves(fn, lds));
+  // direct: a sample block has one workgroup, so up to one round of them more
+  // wavefronts each are more on the chip (20 trees of depth 4, 200 rows, a call:
+  // FP32 36 us with 4, 23 with 8, FP64 45 and 32)
+  const bool one_round = direct != nullptr && nsb <= 256 * resident_groups(fn, 512, lds);
+  const int threads = det ? 64 : 64 * (shape.tuned ? shape.waves_per_block
+                                       : one_round ? 8 : resident_waves(fn, lds));
   // (deterministic: a chunk is a launch; direct: one chunk has all rows)
   if (!det && !shape.tuned && rs.segs == nullptr && direct == nullptr) {
     rs.chunk = chunk_by_rounds(sp, nsb, F, std::is_same<T, double>::value,
