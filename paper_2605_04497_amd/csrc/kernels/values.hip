@@ -1720,11 +1720,9 @@ __device__ __forceinline__ void adjoint_rows_grouped(
 // is one block each, and the sums save what the rows' single adds to memory
 // cost over one pass of consecutive leaves: that size, values and adjoint, 1.24
 // ms without them, 1.18 with.  Beyond it a leaf costs one global atomic per
-// workgroup, not one per sample block.  In FP32 at about 150 features the sums
-// take the CU's second workgroup (152 features, 200 trees of depth 6, 20k rows:
-// 2.15 ms, 1.61 without; 3.04 before).
-// part_rows = 0: no room for the sums next to the tiles, every row adds to
-// memory.  TOP: the bucket's (capacity 8); FP64 at 8 nodes takes the grouped
+// workgroup, not one per sample block.
+// part_rows = 0: the sums would take other wavefronts' room next to the tiles
+// (launch_adj_one); every row adds to memory.  TOP: the bucket's (capacity 8); FP64 at 8 nodes takes the grouped
 // walk with it, the others adjoint_rows_shared with ND = TOP + 3.
 // Three waves per SIMD (168 VGPRs) where the instance is within a few
 // registers of them.
@@ -2095,9 +2093,20 @@ void launch_adj_one(const HostTable& h, const DeviceTable& d, const PathArrays& 
     if (sizeof(T) == 8 && fit >= kSegMaxRows)
       part_rows = kSegMaxRows;
   } else if (fit >= 128) {
-    rs.chunk = std::min({rs.chunk, kAdjRows, fit});
-    rs.n_chunks = n_chunks_of(sp, rs.chunk);
-    part_rows = rs.chunk;
+    // not where their LDS takes wavefronts off the CU.  Values and adjoint, ms
+    // without them and with: FP32, 200 trees of depth 6, 152 features, 20k rows
+    // 1.62, 2.15; 300 of depth 8, 100 features, 5003 rows 2.37, 2.95; FP64, 60
+    // features, 20k rows 14.2, 16.2
+    const int chunk = std::min({rs.chunk, kAdjRows, fit});
+    auto waves_on = [&](size_t bytes) {
+      const int w = shape.tuned ? shape.waves_per_block : resident_waves(fn, bytes);
+      return w * resident_groups(fn, 64 * w, bytes);
+    };
+    if (waves_on(tiles + 2 * (size_t)chunk * sizeof(double)) >= waves_on(tiles)) {
+      rs.chunk = chunk;
+      rs.n_chunks = n_chunks_of(sp, rs.chunk);
+      part_rows = chunk;
+    }
   }
   const int64_t want = std::max(1, shape.items / kAdjItems);
   const int n_groups = part_stride > 0 || part_rows == 0
