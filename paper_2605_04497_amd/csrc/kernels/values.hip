@@ -416,7 +416,12 @@ __device__ __forceinline__ ShortRowRegs<T> load_short_row(const ShortRow<T>* row
 // code; inert padding slots (b = 1, c = 0) give a factor of exactly 1.
 // ND: slots 1..ND of the bucket's rows can be real; the slots past it are inert
 // in every row, and leaving out a factor of exactly 1 changes no bit.
-template <typename T, int NH, int ND, bool NANS>
+// KEEP = false: nothing kept from row to row, so a row is one run of code
+// without branches, which a wavefront alone on its SIMD walks faster
+// (deterministic FP64 calls: 300 trees of depth 8, 100 features, 5003 rows 50.7
+// ms, 59.9 with what is shared kept; 66.3 by values_rows_grouped, whose rows
+// wait for scalar loads of their coefficients).
+template <typename T, int NH, int ND, bool NANS, bool KEEP>
 __device__ __forceinline__ void values_rows_shared(
     const ShortRow<T>* __restrict__ rows, int row0, const Slot0<T>* __restrict__ z0,
     const float* xs, double* as, int pb, int pe, int wave, int nw, int lane, const T* tv,
@@ -454,7 +459,7 @@ __device__ __forceinline__ void values_rows_shared(
     const float hiB = ldu(&z->hi_b);
     const bool mokB = ldu(&z->mok_b) != 0;
     const int d = r.d;
-    const int s = p != p_first ? r.share : 0;
+    const int s = KEEP && p != p_first ? r.share : 0;
     const int mok = r.mok;
     const auto& xo = r.xo;
     const auto& ao = r.ao;
@@ -1232,9 +1237,10 @@ __device__ __forceinline__ ItemRows item_rows(const Segment* segs, const int32_t
 // segments); F: phi's row length.
 // The walk of a first-order instance: values_rows_grouped with TOP = WALK for
 // WALK = 0..4, values_rows_shared with ND = WALK - kPerRow for kPerRow + 3 ..
-// kPerRow + 7 (short rows), values_rows_long for kPerRow, values_rows_batched
+// kPerRow + 7 and, nothing kept, with ND = WALK - kNoKeep for kNoKeep + 3 ..
+// kNoKeep + 7 (short rows), values_rows_long for kPerRow, values_rows_batched
 // for kBatched.
-constexpr int kPerRow = 16, kBatched = -2;
+constexpr int kPerRow = 16, kNoKeep = 32, kBatched = -2;
 
 // (values_rows_batched at 32 slots: four waves per SIMD with 68 bytes of
 // scratch, 7.12 ms, against three with none, 7.38: the case named there.)
@@ -1343,12 +1349,14 @@ values_kernel(const PathHdr* __restrict__ hdr, const int32_t* __restrict__ feat,
       values_rows_batched<DMAX, false>(hdr, feat, lo, hi, bb, cbb, z0, share, xs, as, pb, pe,
                                        wave, nw, lane);
   } else if constexpr (DMAX == 8) {
+    constexpr bool kKeep = WALK < kNoKeep;
+    constexpr int kNd = WALK - (kKeep ? kPerRow : kNoKeep);
     if (any_nan)
-      values_rows_shared<T, NH, WALK - kPerRow, true>(srows, path_begin, z0, xs, as, pb, pe, wave,
-                                                      nw, lane, tv, nc);
+      values_rows_shared<T, NH, kNd, true, kKeep>(srows, path_begin, z0, xs, as, pb, pe, wave, nw,
+                                                  lane, tv, nc);
     else
-      values_rows_shared<T, NH, WALK - kPerRow, false>(srows, path_begin, z0, xs, as, pb, pe,
-                                                       wave, nw, lane, tv, nc);
+      values_rows_shared<T, NH, kNd, false, kKeep>(srows, path_begin, z0, xs, as, pb, pe, wave,
+                                                   nw, lane, tv, nc);
   } else if (any_nan) {
     values_rows_long<T, DMAX, NH, STORE_G, true, NN>(hdr, feat, lo, hi, bb, cbb, z0, share, xs,
                                                      as, pb, pe, wave, nw, lane, tv, wv);
@@ -2516,6 +2524,9 @@ void launch_values(const HostTable& h, const DeviceTable& d, const PathArrays& a
       if (nodes == 4) {
         if (!fp64) go(0.f, QTS_N(8), QTS_N(4), true_type{}, QTS_N(4), walk);
         else go(0.0, QTS_N(8), QTS_N(4), false_type{}, QTS_N(4), walk);
+      } else if (fp64 && deterministic) {
+        go(0.0, QTS_N(8), QTS_N(8), true_type{}, QTS_N(8),
+           QTS_N(kNoKeep + 3 + decltype(top)::value));
       } else if (fp64) {
         go(0.0, QTS_N(8), QTS_N(8), true_type{}, QTS_N(8), top);
       } else {
