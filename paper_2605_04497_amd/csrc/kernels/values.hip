@@ -607,9 +607,11 @@ __device__ __forceinline__ acc_v4 node_sums4(float A, const float (&H)[8], acc_v
 // the root side only those past the shared count are evaluated.
 // (FP32 keeps values_rows_shared: a run's H would be summed in FP32, where
 // every row's term goes into the FP64 accumulator by itself there, and with
-// FP64 sums of H the walk is the slower one: 500 trees of depth 8, 100
-// features, 100k rows, FP32: 23.0 ms with FP32 sums, 24.8 with FP64 sums,
-// values_rows_shared 24.4.)
+// FP64 sums of H the walk is mostly the slower one.  FP32, ms with FP32 sums,
+// with FP64 sums and by values_rows_shared: 500 trees of depth 8, 100 features,
+// 100k rows 23.1, 25.6, 23.7; 500 of depth 6, 50 features, 50k rows 2.53, 3.16,
+// 2.61; 500 of depth 4 0.65, 0.65, 0.58; 1000 of depth 8 grown on data, 100k
+// rows 42.3, 46.7, 49.4.)
 //
 // The row loop is pipelined by hand.  Scalar loads and LDS reads share one
 // wait counter and scalar loads return out of order, so a wait for one is a
