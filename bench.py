@@ -45,8 +45,8 @@ LDS_F64_ATOMIC_RATE = 2.45 * 256 * 2.4e9
 # profiles/values_kernel_c2_values.md.  Valid only for the kernel source they
 # were measured on (its SHA-256 prefix); otherwise traffic is reported as null.
 TRAFFIC = {"kernel_source": "paper_2605_04497_amd/csrc/kernels/values.hip",
-           "sha256_16": "61456a43db1a66e4", "fetch_bytes": 9.3678e+08, "write_bytes": 1.6800e+09,
-           "shape": [8, 32768]}
+           "sha256_16": "fecfe1a7e042081b", "fetch_bytes": 6.0245e+08, "write_bytes": 8.8000e+08,
+           "shape": [8, 16384]}
 
 
 def measured_traffic(shape):
@@ -71,27 +71,27 @@ KERNEL_SOURCES = ("paper_2605_04497_amd/csrc/kernels/values.hip",
                   "paper_2605_04497_amd/csrc/kernels/interactions.hip",
                   "paper_2605_04497_amd/csrc/kernels/dfs.hip",
                   "paper_2605_04497_amd/csrc/kernels/common.hip")
-EXECUTED_FLOPS_SHA = "5421d367ce192d86"
+EXECUTED_FLOPS_SHA = "4dd50fd68e0181a5"
 # (leg, precision) -> (FP32 flops, FP64 flops) per call
 EXECUTED_FLOPS = {
-    ("values", "fp32"): (2.2088e+12, 1.1433e+09),
-    ("values", "fp64"): (3.0889e+08, 2.2295e+12),
-    ("interactions", "fp32"): (1.5295e+12, 5.2878e+09),
-    ("interactions", "fp64"): (1.5499e+07, 2.2244e+12),
-    ("interactions_dfs", "fp32"): (9.6252e+11, 2.4891e+08),
+    ("values", "fp32"): (2.9713e+12, 1.3035e+08),
+    ("values", "fp64"): (3.0889e+08, 2.2285e+12),
+    ("interactions", "fp32"): (1.5298e+12, 5.2113e+09),
+    ("interactions", "fp64"): (1.6548e+07, 2.2250e+12),
+    ("interactions_dfs", "fp32"): (9.6252e+11, 1.7131e+08),
     ("interactions_dfs", "fp64"): (3.7070e+08, 2.0964e+12),
-    ("adjoint", "fp32"): (2.9985e+10, 4.1160e+08),
-    ("adjoint", "fp64"): (1.6019e+07, 2.4037e+10),
-    ("deep_values", "fp32"): (2.3721e+11, 6.0534e+06),
-    ("deep_values", "fp64"): (4.0501e+07, 5.2066e+11),
-    ("deep_interactions", "fp32"): (1.9467e+12, 5.1808e+09),
+    ("adjoint", "fp32"): (2.9997e+10, 3.5917e+08),
+    ("adjoint", "fp64"): (1.6019e+07, 2.3985e+10),
+    ("deep_values", "fp32"): (2.2966e+11, 7.2689e+09),
+    ("deep_values", "fp64"): (4.0180e+07, 5.2064e+11),
+    ("deep_interactions", "fp32"): (1.9467e+12, 5.1763e+09),
     ("deep_interactions", "fp64"): (8.9600e+07, 2.5530e+12),
-    ("deep_interactions_dfs", "fp32"): (3.8001e+11, 2.5019e+08),
+    ("deep_interactions_dfs", "fp32"): (3.8001e+11, 2.4571e+08),
     ("deep_interactions_dfs", "fp64"): (8.6080e+07, 6.8065e+11),
-    ("deep_third_order", "fp32"): (5.7114e+11, 5.0862e+09),
+    ("deep_third_order", "fp32"): (5.7114e+11, 5.0817e+09),
     ("deep_third_order", "fp64"): (1.4541e+08, 6.6197e+11),
-    ("deep_third_order_dfs", "fp32"): (1.8750e+11, 5.7147e+06),
-    ("deep_third_order_dfs", "fp64"): (7.5328e+06, 2.3077e+11),
+    ("deep_third_order_dfs", "fp32"): (1.8750e+11, 1.2347e+06),
+    ("deep_third_order_dfs", "fp64"): (7.5008e+06, 2.3076e+11),
 }
 
 # One call of each leg for the counter runs (`--flop-call LEG:PREC` under
@@ -979,7 +979,7 @@ def main():
                                   "multiplies on vector-register operands issue at up to 1.71 "
                                   "wave instructions per CU per clock in probes on this GPU "
                                   "(2 at this peak), so it applies without packed instructions",
-                     "kernel": "values_kernel (grouped walk of rows of at most 8 features)", "kernel_ms": r32["kernel_ms"],
+                     "kernel": "values_kernel (rows of at most 8 features, prefix and suffix products)", "kernel_ms": r32["kernel_ms"],
                      "kernel_ms_scope": "event pair around each graph replay (zero-fill, "
                                         "values kernel, cast)" if not args.eager else
                                         "event pair around the values kernel launches",
