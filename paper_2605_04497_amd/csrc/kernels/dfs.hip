@@ -575,11 +575,14 @@ void walk_t(const HostTable& h, const DeviceDfs& d, const NodeConsts<T>& nc,
   const size_t limit = raise_lds_limit((const void*)dfs_walk_kernel<T>);
   // as many waves (trees) per workgroup as the LDS allows, up to 16: the walk
   // is bound by the latency of its sequential steps, which more waves hide; but
-  // no more than leave two workgroups per CU (60 trees of up to 20 levels, 64
-  // samples: 480 waves in 30 workgroups FP32 465 us, FP64 553; in 480 331, 401)
+  // no more than leave a workgroup for each of the 256 CUs (60 trees of up to 20
+  // levels, 64 samples: 480 waves in 30 workgroups FP32 465 us, FP64 553; in 480
+  // 331, 401). Two for each would be too many: where the LDS of a CU holds one,
+  // its waves are all that the CU has (500 trees of up to 20 levels, 200
+  // features, 1024 samples, whole call: FP32 111 ms, for two 128; FP64 161, 219)
   const int nsg = (mb + kDfsSamples - 1) / kDfsSamples;
   int waves = (int)std::min<int64_t>(
-      16, std::max<int64_t>(1, (int64_t)nsg * d.n_trees / 512));
+      16, std::max<int64_t>(1, (int64_t)nsg * d.n_trees / 256));
   while (waves > 1 && dfs_walk_lds(F, levels, waves, sizeof(T)) > limit) --waves;
   const size_t lds = dfs_walk_lds(F, levels, waves, sizeof(T));
   if (lds > limit) fail(QTS_E_UNSUPPORTED, "internal: tree too deep for the depth-first walk");
